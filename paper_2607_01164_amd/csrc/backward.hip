@@ -383,14 +383,17 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
         const uint32_t f_lx = (uint32_t)__builtin_amdgcn_ds_bpermute((int)src, mlx);
         const uint32_t f_ly = (uint32_t)__builtin_amdgcn_ds_bpermute((int)src, mly);
         const uint32_t f_lz = (uint32_t)__builtin_amdgcn_ds_bpermute((int)src, mlz);
+        // the record is permuted with every lane active: ds_bpermute reads 0
+        // from an inactive lane, and a last batch of fewer rows than the
+        // wave has Gaussians would leave its source lanes inactive
+        Record fr;
+        fr.f0 = make_float4(bperm_f(src, mrec.f0.x), bperm_f(src, mrec.f0.y), bperm_f(src, mrec.f0.z), 0.0f);
+        fr.f1 = make_float4(bperm_f(src, mrec.f1.x), bperm_f(src, mrec.f1.y), bperm_f(src, mrec.f1.z), 0.0f);
+        fr.f2 = make_float4(bperm_f(src, mrec.f2.x), bperm_f(src, mrec.f2.y), bperm_f(src, mrec.f2.z), 0.0f);
         uint32_t start = 0, len = 0, rx0 = 0;
         float rpy = 0.0f, rpz = 0.0f;
         if (gr < Rw) {
             const uint32_t row = gr - (f_end - f_R);  // row within its Gaussian
-            Record fr;
-            fr.f0 = make_float4(bperm_f(src, mrec.f0.x), bperm_f(src, mrec.f0.y), bperm_f(src, mrec.f0.z), 0.0f);
-            fr.f1 = make_float4(bperm_f(src, mrec.f1.x), bperm_f(src, mrec.f1.y), bperm_f(src, mrec.f1.z), 0.0f);
-            fr.f2 = make_float4(bperm_f(src, mrec.f2.x), bperm_f(src, mrec.f2.y), bperm_f(src, mrec.f2.z), 0.0f);
             const RowRun rr = row_run<GRID>(fr, (int32_t)f_lx, (int32_t)f_ly, (int32_t)f_lz, f_nx, f_ny, row, rx, ry,
                                             rz, fdiv, q, g, bg, point_off);
             start = rr.start;
