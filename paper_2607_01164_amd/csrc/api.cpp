@@ -191,12 +191,14 @@ struct Plan {
     uint32_t *keys;      // [n] sorted cell keys (ncells = outside)
     uint32_t *order;     // [n] query ids in cell order
     uint32_t *keys_alt;  // [n]
-    uint32_t *order_alt; // [n]
+    uint32_t *order_alt; // [n] the sort's, then the refined order (launch_refine_order)
     uint32_t *point_off; // [kSub ncells + 2]
     void *radix_work;
     PointItems items;
     PlanResults res;
     size_t bytes;
+    // the order the forward and the backward take the queries in
+    const uint32_t *walk_order(int64_t n, int64_t ncells) const { return boxed_launch(n, ncells) ? order_alt : order; }
 };
 
 Plan plan_layout(void *base, int64_t n, int64_t ncells) {
@@ -209,7 +211,7 @@ Plan plan_layout(void *base, int64_t n, int64_t ncells) {
     p.order_alt = c.take<uint32_t>(m);
     p.point_off = c.take<uint32_t>((size_t)kSub * ncells + 2);
     p.radix_work = c.take<char>(radix_work_bytes(n > 0 ? n : 1, bits_for((int64_t)kSub * ncells + 1)));
-    p.items.item_off = c.take<uint32_t>((size_t)ncells + 2);
+    p.items.item_off = c.take<uint32_t>((size_t)ncells + 3);
     p.items.max_items = ncells + 1 + (n > 0 ? n : 0) / 64 + 1;
     p.items.items = c.take<uint32_t>((size_t)p.items.max_items);
     p.items.group_sum = c.take<uint64_t>((size_t)item_groups(ncells + 1) + 1);
@@ -439,6 +441,9 @@ gs_status order_queries(const char *who, const QueryParams &qp, const GridParams
     GS_TRY(launch_query_keys(qp, gp, ek, ev, radix_pass0(p.radix_work, nq, bits), stream), "query keys");
     GS_TRY(radix_sort_pairs(ek, ev, ak, av, nq, bits, p.radix_work, stream, true), "query sort");
     GS_TRY(key_offsets(p.keys, nq, p.point_off, (int64_t)kSub * gp.ncells + 1, stream), "query ranges");
+    // the sort is done with its alternate ids: they take the refined order
+    if (boxed_launch(nq, gp.ncells))
+        GS_TRY(launch_refine_order(qp, gp, p.keys, p.order, p.order_alt, p.res.pos, stream), "query places");
     *out = p;
     return GS_OK;
 }
@@ -691,8 +696,8 @@ static gs_status plan_queries(const char *who, const QueryParams &qp, const Grid
 static gs_status sample_ordered(const char *who, const gs_index *index, const QueryParams &qp, const GridParams &gp,
                                 const Plan &p, float *out_value, float *out_influence, hipStream_t stream) {
     IndexWork w = index_layout(index->work, index->n_gauss, &index->grid, index->capacity);
-    GS_TRY(launch_sample_points(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets, p.order, p.point_off, p.items,
-                                cutoff_T(index->tau), index->tau, out_value, out_influence, p.res, stream),
+    GS_TRY(launch_sample_points(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets, p.keys,
+                                p.walk_order(qp.n, gp.ncells), p.point_off, p.items, cutoff_T(index->tau), index->tau, out_value, out_influence, p.res, stream),
            who);
     return GS_OK;
 }
@@ -710,8 +715,8 @@ gs_status gs_sample(const gs_gaussians *gauss, const gs_index *index, const gs_q
     IndexWork w = index_layout(index->work, index->n_gauss, &index->grid, index->capacity);
     const float T = cutoff_T(index->tau);
     if (query->kind == GS_QUERY_GRID) {
-        GS_TRY(launch_sample_grid(qp, gp, w.rec, index->gids, index->cell_offsets, T, index->tau, out_value,
-                                  out_influence, stream),
+        GS_TRY(launch_sample_grid(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets, T, index->tau,
+                                  out_value, out_influence, stream),
                "gs_sample: grid sampler");
         return GS_OK;
     }
@@ -746,8 +751,8 @@ gs_status gs_sample_planned(const gs_gaussians *gauss, const gs_index *index, co
     const QueryParams qp = query_params(query, &index->grid);
     if (query->kind == GS_QUERY_GRID) {
         IndexWork w = index_layout(index->work, index->n_gauss, &index->grid, index->capacity);
-        GS_TRY(launch_sample_grid(qp, gp, w.rec, index->gids, index->cell_offsets, cutoff_T(index->tau), index->tau,
-                                  out_value, out_influence, stream),
+        GS_TRY(launch_sample_grid(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets,
+                                  cutoff_T(index->tau), index->tau, out_value, out_influence, stream),
                "gs_sample_planned: grid sampler");
         return GS_OK;
     }
@@ -787,7 +792,7 @@ gs_status gs_sample_gaussian_major(const gs_gaussians *gauss, const gs_index *in
     if ((st = order_queries("gs_sample_gaussian_major", qp, gp, nq, plan, plan_bytes, &p, stream)) != GS_OK)
         return st;
     GS_TRY(launch_sample_gauss_major(qp, gp, bwd_geom(gp, qp, cutoff_T(index->tau)), w.rec, w.box, w.gorder,
-                                     index->n_gauss, p.order, p.point_off,
+                                     index->n_gauss, p.walk_order(nq, gp.ncells), p.point_off,
                                      cutoff_T(index->tau), index->tau, out_value, out_influence, p.res, work, stream),
            "gs_sample_gaussian_major");
     return GS_OK;
@@ -829,7 +834,8 @@ gs_status gs_sample_backward(const gs_gaussians *gauss, const gs_index *index, c
     IndexWork w = index_layout(index->work, n, &index->grid, index->capacity);
     BwdWork bw = bwd_layout(work, index, query);
     const float T = cutoff_T(index->tau);
-    GS_TRY(launch_backward(qp, gp, bwd_geom(gp, qp, T), w.rec, w.box, w.gorder, n, index->n_pairs, p.order,
+    GS_TRY(launch_backward(qp, gp, bwd_geom(gp, qp, T), w.rec, w.box, w.gorder, n, index->n_pairs,
+                           p.walk_order(nq, gp.ncells),
                            p.point_off, p.res.pos, p.res.out, value, influence, grad_value, grad_influence, T, bw.b,
                            gauss->scale, gauss->rot, d_mean, d_scale, d_rot, d_value, d_weight, stream),
            "gs_sample_backward");

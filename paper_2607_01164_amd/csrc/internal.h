@@ -334,8 +334,8 @@ hipError_t launch_preprocess(const float *mean, const float *scale, const float 
                              uint8_t *lines, RowRec *rows, uint32_t *rbase, uint32_t *rtotal, int64_t rcap,
                              uint8_t *cell_coarse, uint64_t *count, uint64_t *block_sum, hipStream_t s);
 // A Gaussian is coarse when the cell diagonal passes kOffsetCells times its
-// largest scale: the forward's dense walk then evaluates the cells of its
-// box as U (p - mu) (see offset_planes).
+// largest scale: the forward then evaluates the cells of its box as U (p -
+// mu) instead of by offsets to the cell's centre.
 #ifndef GS_OFFSET_CELLS
 #define GS_OFFSET_CELLS 64.0
 #endif
@@ -405,12 +405,19 @@ __device__ __forceinline__ void query_position(const QueryParams &q, const GridP
 // the first sort digit's tile counts.
 hipError_t launch_query_keys(const QueryParams &q, const GridParams &g, uint32_t *keys, uint32_t *ids,
                              const RadixPass0 &pass0, hipStream_t s);
-hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint32_t *gids,
-                              const uint32_t *cell_off, float T, float tau, float *out_v, float *out_i,
-                              hipStream_t s);
+// cell_coarse: the index's per-cell flags (launch_preprocess).
+hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint8_t *cell_coarse,
+                              const uint32_t *gids, const uint32_t *cell_off, float T, float tau, float *out_v,
+                              float *out_i, hipStream_t s);
+// Whether a launch of nq ordered queries in ncells cells is boxed: its plan
+// order is then refined by place inside quarters of cells, and the plan holds
+// the positions in it (PlanResults::pos, the place in w) before the forward.
+bool boxed_launch(int64_t nq, int64_t ncells);
+hipError_t launch_refine_order(const QueryParams &q, const GridParams &g, const uint32_t *keys, const uint32_t *order,
+                               uint32_t *refined, float4 *pos, hipStream_t s);
 // Work items of the ordered-query sampler (kept in the plan).
 struct PointItems {
-    uint32_t *item_off;   // [ncells + 2]
+    uint32_t *item_off;   // [ncells + 3]
     uint32_t *items;      // [max_items]
     int64_t max_items;    // ncells + 1 + n / 64 + 1
     uint64_t *group_sum;  // [item_groups(ncells + 1) + 1] work items per 1024 buckets, (dense << 32) | sparse
@@ -418,8 +425,9 @@ struct PointItems {
 };
 // groups of 1024 buckets (plus the element after the last bucket)
 inline int64_t item_groups(int64_t nbuckets) { return (nbuckets + 1 + 1023) / 1024; }
-// The forward's results in plan order, kept in the plan for the backward:
-// position (x, y, z, 0) and (Phi, I) of the k-th query in cell order.
+// The queries' positions (x, y, z; w unused, or the place inside the quarter
+// of the cell in boxed launches) and the forward's results (Phi, I), kept in
+// the plan for the backward, both in the order the forward took.
 struct PlanResults {
     float4 *pos;
     float2 *out;
@@ -429,11 +437,10 @@ struct PlanResults {
 // ordering's last step).
 hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
                              hipStream_t s);
-// cell_coarse: the index's per-cell flags (launch_preprocess).
+// order: the plan's, the refined one in boxed launches.
 hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec,
-                                const uint8_t *cell_coarse,
-                                const uint32_t *gids,
-                                const uint32_t *cell_off, const uint32_t *order, const uint32_t *point_off,
+                                const uint8_t *cell_coarse, const uint32_t *gids, const uint32_t *cell_off,
+                                const uint32_t *keys, const uint32_t *order, const uint32_t *point_off,
                                 const PointItems &it, float T, float tau, float *out_v, float *out_i,
                                 const PlanResults &pr, hipStream_t s);
 

@@ -1,16 +1,30 @@
 // Forward sampling (paper Eq. 2 with the cutoff test of Sec. 4.1.1 and the
 // definedness rule of Sec. 4.1.3).
 //
-// Grid queries (Sec. 4.1.3, Fig. 4 C): one wavefront per (cell, 64 voxels of
-// the cell); every lane is a voxel and all lanes walk the cell's Gaussian
-// list together. The 48-byte Gaussian records are staged in the wave's LDS
-// planes 64 at a time (the paper's shared-memory batches) and read there
-// with one address for all lanes.
+// The whitened offset u = U (p - mu) of a (Gaussian, query) pair is linear in
+// the query: with offsets a = p - o from a point o of the cell and c = U (mu
+// - o), u = U a - c is a product of the 3 x 4 matrix (U, -c) with (a, 1). For
+// 16 queries and 16 Gaussians these are three 16x16x4 float32 matrix
+// products (v_mfma_f32_16x16x4_f32), chains of float32 fused multiply-adds as
+// the vector form's. They do not run beside vector work (measured: 36 cycles
+// each, added to the vector instructions' time), so they cost 27 issue slots
+// per 256 pairs where the vector form takes 24; what they save is the vector
+// form's read of every record from LDS once per 64 queries, which bounds it
+// (24 LDS cycles a record and wave, four SIMDs to an LDS), and lanes: tiles
+// hold 16 queries instead of 64.
 //
-// Voxel-list and point queries (Sec. 5.1.2): the queries are first ordered
-// by cell and, inside a cell, by quarter of the cell along x (query_keys +
-// radix sort, kept in the plan) and the work is split by cell: dense cells run like grid cells, cells of fewer queries spread
-// queries and candidates over the lanes (see k_sample_cells).
+// Grid queries (Sec. 4.1.3, Fig. 4 C): one wavefront per (cell, 64 voxels of
+// the cell), the voxels as tiles of 16 (walk_tiles). Measured against the
+// vector form: 2^27 voxels and 2^20 clustered Gaussians 5.28 -> 5.07 ms, 128^3
+// voxels and 131,072 Gaussians 109 -> 96 us.
+//
+// Voxel-list, point and jittered queries (Sec. 5.1.2): the queries are first
+// ordered by cell and, inside a cell, by quarter of the cell along x
+// (query_keys + radix sort, kept in the plan), and the work is split by cell
+// (see k_sample_cells). Where cells hold many queries on average, these are
+// also ordered by place inside the quarter (k_refine_order), and dense cells
+// are cut into boxes that meet only the candidates reaching them
+// (k_sample_dense).
 #include "expand.h"
 #include "internal.h"
 #include "radix.h"
@@ -33,7 +47,11 @@ namespace {
 // one works through the dense part.
 constexpr int kSampWaves = 1;
 constexpr int kSampBlock = kSampWaves * kWave;
-constexpr int kSampPerSimd = 7;  // waves per SIMD the point sampler is compiled for
+// Waves per SIMD the samplers are compiled for. (A bound also keeps matrix
+// products' results in ordinary registers: with the whole register file to
+// itself the compiler puts them in accumulation registers and moves each out
+// again.)
+constexpr int kSampPerSimd = 7;
 
 // Q' = Q log2(e) / 2 of a record at a point (record_q), G = 2^-Q'.
 __device__ __forceinline__ float cutoff_q(const Record &r, float px, float py, float pz) {
@@ -107,7 +125,7 @@ __device__ __forceinline__ void accumulate_off_sel(const Record &r, float ax, fl
 
 // Four consecutive work items per XCD (xcd_group): the items of one cell
 // share that XCD's L2 (C5's forward 1.6 % faster, C4's unchanged).
-constexpr uint32_t kXcdItems = 4;
+constexpr uint32_t kXcdItems = 4, kXcdDense = 2;
 
 // The centre of cell c (float32; any point of the cell would do), for a
 // wave-uniform c: kept in scalar registers.
@@ -117,6 +135,126 @@ __device__ __forceinline__ void cell_centre(const GridParams &g, uint32_t c, flo
     ox = readfirst_f(g.lo[0] + ((float)cx + 0.5f) / g.invc[0]);
     oy = readfirst_f(g.lo[1] + ((float)cy + 0.5f) / g.invc[1]);
     oz = readfirst_f(g.lo[2] + ((float)cz + 0.5f) / g.invc[2]);
+}
+
+constexpr int kDenseWaves = kWavesPerBlock;  // waves of a dense item's workgroup
+constexpr int kDensePerSimd = 6;            // its LDS holds six workgroups a CU
+constexpr uint32_t kTile = 16;              // queries of a matrix tile, and Gaussians
+
+// LDS of a dense item's workgroup. The records of up to kBlock candidates:
+// the rows (U_iz, U_iy, U_ix, -c_i) of (U, -c), in the order the matrix
+// product's fused multiply-adds take them (sums of U a stay small against c,
+// which comes last), and (w, w v). Entry kBlock is an
+// all-zero record that pads lists to whole tiles. The walk of a coarse cell
+// uses the rows' space for staged records, a quarter of it a wave
+// (wave_records).
+struct DenseLds {
+    float4 b[3][kBlock + 1];
+    float2 w[kBlock];
+    // each wave's list of the candidates that reach its queries: their
+    // entries, and their weights in list order
+    uint16_t list[kDenseWaves][kBlock + kTile];
+    float lw[kDenseWaves][kBlock + kTile], lv[kDenseWaves][kBlock + kTile];
+    uint16_t tile_start[kBlock], tile_bin[kBlock];
+    uint64_t ballot[2][kDenseWaves];
+};
+static_assert(sizeof(float4) * kRecordQuads * kWave * kDenseWaves <= sizeof(DenseLds::b), "staged records fit the rows");
+
+// LDS of a one-wave workgroup: planes of kWave rows (or staged records), the
+// rows' weights w and w v, and what their -c leave when rounded to float32.
+struct WaveLds {
+    float4 b[kRecordQuads * kWave];
+    float w[kWave], v[kWave], c[3][kWave];
+};
+
+__device__ __forceinline__ float4 *wave_records(DenseLds &L, uint32_t wave) {
+    return &L.b[0][0] + kRecordQuads * kWave * wave;
+}
+
+typedef float mfma_f4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ Record load_record(const Record *__restrict__ rec, uint32_t g) {
+    const float4 *p = (const float4 *)(rec + g);
+    Record r;
+    r.f0 = p[0];
+    r.f1 = p[1];
+    r.f2 = p[2];
+    return r;
+}
+
+// A candidate's rows into entry b[0] of planes `plane` entries apart: record
+// r about o, or the all-zero record. c is formed in float64 and rounded once;
+// rest gets what the rounding left of -c.
+__device__ __forceinline__ void stage_rows(float4 *b, uint32_t plane, bool live, const Record &r, float ox, float oy,
+                                           float oz, float (&rest)[3]) {
+    float4 b0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b1 = b0, b2 = b0;
+    rest[0] = rest[1] = rest[2] = 0.0f;
+    if (live) {
+        const double bx = (double)r.f0.x - (double)ox, by = (double)r.f0.y - (double)oy;
+        const double bz = (double)r.f0.z - (double)oz;
+        const double c0 = -((double)r.f1.x * bx + ((double)r.f1.y * by + (double)r.f1.z * bz));
+        const double c1 = -((double)r.f2.x * by + (double)r.f2.y * bz);
+        const double c2 = -((double)r.f2.z * bz);
+        b0 = make_float4(r.f1.z, r.f1.y, r.f1.x, (float)c0);
+        b1 = make_float4(r.f2.y, r.f2.x, 0.0f, (float)c1);
+        b2 = make_float4(r.f2.z, 0.0f, 0.0f, (float)c2);
+        rest[0] = (float)(c0 - (double)b0.w);
+        rest[1] = (float)(c1 - (double)b1.w);
+        rest[2] = (float)(c2 - (double)b2.w);
+    }
+    b[0] = b0;
+    b[plane] = b1;
+    b[2 * plane] = b2;
+}
+
+// Operand of the matrix products that holds a tile's queries: lane l has
+// component l / 16 of (a_z, a_y, a_x, 1) for query l % 16.
+__device__ __forceinline__ float tile_operand(uint32_t k, float ax, float ay, float az) {
+    return k == 0 ? az : (k == 1 ? ay : (k == 2 ? ax : 1.0f));
+}
+
+// The 256 pairs of 16 candidates (operands g0, g1, g2: lane l has component
+// l / 16 of the rows of candidate l % 16) and one tile of queries (operand q).
+// Lane l gets the pairs of query l % 16 with candidates 4 (l / 16) + r, r < 4,
+// whose weights are w[r] and v[r], and adds them to its sums: three matrix
+// products (96 cycles of the matrix core) beside eight vector instructions
+// per 64 pairs, where the vector form takes 14 and reads each record from LDS
+// once per 64 queries.
+// The products start from c0, c1, c2.
+__device__ __forceinline__ void tile_pairs(float q, float g0, float g1, float g2, const float4 &w, const float4 &v,
+                                           float T, float &I, float &V, mfma_f4 c0 = {0.0f, 0.0f, 0.0f, 0.0f},
+                                           mfma_f4 c1 = {0.0f, 0.0f, 0.0f, 0.0f},
+                                           mfma_f4 c2 = {0.0f, 0.0f, 0.0f, 0.0f}) {
+    const mfma_f4 u0 = __builtin_amdgcn_mfma_f32_16x16x4f32(g0, q, c0, 0, 0, 0);
+    const mfma_f4 u1 = __builtin_amdgcn_mfma_f32_16x16x4f32(g1, q, c1, 0, 0, 0);
+    const mfma_f4 u2 = __builtin_amdgcn_mfma_f32_16x16x4f32(g2, q, c2, 0, 0, 0);
+    const float wr[4] = {w.x, w.y, w.z, w.w}, vr[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float Q = fmaf_(u0[r], u0[r], fmaf_(u1[r], u1[r], u2[r] * u2[r]));
+        // selected, not branched: adding w 0 and (w v) 0 leaves the sums as
+        // they are (they start at +0; w and v are finite)
+        const float G = Q <= T ? exp2_hw(-Q) : 0.0f;
+        I = fmaf_(wr[r], G, I);
+        V = fmaf_(vr[r], G, V);
+    }
+}
+
+// a and b, each a sum per lane, added over the wave's halves: lanes 0..31 get
+// a's totals of lanes l and l + 32, lanes 32..63 b's.
+__device__ __forceinline__ float swap32_sum(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// The same over the rows of 16 of each half: even rows get a's, odd rows b's.
+__device__ __forceinline__ float swap16_sum(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Tile t's sums over its candidates for t < 4: lane l gets those of query
+// l % 16 of tile l / 16.
+__device__ __forceinline__ float tile_sum(float t0, float t1, float t2, float t3) {
+    return swap16_sum(swap32_sum(t0, t2), swap32_sum(t1, t3));
 }
 
 // Walk a wave-uniform candidate list [ja, jb) for one query per lane. The
@@ -223,35 +361,112 @@ __device__ __forceinline__ void walk_staged_r(const Record *__restrict__ rec, bo
 }
 
 
-__global__ __launch_bounds__(kSampBlock) void k_sample_grid(QueryParams q, GridParams g, const Record *__restrict__ rec,
+// A wave alone against a wave-uniform list [ja, jb): up to 64 queries, one a
+// lane at offsets (ax, ay, az) from o, tile t < NT holding lanes 16 t .. 16 t +
+// 15, with every candidate, 64 staged at a time (their records loaded ahead
+// would cost the registers of a wave in eight). Lane l gets its query's sums. A query's sums depend on its
+// cell's list only: candidate j is always the (j - ja) % 16th of its tile. The
+// products carry what float32 leaves of c: without it u had a quarter more
+// rounding errors at the cutoff than U (p - mu), with it no more (counted
+// against 64-bit sums on grids; 2 % of the walk).
+template <uint32_t NT>
+__device__ __forceinline__ void walk_tiles(WaveLds &L, uint32_t lane, const Record *__restrict__ rec,
+                                           const uint32_t *__restrict__ gids, uint32_t ja, uint32_t jb, float ax,
+                                           float ay, float az, float ox, float oy, float oz, float T, float &Io,
+                                           float &Vo) {
+    const uint32_t k = lane >> 4;
+    float q[NT], I[4] = {0.0f, 0.0f, 0.0f, 0.0f}, V[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (uint32_t t = 0; t < NT; ++t) {
+        const int src = (int)(kTile * t + (lane & 15u));
+        q[t] = tile_operand(k, __shfl(ax, src, kWave), __shfl(ay, src, kWave), __shfl(az, src, kWave));
+    }
+    const float *rows = (const float *)(L.b + (lane & 15u)) + k;
+    constexpr uint32_t plane = 4u * kWave;  // floats from one row's plane to the next
+    uint32_t gnext = 0;
+    if (ja + lane < jb) gnext = gids[ja + lane];
+    for (uint32_t c0 = ja; c0 < jb; c0 += kWave) {
+        const bool live = c0 + lane < jb;
+        Record r = {};
+        if (live) r = load_record(rec, gnext);
+        float rest[3];
+        stage_rows(L.b + lane, kWave, live, r, ox, oy, oz, rest);
+        L.c[0][lane] = rest[0];
+        L.c[1][lane] = rest[1];
+        L.c[2][lane] = rest[2];
+        L.w[lane] = live ? r.f0.w : 0.0f;
+        L.v[lane] = live ? r.f1.w : 0.0f;
+        if (c0 + kWave + lane < jb) gnext = gids[c0 + kWave + lane];
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t left = jb - c0;
+        const uint32_t groups = left >= (uint32_t)kWave ? kWave / kTile : (left + kTile - 1) / kTile;
+        for (uint32_t gr = 0; gr < groups; ++gr) {
+            const float *p = rows + 4u * kTile * gr;
+            const float g0 = p[0], g1 = p[plane], g2 = p[2 * plane];
+            const float4 w = *(const float4 *)(L.w + kTile * gr + 4u * k);
+            const float4 v = *(const float4 *)(L.v + kTile * gr + 4u * k);
+#pragma unroll
+            for (uint32_t t = 0; t < NT; ++t)
+                tile_pairs(q[t], g0, g1, g2, w, v, T, I[t], V[t], *(const mfma_f4 *)(L.c[0] + kTile * gr + 4u * k),
+                           *(const mfma_f4 *)(L.c[1] + kTile * gr + 4u * k),
+                           *(const mfma_f4 *)(L.c[2] + kTile * gr + 4u * k));
+        }
+        // every lane has read the rows before the next chunk overwrites them
+        __builtin_amdgcn_wave_barrier();
+    }
+    Io = tile_sum(I[0], I[1], I[2], I[3]);
+    Vo = tile_sum(V[0], V[1], V[2], V[3]);
+}
+
+// walk_tiles for n <= 64 queries.
+__device__ __forceinline__ void walk_lanes(uint32_t n, WaveLds &L, uint32_t lane, const Record *__restrict__ rec,
+                                           const uint32_t *__restrict__ gids, uint32_t ja, uint32_t jb, float ax,
+                                           float ay, float az, float ox, float oy, float oz, float T, float &Io,
+                                           float &Vo) {
+    if (n <= kTile)
+        walk_tiles<1>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
+    else if (n <= 2 * kTile)
+        walk_tiles<2>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
+    else if (n <= 3 * kTile)
+        walk_tiles<3>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
+    else
+        walk_tiles<4>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
+}
+
+__global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams q, GridParams g, const Record *__restrict__ rec,
+                                                        const uint8_t *__restrict__ cell_coarse,
                                                         const uint32_t *__restrict__ gids,
                                                         const uint32_t *__restrict__ cell_off, float T, float tau,
                                                         float *__restrict__ out_v, float *__restrict__ out_i) {
-    __shared__ float4 s_grec[kSampWaves][kRecordQuads * kWave];
+    __shared__ WaveLds L;
     const uint32_t rx = (uint32_t)(q.dims[0] / g.cells[0]);
     const uint32_t ry = (uint32_t)(q.dims[1] / g.cells[1]);
     const uint32_t rz = (uint32_t)(q.dims[2] / g.cells[2]);
     const uint32_t vpc = rx * ry * rz;
     const uint32_t wpc = (vpc + kWave - 1) / kWave;
-    const uint32_t lane = threadIdx.x % kWave;
-    const uint64_t wave_id =
-        (uint64_t)blockIdx.x * kSampWaves + threadIdx.x / kWave;
-    const uint64_t cell = wave_id / wpc;
-    if (cell >= (uint64_t)g.ncells) return;
-    const uint32_t chunk = (uint32_t)(wave_id - cell * wpc);
+    const uint32_t lane = threadIdx.x;
+    // ncells wpc < 2^32: at most a wave per cell and one per 64 voxels
+    const uint32_t cell = blockIdx.x / wpc;
+    const uint32_t chunk = blockIdx.x - cell * wpc;
     const uint32_t local = chunk * kWave + lane;
-    const uint32_t cx = (uint32_t)(cell % (uint32_t)g.cells[0]);
-    const uint32_t cy = (uint32_t)((cell / (uint32_t)g.cells[0]) % (uint32_t)g.cells[1]);
-    const uint32_t cz = (uint32_t)(cell / ((uint64_t)g.cells[0] * (uint32_t)g.cells[1]));
-    const uint32_t lx = local % rx, ly = (local / rx) % ry, lz = local / (rx * ry);
+    const uint32_t nx = (uint32_t)g.cells[0], ny = (uint32_t)g.cells[1];
+    const uint32_t cyz = cell / nx, cx = cell - cyz * nx, cz = cyz / ny, cy = cyz - cz * ny;
+    const uint32_t lyz = local / rx, lx = local - lyz * rx, lz = lyz / ry, ly = lyz - lz * ry;
     const int32_t vx = (int32_t)(cx * rx + lx), vy = (int32_t)(cy * ry + ly), vz = (int32_t)(cz * rz + lz);
     const float px = voxel_center(vx, g.lo[0], q.vsz[0]);
     const float py = voxel_center(vy, g.lo[1], q.vsz[1]);
     const float pz = voxel_center(vz, g.lo[2], q.vsz[2]);
-    const uint32_t j0 = __builtin_amdgcn_readfirstlane(cell_off[cell]);
-    const uint32_t j1 = __builtin_amdgcn_readfirstlane(cell_off[cell + 1]);
+    const uint32_t j0 = ((ConstU32 *)cell_off)[cell], j1 = ((ConstU32 *)cell_off)[cell + 1];
     float I = 0.0f, V = 0.0f;
-    walk_staged(rec, gids, j0, j1, lane, s_grec[threadIdx.x / kWave], px, py, pz, T, I, V);
+    if (j0 < j1) {
+        if (__builtin_amdgcn_readfirstlane(cell_coarse[cell]) != 0) {
+            walk_staged(rec, gids, j0, j1, lane, L.b, px, py, pz, T, I, V);
+        } else {
+            float ox, oy, oz;
+            cell_centre(g, cell, ox, oy, oz);
+            walk_lanes(vpc - chunk * kWave, L, lane, rec, gids, j0, j1, px - ox, py - oy, pz - oz, ox, oy, oz, T, I, V);
+        }
+    }
     if (local < vpc) {
         const uint64_t idx = (uint64_t)vx + (uint64_t)q.dims[0] * ((uint64_t)vy + (uint64_t)q.dims[1] * (uint64_t)vz);
         const bool def = I > tau;
@@ -302,6 +517,185 @@ __global__ __launch_bounds__(kBlock) void k_query_keys(QueryParams q, GridParams
     hist.finish_tile(blockIdx.x);
 }
 
+// The queries of a quarter of a cell in spatial order, for the dense cells'
+// walk: by place code, stably, inside blocks of kRefineTile consecutive
+// queries of the plan, so that runs of queries with one code prefix lie in
+// one box. Also their positions in that order, the code in the w component.
+// Bound by the random reads of 12-byte positions, which the sampler used to
+// make itself.
+constexpr int kRefineItems = 4;
+constexpr int kRefineTile = kBlock * kRefineItems;  // 1024
+// The place of a query in its quarter of a cell, bits from the top: halves
+// of the cell along z and y, quarters along z and y, the half of the quarter
+// along x, eighths along z and y. A prefix of 2 bits names a box of 1/4 x
+// 1/2 x 1/2 of the cell, one of 4 bits a cube of side 1/4.
+constexpr int kPlaceBits = 7;
+// A block is left as it is when no run of one quarter is longer than this.
+constexpr int kRefineRun = 16;
+
+__device__ __forceinline__ uint32_t place_code(const GridParams &g, uint32_t key, float px, float py, float pz) {
+    const uint32_t c = key / kSub, nx = (uint32_t)g.cells[0], ny = (uint32_t)g.cells[1];
+    const uint32_t cyz = c / nx, cx = c - cyz * nx, cz = cyz / ny, cy = cyz - cz * ny;
+    // eighths of the cell along each axis, 0..7 (of a quarter along x: 0, 1)
+    const float tx = (px - g.lo[0]) * g.invc[0] - (float)cx, ty = (py - g.lo[1]) * g.invc[1] - (float)cy;
+    const float tz = (pz - g.lo[2]) * g.invc[2] - (float)cz;
+    const uint32_t ex = (uint32_t)fminf(fmaxf(tx * 8.0f - 2.0f * (float)(key % kSub), 0.0f), 1.0f);
+    const uint32_t ey = (uint32_t)fminf(fmaxf(ty * 8.0f, 0.0f), 7.0f);
+    const uint32_t ez = (uint32_t)fminf(fmaxf(tz * 8.0f, 0.0f), 7.0f);
+    return ((ez >> 2) << 6) | ((ey >> 2) << 5) | (((ez >> 1) & 1u) << 4) | (((ey >> 1) & 1u) << 3) | (ex << 2) |
+           ((ez & 1u) << 1) | (ey & 1u);
+}
+
+// Stable places of the block's kRefineTile elements by digit (< 2^bits):
+// element (wave, i, lane), in that order, gets slot[i]. cnt: kWavesPerBlock
+// << bits words of LDS; waves rank their rows with one ballot per digit bit
+// and a running count per digit, as the radix sort does.
+__device__ __forceinline__ void block_split(const uint32_t (&d)[kRefineItems], int bits, uint32_t *cnt, uint32_t *scan,
+                                            uint32_t (&slot)[kRefineItems]) {
+    const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, nd = 1u << bits;
+    for (uint32_t i = tid; i < kWavesPerBlock * nd; i += kBlock) cnt[i] = 0;
+    __syncthreads();
+    const uint64_t lt = lane == 0 ? 0ull : ~0ull >> (64 - lane);
+    uint32_t *mine = cnt + wave * nd;
+#pragma unroll
+    for (int i = 0; i < kRefineItems; ++i) {
+        uint64_t m = ~0ull;
+        for (int b = 0; b < bits; ++b) {
+            const bool bit = (d[i] >> b) & 1u;
+            const uint64_t bm = __ballot(bit);
+            m &= bit ? bm : ~bm;
+        }
+        const uint32_t before = (uint32_t)__popcll(m & lt);
+        const uint32_t base = mine[d[i]];
+        // every lane of the wave has read the counter before its leader writes
+        __builtin_amdgcn_wave_barrier();
+        if (before == 0) mine[d[i]] = base + (uint32_t)__popcll(m);
+        __builtin_amdgcn_wave_barrier();
+        slot[i] = base + before;
+    }
+    __syncthreads();
+    // exclusive scan over (digit, wave): thread t takes nd / kBlock digits
+    const uint32_t per = (nd + kBlock - 1) / kBlock;
+    uint32_t s = 0;
+    for (uint32_t j = 0; j < per; ++j) {
+        const uint32_t dg = tid * per + j;
+        if (dg < nd)
+            for (uint32_t w = 0; w < kWavesPerBlock; ++w) s += cnt[w * nd + dg];
+    }
+    uint32_t tot;
+    uint32_t run = block_excl_scan(s, scan, &tot);
+    for (uint32_t j = 0; j < per; ++j) {
+        const uint32_t dg = tid * per + j;
+        if (dg < nd)
+            for (uint32_t w = 0; w < kWavesPerBlock; ++w) {
+                const uint32_t t = cnt[w * nd + dg];
+                cnt[w * nd + dg] = run;
+                run += t;
+            }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kRefineItems; ++i) slot[i] += mine[d[i]];
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kBlock) void k_refine_order(QueryParams q, GridParams g,
+                                                         const uint32_t *__restrict__ keys,
+                                                         const uint32_t *__restrict__ order,
+                                                         uint32_t *__restrict__ refined, float4 *__restrict__ pos) {
+    __shared__ float4 s_pos[kRefineTile];
+    __shared__ uint32_t s_pid[kRefineTile];
+    __shared__ uint32_t s_cnt[kWavesPerBlock * kRefineTile];  // up to kRefineTile runs
+    __shared__ uint16_t s_run[kRefineTile], s_at[kRefineTile];
+    __shared__ uint32_t s_scan[kWavesPerBlock];
+    const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int64_t base = (int64_t)blockIdx.x * kRefineTile;
+    const uint32_t have = q.n - base < kRefineTile ? (uint32_t)(q.n - base) : (uint32_t)kRefineTile;
+    uint32_t pid[kRefineItems], code[kRefineItems], starts = 0;
+    float4 p[kRefineItems];
+    bool first[kRefineItems];
+    bool longrun = false;
+#pragma unroll
+    for (int i = 0; i < kRefineItems; ++i) {
+        const uint32_t e = wave * (kWave * kRefineItems) + (uint32_t)i * kWave + lane;
+        pid[i] = 0;
+        code[i] = 0;
+        first[i] = false;
+        p[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (e < have) {
+            const uint32_t key = keys[base + e];
+            pid[i] = order[base + e];
+            first[i] = e == 0 || keys[base + e - 1] != key;
+            longrun = longrun || (e + kRefineRun < have && keys[base + e + kRefineRun] == key);
+            bool valid;
+            query_position(q, g, pid[i], p[i].x, p[i].y, p[i].z, valid);
+            if (key < kSub * (uint32_t)g.ncells) code[i] = place_code(g, key, p[i].x, p[i].y, p[i].z);
+            p[i].w = __uint_as_float(code[i]);
+        } else {
+            first[i] = e == have;  // the elements past the end are a last run
+        }
+        starts += (uint32_t)__popcll(__ballot(first[i]));
+    }
+    if (__syncthreads_or(longrun) == 0) {
+#pragma unroll
+        for (int i = 0; i < kRefineItems; ++i) {
+            const uint32_t e = wave * (kWave * kRefineItems) + (uint32_t)i * kWave + lane;
+            if (e < have) {
+                refined[base + e] = pid[i];
+                pos[base + e] = p[i];
+            }
+        }
+        return;
+    }
+    // runs in order, then each by place: stable splits by place and by run
+    if (lane == 0) s_scan[wave] = starts;
+    __syncthreads();
+    uint32_t run = 0, nruns = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < (uint32_t)kWavesPerBlock; ++w) {
+        if (w < wave) run += s_scan[w];
+        nruns += s_scan[w];
+    }
+    __syncthreads();
+    const uint64_t le = ~0ull >> (63 - lane);
+#pragma unroll
+    for (int i = 0; i < kRefineItems; ++i) {
+        const uint32_t e = wave * (kWave * kRefineItems) + (uint32_t)i * kWave + lane;
+        const uint64_t m = __ballot(first[i]);
+        s_run[e] = (uint16_t)(run + (uint32_t)__popcll(m & le) - 1u);
+        run += (uint32_t)__popcll(m);
+        s_pos[e] = p[i];
+        s_pid[e] = pid[i];
+    }
+    uint32_t slot[kRefineItems];
+    block_split(code, kPlaceBits, s_cnt, s_scan, slot);
+#pragma unroll
+    for (int i = 0; i < kRefineItems; ++i)
+        s_at[slot[i]] = (uint16_t)(wave * (kWave * kRefineItems) + (uint32_t)i * kWave + lane);
+    __syncthreads();
+    if (nruns > 1) {
+        uint32_t d[kRefineItems], el[kRefineItems];
+#pragma unroll
+        for (int i = 0; i < kRefineItems; ++i) {
+            el[i] = s_at[wave * (kWave * kRefineItems) + (uint32_t)i * kWave + lane];
+            d[i] = s_run[el[i]];
+        }
+        block_split(d, 32 - __builtin_clz(nruns - 1u), s_cnt, s_scan, slot);
+#pragma unroll
+        for (int i = 0; i < kRefineItems; ++i) s_at[slot[i]] = (uint16_t)el[i];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < kRefineItems; ++i) {
+        const uint32_t e = (uint32_t)i * kBlock + tid;
+        if (e < have) {
+            const uint32_t at = s_at[e];
+            refined[base + e] = s_pid[at];
+            pos[base + e] = s_pos[at];
+        }
+    }
+}
+
 // Work items of the ordered-query sampler: one per cell holding fewer than
 // 2 kDenseMin queries, one per dense item (64 or 128 queries, see
 // dense_item_queries) of a denser cell. The bucket of queries outside the
@@ -318,6 +712,11 @@ constexpr uint32_t kDenseMin = 32;
 // of clustered points, runs 11 % faster with one; 218, 10^8 points, 19 %
 // faster with two).
 constexpr uint32_t kDenseBalance = 32;
+// Queries of a boxed launch's dense items, each taken by a workgroup whose
+// waves share the cell's records in LDS. Sixteen tiles, one pass of four
+// waves with four tiles each, hold 256 queries when every tile is full; tiles
+// do not cross boxes, so 192 fill them about as far as they go.
+constexpr uint32_t kBoxedQ = 192;
 constexpr uint32_t kChunkB = 8;  // queries evaluated together by a sparse-cell item
 constexpr uint32_t kRowsMin = 4;                 // from this many queries a cell uses 4 query rows
 constexpr uint32_t kRowsMax = (kDenseMin + 3) / 4;  // queries per row at most
@@ -359,7 +758,7 @@ __global__ __launch_bounds__(kBlock) void k_item_sums(const uint32_t *__restrict
 }
 
 // item_off[c] for c <= nbuckets: the first item of bucket c (item_off[nbuckets]
-// = the total), and the item list: item_off[c] .. item_off[c] + items(c) - 1
+// = the total, followed by the dense buckets' total), and the item list: item_off[c] .. item_off[c] + items(c) - 1
 // name bucket c. group_sum: the groups' sums, or (scanned) their exclusive
 // prefixes followed by the total.
 __global__ __launch_bounds__(kBlock) void k_item_offsets(const uint32_t *__restrict__ point_off, int64_t nbuckets,
@@ -403,7 +802,10 @@ __global__ __launch_bounds__(kBlock) void k_item_offsets(const uint32_t *__restr
         const uint32_t first = dense ? (uint32_t)(run >> 32) : dense_total + (uint32_t)run;
         const uint32_t cnt = dense ? (uint32_t)(v[i] >> 32) : (uint32_t)v[i];
         if (c < nbuckets) item_off[c] = first;
-        if (c == nbuckets) item_off[c] = dense_total + (uint32_t)total;
+        if (c == nbuckets) {
+            item_off[c] = dense_total + (uint32_t)total;
+            item_off[c + 1] = dense_total;
+        }
         for (uint32_t k = 0; k < cnt; ++k)
             if ((int64_t)(first + k) < max_items) items[first + k] = (uint32_t)c;
         run += v[i];
@@ -432,6 +834,16 @@ __device__ __forceinline__ void write_out(float I, float V, float tau, bool work
     out_i[pid] = inf;
     pr.pos[k] = make_float4(px, py, pz, 0.0f);
     pr.out[k] = make_float2(phi, inf);
+}
+
+// The same where the plan holds the positions already (boxed launches).
+__device__ __forceinline__ void write_out(float I, float V, float tau, uint32_t pid, uint32_t k, float *out_v,
+                                          float *out_i, float2 *plan_out) {
+    const bool def = I > tau;
+    const float phi = def ? V / I : 0.0f, inf = def ? I : 0.0f;
+    out_v[pid] = phi;
+    out_i[pid] = inf;
+    plan_out[k] = make_float2(phi, inf);
 }
 
 // Sum over the SL lanes of a candidate-slot row (16: DPP row sum; 8: quad
@@ -570,6 +982,290 @@ __device__ __forceinline__ void dense_item(uint32_t lane, uint32_t qa, uint32_t 
                       out_v, out_i, pr);
 }
 
+// A launch is boxed when its cells hold kBoxedMean queries or more on
+// average: the queries are ordered by place too (k_refine_order) and dense
+// cells are cut into boxes, prefixes of the place code (dense_level: how many
+// of its bits; quarters of the cell along x at 0). A tile holds queries of
+// one box, and meets only the candidates whose ellipsoid can reach the box.
+// The more queries a cell has, the finer its boxes: each level tests about
+// half the pairs of the one before, and a box should fill a tile; cells of
+// fewer than kLevel2Queries are one box. The level depends on the cell's
+// count only and the boxes on the grid, so a query's sums do not depend on
+// how the queries were split into items.
+// Measured, forward with its query ordering: 10^8 clustered points in 64^3
+// cells (381 a cell) 35.3 ms without boxes and 30.9 with them; 2^21 clustered points in 64^3 (8 a cell)
+// 1.17 ms without boxes and 1.24 with them, most cells having no use for the
+// order by place.
+constexpr int64_t kBoxedMean = 64;
+constexpr uint32_t kLevel2Queries = 320, kLevel4Queries = 1536;
+constexpr uint32_t kWholeCell = 32;  // no level: one box
+__device__ __forceinline__ uint32_t dense_level(uint32_t n) {
+    return n < kLevel2Queries ? kWholeCell : (n < kLevel4Queries ? 2u : 4u);
+}
+
+// A box of the cell about its centre: centre and half extents, the latter
+// widened by slack (the queries' places are computed in float32).
+struct Box3 {
+    float cx, cy, cz, hx, hy, hz;
+};
+
+// bin: quarter along x, then `level` bits of the place code (z and y halves,
+// z and y quarters).
+__device__ __forceinline__ Box3 cell_box(uint32_t bin, uint32_t level, float wx, float wy, float wz,
+                                         const float (&slack)[3]) {
+    Box3 b;
+    if (level == kWholeCell) {
+        b.cx = b.cy = b.cz = 0.0f;
+        b.hx = 0.5f * wx + slack[0];
+        b.hy = 0.5f * wy + slack[1];
+        b.hz = 0.5f * wz + slack[2];
+        return b;
+    }
+    const uint32_t qx = bin >> level;
+    uint32_t iz = 0, iy = 0;
+    float parts = 1.0f;
+    if (level == 2) {
+        iz = (bin >> 1) & 1u;
+        iy = bin & 1u;
+        parts = 2.0f;
+    } else if (level == 4) {
+        iz = ((bin >> 3) & 1u) * 2u + ((bin >> 1) & 1u);
+        iy = ((bin >> 2) & 1u) * 2u + (bin & 1u);
+        parts = 4.0f;
+    }
+    b.hx = 0.125f * wx;
+    b.hy = 0.5f * wy / parts;
+    b.hz = 0.5f * wz / parts;
+    b.cx = (2.0f * (float)qx + 1.0f) * b.hx - 0.5f * wx;
+    b.cy = (2.0f * (float)iy + 1.0f) * b.hy - 0.5f * wy;
+    b.cz = (2.0f * (float)iz + 1.0f) * b.hz - 0.5f * wz;
+    b.hx += slack[0];
+    b.hy += slack[1];
+    b.hz += slack[2];
+    return b;
+}
+
+// The staged candidates [0, cnt) whose ellipsoid may reach the box, in order,
+// into the wave's list, padded with the all-zero record to whole tiles;
+// returns their number. Each component of u over the box lies within
+// |U_i| h of its value at the box's centre, so Q' is at least the sum of the
+// squares that are left; Tm is the cutoff widened for the rounding of both.
+__device__ __forceinline__ uint32_t list_reaching(DenseLds &L, uint32_t wave, uint32_t lane, uint32_t cnt,
+                                                  const Box3 &x, float Tm) {
+    uint16_t *list = L.list[wave];
+    uint32_t S = 0;
+    for (uint32_t c = 0; c < cnt; c += kWave) {
+        const uint32_t j = c + lane;
+        const float4 r0 = L.b[0][j], r1 = L.b[1][j], r2 = L.b[2][j];
+        const float e0 = fmaf_(r0.z, x.cx, fmaf_(r0.y, x.cy, fmaf_(r0.x, x.cz, r0.w)));
+        const float e1 = fmaf_(r1.y, x.cy, fmaf_(r1.x, x.cz, r1.w));
+        const float e2 = fmaf_(r2.x, x.cz, r2.w);
+        const float h0 = fmaf_(fabsf(r0.z), x.hx, fmaf_(fabsf(r0.y), x.hy, fabsf(r0.x) * x.hz));
+        const float h1 = fmaf_(fabsf(r1.y), x.hy, fabsf(r1.x) * x.hz);
+        const float h2 = fabsf(r2.x) * x.hz;
+        const float d0 = fmaxf(fabsf(e0) - h0, 0.0f), d1 = fmaxf(fabsf(e1) - h1, 0.0f);
+        const float d2 = fmaxf(fabsf(e2) - h2, 0.0f);
+        const bool in = j < cnt && !(fmaf_(d0, d0, fmaf_(d1, d1, d2 * d2)) > Tm);
+        const uint64_t m = __ballot(in);
+        if (in) {
+            const uint32_t at =
+                S + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            const float2 w = L.w[j];
+            list[at] = (uint16_t)j;
+            L.lw[wave][at] = w.x;
+            L.lv[wave][at] = w.y;
+        }
+        S += (uint32_t)__popcll(m);
+    }
+    if (lane < kTile) {
+        list[S + lane] = (uint16_t)kBlock;
+        L.lw[wave][S + lane] = L.lv[wave][S + lane] = 0.0f;
+    }
+    __builtin_amdgcn_wave_barrier();
+    return S;
+}
+
+// A dense cell's work item of a boxed launch: queries [qa, qa + qn) of the
+// plan, qn <= kBoxedQ,
+// by the whole workgroup. The queries are cut into tiles of up to 16 that do
+// not cross a box (found with ballots over the queries' bins), at most
+// kSlots of them to a wave and pass. The cell's records are staged kBlock at
+// a time; each wave lists the ones that reach its tiles' box, and takes the
+// list 16 candidates at a time.
+constexpr uint32_t kSlots = 4;
+__device__ __forceinline__ void dense_item(DenseLds &L, uint32_t wave, uint32_t lane, uint32_t qa, uint32_t qn,
+                                           uint32_t n, uint32_t ja, uint32_t jb, uint32_t c, const GridParams &g,
+                                           const Record *__restrict__ rec, const uint32_t *__restrict__ gids,
+                                           const uint32_t *__restrict__ keys, const uint32_t *__restrict__ order,
+                                           const float4 *__restrict__ pos, float T, float tau,
+                                           float *__restrict__ out_v, float *__restrict__ out_i,
+                                           float2 *__restrict__ plan_out) {
+    const uint32_t tid = threadIdx.x, level = dense_level(n);
+    float ox, oy, oz;
+    cell_centre(g, c, ox, oy, oz);
+    const float wx = 1.0f / g.invc[0], wy = 1.0f / g.invc[1], wz = 1.0f / g.invc[2];
+    const float slack[3] = {0x1p-19f * (fabsf(g.lo[0]) + fabsf(g.hi[0]) + wx),
+                            0x1p-19f * (fabsf(g.lo[1]) + fabsf(g.hi[1]) + wy),
+                            0x1p-19f * (fabsf(g.lo[2]) + fabsf(g.hi[2]) + wz)};
+    const float Tm = T * (1.0f + 0x1p-14f);
+    // tiles: a query starts one at the start of its run of one bin, and 16,
+    // 32, ... queries into it
+    uint32_t bin = 0;
+    bool start = false;
+    if (level == kWholeCell) {
+        start = tid == 0;
+    } else if (tid < qn) {
+        const uint32_t shift = (uint32_t)kPlaceBits - level;
+        auto bin_at = [&](uint32_t k) {
+            return ((keys[k] % kSub) << level) | (__float_as_uint(pos[k].w) >> shift);
+        };
+        bin = bin_at(qa + tid);
+        start = tid == 0 || bin_at(qa + tid - 1) != bin;
+    }
+    const uint64_t le = ~0ull >> (63 - lane);
+    const uint64_t sm = __ballot(start);
+    if (lane == 0) L.ballot[0][wave] = sm;
+    __syncthreads();
+    uint32_t rs = 0;  // start of the query's run
+    for (uint32_t w = 0; w <= wave; ++w) {
+        const uint64_t m = w == wave ? (sm & le) : L.ballot[0][w];
+        if (m != 0) rs = kWave * w + 63u - (uint32_t)__builtin_clzll(m);
+    }
+    const bool head = tid < qn && ((tid - rs) % kTile) == 0;
+    const uint64_t hm = __ballot(head);
+    if (lane == 0) L.ballot[1][wave] = hm;
+    __syncthreads();
+    uint32_t before = 0, nt = 0;
+    for (uint32_t w = 0; w < (uint32_t)kDenseWaves; ++w) {
+        const uint32_t cnt = (uint32_t)__popcll(L.ballot[1][w]);
+        if (w < wave) before += cnt;
+        nt += cnt;
+    }
+    if (head) {
+        const uint32_t t = before + (uint32_t)__popcll(hm & le) - 1u;
+        L.tile_start[t] = (uint16_t)tid;
+        L.tile_bin[t] = (uint16_t)bin;
+    }
+    __syncthreads();
+    const uint32_t k = lane >> 4;
+    const uint32_t npass = (nt + kSlots * kDenseWaves - 1) / (kSlots * kDenseWaves);
+    const uint32_t per = (nt + npass - 1) / npass;
+    for (uint32_t pass = 0; pass < npass; ++pass) {
+        const uint32_t t0 = pass * per, tn = nt - t0 < per ? nt - t0 : per;
+        const uint32_t ta = t0 + tn * wave / kDenseWaves, tb = t0 + tn * (wave + 1) / kDenseWaves;
+        float qt[kSlots], I[kSlots], V[kSlots];
+        uint32_t ts[kSlots], tc[kSlots], tbin[kSlots];
+#pragma unroll
+        for (uint32_t t = 0; t < kSlots; ++t) {
+            ts[t] = tc[t] = 0;
+            tbin[t] = 0xFFFFFFFFu;
+            qt[t] = I[t] = V[t] = 0.0f;
+            if (ta + t < tb) {
+                ts[t] = __builtin_amdgcn_readfirstlane(L.tile_start[ta + t]);
+                tbin[t] = __builtin_amdgcn_readfirstlane(L.tile_bin[ta + t]);
+                const uint32_t end =
+                    ta + t + 1 < nt ? __builtin_amdgcn_readfirstlane(L.tile_start[ta + t + 1]) : qn;
+                tc[t] = end - ts[t];
+                // lanes past the tile's last query take that query again
+                const uint32_t i = (lane & 15u) < tc[t] ? (lane & 15u) : tc[t] - 1u;
+                const float4 p = pos[qa + ts[t] + i];
+                qt[t] = tile_operand(k, p.x - ox, p.y - oy, p.z - oz);
+            }
+        }
+        Record r = {};
+        if (ja + tid < jb) r = load_record(rec, gids[ja + tid]);
+        for (uint32_t c0 = ja; c0 < jb; c0 += kBlock) {
+            __syncthreads();  // every wave has read the chunk before
+            float rest[3];  // not carried: boxes are small
+            stage_rows(&L.b[0][tid], kBlock + 1, c0 + tid < jb, r, ox, oy, oz, rest);
+            L.w[tid] = make_float2(r.f0.w, r.f1.w);
+            const uint32_t cn = c0 + kBlock;
+            if (cn + tid < jb) r = load_record(rec, gids[cn + tid]);
+            __syncthreads();
+            const uint32_t cnt = jb - c0 < (uint32_t)kBlock ? jb - c0 : (uint32_t)kBlock;
+            uint32_t S = 0;
+#pragma unroll
+            for (uint32_t t = 0; t < kSlots; ++t) {
+                if (tbin[t] == 0xFFFFFFFFu) continue;
+                if (t == 0 || tbin[t] != tbin[t - 1])
+                    S = list_reaching(L, wave, lane, cnt, cell_box(tbin[t], level, wx, wy, wz, slack), Tm);
+                const uint16_t *list = L.list[wave] + (lane & 15u);
+                const float *lw = L.lw[wave] + 4u * k, *lv = L.lv[wave] + 4u * k;
+                for (uint32_t s = 0; s < S; s += kTile) {
+                    const float *p = (const float *)&L.b[0][list[s]] + k;
+                    constexpr uint32_t plane = 4u * (kBlock + 1);
+                    tile_pairs(qt[t], p[0], p[plane], p[2 * plane], *(const float4 *)(lw + s),
+                               *(const float4 *)(lv + s), T, I[t], V[t]);
+                }
+            }
+        }
+        // lane l writes query l % 16 of tile l / 16
+        static_assert(kSlots == 4, "a tile for every row of 16 lanes");
+        const float Io = tile_sum(I[0], I[1], I[2], I[3]), Vo = tile_sum(V[0], V[1], V[2], V[3]);
+        const uint32_t qs = k == 0 ? ts[0] : (k == 1 ? ts[1] : (k == 2 ? ts[2] : ts[3]));
+        const uint32_t qc = k == 0 ? tc[0] : (k == 1 ? tc[1] : (k == 2 ? tc[2] : tc[3]));
+        const uint32_t i = lane & 15u;
+        if (i < qc) write_out(Io, Vo, tau, order[qa + qs + i], qa + qs + i, out_v, out_i, plan_out);
+    }
+}
+
+struct CellItem {
+    uint32_t c, chunk, pa, n, ja, jb;
+    bool coarse;
+};
+
+__device__ __forceinline__ CellItem cell_item(uint32_t w, uint32_t ncells, const uint8_t *cell_coarse,
+                                              const uint32_t *cell_off, const uint32_t *point_off,
+                                              const uint32_t *item_off, const uint32_t *items) {
+    CellItem it;
+    it.c = ((ConstU32 *)items)[w];
+    it.chunk = w - ((ConstU32 *)item_off)[it.c];
+    it.pa = ((ConstU32 *)point_off)[kSub * it.c];
+    it.n = ((ConstU32 *)point_off)[it.c < ncells ? kSub * (it.c + 1) : kSub * it.c + 1] - it.pa;
+    it.ja = it.jb = 0;
+    it.coarse = false;
+    if (it.c < ncells) {
+        it.ja = ((ConstU32 *)cell_off)[it.c];
+        it.jb = ((ConstU32 *)cell_off)[it.c + 1];
+        it.coarse = __builtin_amdgcn_readfirstlane(cell_coarse[it.c]) != 0;
+    }
+    return it;
+}
+
+__global__ __launch_bounds__(kBlock, kDensePerSimd) void k_sample_dense(
+    GridParams g, const Record *__restrict__ rec, const uint8_t *__restrict__ cell_coarse,
+    const uint32_t *__restrict__ gids, const uint32_t *__restrict__ cell_off, const uint32_t *__restrict__ point_off,
+    const uint32_t *__restrict__ keys, const uint32_t *__restrict__ order, const uint32_t *__restrict__ item_off,
+    const uint32_t *__restrict__ items, float T, float tau, float *__restrict__ out_v, float *__restrict__ out_i,
+    const float4 *__restrict__ pos, float2 *__restrict__ plan_out) {
+    __shared__ DenseLds L;
+    const uint32_t lane = threadIdx.x % kWave;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t ncells = (uint32_t)g.ncells;
+    const uint32_t w = xcd_group<kXcdDense>(blockIdx.x, gridDim.x);
+    if (w >= ((ConstU32 *)item_off)[ncells + 2]) return;
+    const CellItem it = cell_item(w, ncells, cell_coarse, cell_off, point_off, item_off, items);
+    const uint32_t nit = (it.n + kBoxedQ - 1) / kBoxedQ;
+    const uint32_t per = (it.n + nit - 1) / nit;
+    const uint32_t qa = it.pa + it.chunk * per;
+    const uint32_t left = it.pa + it.n - qa, qn = left < per ? left : per;
+    if (!it.coarse && it.ja < it.jb) {
+        if (threadIdx.x == 0) {  // the record that pads the lists
+            L.b[0][kBlock] = L.b[1][kBlock] = L.b[2][kBlock] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        dense_item(L, wave, lane, qa, qn, it.n, it.ja, it.jb, it.c, g, rec, gids, keys, order, pos, T, tau, out_v,
+                   out_i, plan_out);
+        return;
+    }
+    // lanes are queries (an empty list leaves their sums at 0)
+    const uint32_t i = threadIdx.x;
+    float4 p = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (i < qn) p = pos[qa + i];
+    float I = 0.0f, V = 0.0f;
+    if (kWave * wave < qn) walk_staged(rec, gids, it.ja, it.jb, lane, wave_records(L, wave), p.x, p.y, p.z, T, I, V);
+    if (i < qn) write_out(I, V, tau, order[qa + i], qa + i, out_v, out_i, plan_out);
+}
+
 // One wavefront per item, by the queries n of the cell:
 //  * n >= 64: lanes are queries, up to dense_q / 64 each (dense_q
 //    queries per item, a cell's queries split evenly over its items), and
@@ -589,7 +1285,7 @@ __global__ __launch_bounds__(kSampBlock, kSampPerSimd) void k_sample_cells(Query
                                                          const uint32_t *__restrict__ order,
                                                          const uint32_t *__restrict__ item_off,
                                                          const uint32_t *__restrict__ items, int64_t max_items,
-                                                         uint32_t dense_q, float T, float tau,
+                                                         uint32_t dense_q, bool boxed, float T, float tau,
                                                          float *__restrict__ out_v, float *__restrict__ out_i,
                                                          PlanResults pr) {
     // per wave: the records of 64 candidates, as three 1 KiB planes of
@@ -598,7 +1294,9 @@ __global__ __launch_bounds__(kSampBlock, kSampPerSimd) void k_sample_cells(Query
     const uint32_t lane = threadIdx.x % kWave;
     const uint32_t ncells = (uint32_t)g.ncells;
     const uint32_t bid = xcd_group<kXcdItems>(blockIdx.x, gridDim.x);
-    const uint64_t w = (uint64_t)bid * kSampWaves + threadIdx.x / kWave;
+    // a boxed launch's dense items, the first of the list, are k_sample_dense's
+    const uint64_t w =
+        (uint64_t)bid * kSampWaves + threadIdx.x / kWave + (boxed ? ((ConstU32 *)item_off)[ncells + 2] : 0u);
     const uint32_t tot = ((ConstU32 *)item_off)[ncells + 1];
     const uint64_t total = tot < (uint64_t)max_items ? tot : (uint64_t)max_items;
     if (w >= total) return;
@@ -766,26 +1464,28 @@ hipError_t launch_query_keys(const QueryParams &q, const GridParams &g, uint32_t
     return hipGetLastError();
 }
 
-hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint32_t *gids,
-                              const uint32_t *cell_off, float T, float tau, float *out_v, float *out_i,
-                              hipStream_t s) {
+hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint8_t *cell_coarse,
+                              const uint32_t *gids, const uint32_t *cell_off, float T, float tau, float *out_v,
+                              float *out_i, hipStream_t s) {
     const int64_t vpc = (int64_t)(q.dims[0] / g.cells[0]) * (q.dims[1] / g.cells[1]) * (q.dims[2] / g.cells[2]);
     const int64_t wpc = (vpc + kWave - 1) / kWave;
-    const int64_t waves = g.ncells * wpc;
-    const int64_t blocks = (waves + kSampWaves - 1) / kSampWaves;
+    const int64_t blocks = g.ncells * wpc;
     if (blocks <= 0) return hipSuccess;
     prof_begin("sample_grid", s);
-    hipLaunchKernelGGL(k_sample_grid, dim3((uint32_t)blocks), dim3(kSampBlock), 0, s, q, g, rec, gids, cell_off, T, tau,
-                       out_v, out_i);
+    hipLaunchKernelGGL(k_sample_grid, dim3((uint32_t)blocks), dim3(kWave), 0, s, q, g, rec, cell_coarse, gids,
+                       cell_off, T, tau, out_v, out_i);
     prof_end("sample_grid", s);
     return hipGetLastError();
 }
 
-// Queries per dense work item for nq ordered queries on the current device:
-// 128 (two a lane) from kDenseBalance items per wave slot of the chip at
-// 64, else 64. The item list and the sampler both take it from nq, so they
-// agree.
-static uint32_t dense_item_queries(int64_t nq) {
+bool boxed_launch(int64_t nq, int64_t ncells) { return nq >= kBoxedMean * ncells; }
+
+// Queries per dense work item for nq ordered queries in ncells cells on the
+// current device: kBoxedQ in a boxed launch; else 128 (two a lane) from
+// kDenseBalance items per wave slot of the chip at 64, else 64. The item list
+// and the sampler both take it from nq and the grid, so they agree.
+static uint32_t dense_item_queries(int64_t nq, int64_t ncells) {
+    if (boxed_launch(nq, ncells)) return kBoxedQ;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
@@ -799,7 +1499,7 @@ static uint32_t dense_item_queries(int64_t nq) {
 hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
                              hipStream_t s) {
     if (nq <= 0) return hipSuccess;
-    const uint32_t dense_q = dense_item_queries(nq);
+    const uint32_t dense_q = dense_item_queries(nq, g.ncells);
     const int64_t nbuckets = g.ncells + 1;  // cells and the outside bucket
     // buckets 0..nbuckets-1 and one empty element after them (its offset is the total)
     const int64_t ngroups = (nbuckets + 1 + kItemGroup - 1) / kItemGroup;
@@ -819,17 +1519,37 @@ hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *po
     return e;
 }
 
-hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec, const uint8_t *cell_coarse,
-                                const uint32_t *gids, const uint32_t *cell_off, const uint32_t *order, const uint32_t *point_off,
+hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec,
+                                const uint8_t *cell_coarse, const uint32_t *gids, const uint32_t *cell_off,
+                                const uint32_t *keys, const uint32_t *order, const uint32_t *point_off,
                                 const PointItems &it, float T, float tau, float *out_v, float *out_i,
                                 const PlanResults &pr, hipStream_t s) {
     if (q.n <= 0) return hipSuccess;
+    const bool boxed = boxed_launch(q.n, g.ncells);
     prof_begin("sample_points", s);
-    hipLaunchKernelGGL(k_sample_cells, dim3((uint32_t)((it.max_items + kSampWaves - 1) / kSampWaves)),
-                       dim3(kSampBlock), 0, s, q, g, rec, cell_coarse, gids, cell_off, point_off, order, it.item_off,
-                       it.items,
-                       it.max_items, dense_item_queries(q.n), T, tau, out_v, out_i, pr);
+    // dense cells hold at least 64 queries
+    if (boxed && q.n >= 2 * (int64_t)kDenseMin) {
+        hipLaunchKernelGGL(k_sample_dense, dim3((uint32_t)(q.n / (2 * kDenseMin))), dim3(kBlock), 0, s, g, rec,
+                           cell_coarse, gids, cell_off, point_off, keys, order, it.item_off, it.items, T, tau, out_v,
+                           out_i, pr.pos, pr.out);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    const int64_t waves = boxed ? g.ncells + 1 : it.max_items;
+    hipLaunchKernelGGL(k_sample_cells, dim3((uint32_t)((waves + kSampWaves - 1) / kSampWaves)), dim3(kSampBlock), 0, s,
+                       q, g, rec, cell_coarse, gids, cell_off, point_off, order, it.item_off, it.items, it.max_items,
+                       dense_item_queries(q.n, g.ncells), boxed, T, tau, out_v, out_i, pr);
     prof_end("sample_points", s);
+    return hipGetLastError();
+}
+
+hipError_t launch_refine_order(const QueryParams &q, const GridParams &g, const uint32_t *keys, const uint32_t *order,
+                               uint32_t *refined, float4 *pos, hipStream_t s) {
+    if (q.n <= 0) return hipSuccess;
+    prof_begin("refine_order", s);
+    hipLaunchKernelGGL(k_refine_order, dim3((uint32_t)((q.n + kRefineTile - 1) / kRefineTile)), dim3(kBlock), 0, s, q,
+                       g, keys, order, refined, pos);
+    prof_end("refine_order", s);
     return hipGetLastError();
 }
 
