@@ -323,13 +323,15 @@ BwdGeom bwd_geom(const GridParams &gp, const QueryParams &qp, float T) {
         b.cw[j] = (float)(1.0 / (double)gp.invc[j + 1]);
         b.slack[j] = (float)(std::ldexp(1.0, -18) * (std::fabs((double)gp.lo[j + 1]) + std::fabs((double)gp.hi[j + 1])));
     }
-    const double ext0 = (double)gp.hi[0] - (double)gp.lo[0];
-    b.ivsz0 = qp.kind == GS_QUERY_GRID ? (float)(1.0 / (double)qp.vsz[0]) : 0.0f;
-    b.xslack = qp.kind == GS_QUERY_GRID
-                   ? (float)(std::ldexp(1.0, -20) * (double)qp.dims[0] *
-                                 (1.0 + (std::fabs((double)gp.lo[0]) + std::fabs((double)gp.hi[0])) / ext0) +
-                             std::ldexp(1.0, -12))
-                   : 0.0f;
+    for (int j = 0; j < 3; ++j) {
+        b.ivsz[j] = b.vslack[j] = 0.0f;
+        if (qp.kind != GS_QUERY_GRID) continue;
+        const double lo = gp.lo[j], hi = gp.hi[j];
+        b.ivsz[j] = (float)(1.0 / (double)qp.vsz[j]);
+        b.vslack[j] = (float)(std::ldexp(1.0, -20) * (double)qp.dims[j] *
+                                  (1.0 + (std::fabs(lo) + std::fabs(hi)) / (hi - lo)) +
+                              std::ldexp(1.0, -12));
+    }
     b.K = (uint32_t)(kSub * gp.cells[0]);
     return b;
 }

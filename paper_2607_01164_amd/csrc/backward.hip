@@ -217,6 +217,7 @@ constexpr uint32_t kPack = 4;
 constexpr uint32_t kPackLarge = 1;
 constexpr int64_t kPackMinGauss = 65536;
 constexpr int64_t kLargeBoxCells = 32;
+static_assert(kPackLarge == 1, "the launches have waves of one and of kPack Gaussians");
 
 // Partials of the wave's current Gaussian are reduced over the wave and
 // stored: lane k < 12 writes moment k (the 12th is 0).
@@ -245,56 +246,70 @@ __device__ __forceinline__ float bperm_f(uint32_t src, float v) {
     return __int_as_float(__builtin_amdgcn_ds_bpermute((int)src, __float_as_int(v)));
 }
 
-// Row `row` of a Gaussian's box (lower corner (lx, ly, lz) in cells, nx
-// cells along x, ny along y): for grids voxel row (vy, vz) of the box, for
-// ordered queries the row of cells (cy, cz), y fastest. The row's first
-// element (voxel index, or place in the plan's order), its length, and for
-// grids its first voxel along x and the row's y, z.
-struct RowRun {
-    uint32_t start, len, x0;
-    float py, pz;
+// Row `row` of `ny` rows a layer as (yy, zz), by a float reciprocal below 2^21
+// rows: (row + 1/2) / ny lies at least 1/(2 ny) from an integer; v_rcp (1 ulp)
+// and the product err by less than 1.5 2^-23 (row + 1/2) / ny, which cannot
+// cross it while row < 2^21.
+__device__ __forceinline__ void row_yz(uint32_t row, uint32_t ny, bool fdiv, uint32_t &yy, uint32_t &zz) {
+    zz = fdiv ? (uint32_t)(((float)row + 0.5f) * __builtin_amdgcn_rcpf((float)ny)) : row / ny;
+    yy = row - zz * ny;
+}
+
+// The voxels a Gaussian's rows can hold on a grid: x0 .. x1 of its box, and
+// the rows y0 .. y0 + ny - 1, z0 .. z0 + nz - 1 that its cutoff ellipsoid
+// reaches. Q >= (U22 dz)^2, and over x and z Q is at least dy^2 U11^2 / (1 +
+// (U12 / U22)^2), which bound |dz| and |dy|; both ranges are cut to the box.
+// (The box's rows are whole cells; most of them miss the ellipsoid.)
+struct GridRows {
+    uint32_t x0, x1, y0, ny, z0, nz;
 };
 
-template <bool GRID>
-__device__ __forceinline__ RowRun row_run(const Record &r, int32_t lx, int32_t ly, int32_t lz, uint32_t nx,
-                                          uint32_t ny, uint32_t row, uint32_t rx, uint32_t ry, uint32_t rz, bool fdiv,
-                                          const QueryParams &q, const GridParams &g, const BwdGeom &bg,
-                                          const uint32_t *__restrict__ point_off) {
-    RowRun o;
-    o.start = o.len = o.x0 = 0;
-    o.py = o.pz = 0.0f;
-    const uint32_t nry = GRID ? ny * ry : ny;
-    // row -> (yy, zz) by a float reciprocal: (row + 1/2) / nry lies at least
-    // 1/(2 nry) from an integer; v_rcp (1 ulp) and the product err by less
-    // than 1.5 2^-23 (row + 1/2) / nry, which cannot cross it while
-    // row < 2^21
-    uint32_t zz;
-    if (fdiv)
-        zz = (uint32_t)(((float)row + 0.5f) * __builtin_amdgcn_rcpf((float)nry));
-    else
-        zz = row / nry;
-    const uint32_t yy = row - zz * nry;
-    if (GRID) {
-        float xl, xh;
-        (void)rz;
-        const uint32_t vy = (uint32_t)ly * ry + yy, vz = (uint32_t)lz * rz + zz;
-        o.py = g.lo[1] + ((float)vy + 0.5f) * q.vsz[1];
-        o.pz = g.lo[2] + ((float)vz + 0.5f) * q.vsz[2];
-        const float dy = o.py - r.f0.y, dz = o.pz - r.f0.z;
-        if (!slab_xrange(r, dy, dy, dz, dz, bg.T2, xl, xh)) return o;
-        // voxels vx of the box with lo + (vx + 1/2) vsz in [xl, xh]
-        const float vmin = (float)((uint32_t)lx * rx), vmax = (float)(((uint32_t)lx + nx) * rx) - 1.0f;
-        const float a = fminf(fmaxf((xl - g.lo[0]) * bg.ivsz0 - 0.5f - bg.xslack, vmin), vmax + 1.0f);
-        const float b = fminf(fmaxf((xh - g.lo[0]) * bg.ivsz0 - 0.5f + bg.xslack, vmin - 1.0f), vmax);
-        const float v0 = ceilf(a), v1 = floorf(b);
-        if (v1 < v0) return o;
-        o.x0 = (uint32_t)v0;
-        o.len = (uint32_t)(v1 - v0) + 1u;
-        o.start = (uint32_t)q.dims[0] * (vy + (uint32_t)q.dims[1] * vz) + o.x0;
-    } else {
-        o.len = plan_row(r, (uint32_t)lx, nx, (uint32_t)ly + yy, (uint32_t)lz + zz, g, bg, point_off, o.start);
-    }
+__device__ __forceinline__ GridRows grid_rows(const Record &r, const CellBox &b, const QueryParams &q,
+                                              const GridParams &g, const BwdGeom &bg) {
+    const uint32_t rx = (uint32_t)(q.dims[0] / g.cells[0]), ry = (uint32_t)(q.dims[1] / g.cells[1]);
+    const uint32_t rz = (uint32_t)(q.dims[2] / g.cells[2]);
+    GridRows o;
+    o.x0 = (uint32_t)b.lo.x * rx;
+    o.x1 = ((uint32_t)b.hi.x + 1u) * rx - 1u;
+    const float rt = __builtin_sqrtf(bg.T2);
+    const float t = r.f2.y / r.f2.z;
+    const float hy = rt * __builtin_sqrtf(fmaf_(t, t, 1.0f)) / r.f2.x, hz = rt / r.f2.z;
+    // rows whose centre lo + (v + 1/2) vsz lies in [mu - h, mu + h]; a range
+    // that is not a number leaves the box's
+    auto cut = [](float mu, float h, float lo, float iv, float slack, uint32_t v0, uint32_t v1, uint32_t &first,
+                  uint32_t &n) {
+        const float a = fmaxf(ceilf((mu - h - lo) * iv - 0.5f - slack), (float)v0);
+        const float c = fminf(floorf((mu + h - lo) * iv - 0.5f + slack), (float)v1);
+        const bool some = a <= c;
+        first = some ? (uint32_t)a : v0;
+        n = some ? (uint32_t)(c - a) + 1u : 0u;
+    };
+    cut(r.f0.y, hy, g.lo[1], bg.ivsz[1], bg.vslack[1], (uint32_t)b.lo.y * ry, ((uint32_t)b.hi.y + 1u) * ry - 1u, o.y0,
+        o.ny);
+    cut(r.f0.z, hz, g.lo[2], bg.ivsz[2], bg.vslack[2], (uint32_t)b.lo.z * rz, ((uint32_t)b.hi.z + 1u) * rz - 1u, o.z0,
+        o.nz);
     return o;
+}
+
+// Voxel row (vy, vz) of a Gaussian with voxels x0 .. x1: the voxels within the
+// cutoff T2 (a run; first and number), and the row's y, z.
+__device__ __forceinline__ uint32_t grid_row(const Record &r, uint32_t x0, uint32_t x1, uint32_t vy, uint32_t vz,
+                                             const QueryParams &q, const GridParams &g, const BwdGeom &bg,
+                                             uint32_t &first, float &py, float &pz) {
+    first = 0;
+    py = g.lo[1] + ((float)vy + 0.5f) * q.vsz[1];
+    pz = g.lo[2] + ((float)vz + 0.5f) * q.vsz[2];
+    const float dy = py - r.f0.y, dz = pz - r.f0.z;
+    float xl, xh;
+    if (!slab_xrange(r, dy, dy, dz, dz, bg.T2, xl, xh)) return 0;
+    // voxels vx of the box with lo + (vx + 1/2) vsz in [xl, xh]
+    const float vmin = (float)x0, vmax = (float)x1;
+    const float a = fminf(fmaxf((xl - g.lo[0]) * bg.ivsz[0] - 0.5f - bg.vslack[0], vmin), vmax + 1.0f);
+    const float b = fminf(fmaxf((xh - g.lo[0]) * bg.ivsz[0] - 0.5f + bg.vslack[0], vmin - 1.0f), vmax);
+    const float v0 = ceilf(a), v1 = floorf(b);
+    if (v1 < v0) return 0;
+    first = (uint32_t)v0;
+    return (uint32_t)(v1 - v0) + 1u;
 }
 
 // PACK consecutive Gaussians of gorder per wavefront. The rows of the
@@ -307,8 +322,8 @@ __device__ __forceinline__ RowRun row_run(const Record &r, int32_t lx, int32_t l
 // test is all a non-contributing pair costs; contributing pairs go to a
 // per-wave LDS queue, and every 64 queued pairs are processed with all
 // lanes busy.
-template <bool GRID, uint32_t PACK>
-__global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, GridParams g, BwdGeom bg,
+template <uint32_t PACK>
+__global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(GridParams g, BwdGeom bg,
                                                            const Record *__restrict__ rec,
                                                            const CellBox *__restrict__ box,
                                                            const uint32_t *__restrict__ gorder, int64_t n_gauss,
@@ -326,12 +341,6 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
     const uint32_t nk = (uint64_t)n_gauss - first < PACK ? (uint32_t)((uint64_t)n_gauss - first) : PACK;
     float4 *qu = s_qu[wib];
     uint32_t *qk = s_qk[wib];
-    uint32_t rx = 1, ry = 1, rz = 1;
-    if (GRID) {
-        rx = (uint32_t)(q.dims[0] / g.cells[0]);
-        ry = (uint32_t)(q.dims[1] / g.cells[1]);
-        rz = (uint32_t)(q.dims[2] / g.cells[2]);
-    }
     // lane i < nk describes Gaussian i of the wave: id, box, rows
     uint32_t mgid = 0, mR = 0, mnx = 0, mny = 1;
     int32_t mlx = 0, mly = 0, mlz = 0;
@@ -345,7 +354,7 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
             mnx = (uint32_t)(bx.hi.x - bx.lo.x + 1);
             mny = (uint32_t)(bx.hi.y - bx.lo.y + 1);
             const uint32_t nz = (uint32_t)(bx.hi.z - bx.lo.z + 1);
-            mR = GRID ? mny * ry * nz * rz : mny * nz;
+            mR = mny * nz;
             mlx = bx.lo.x;
             mly = bx.lo.y;
             mlz = bx.lo.z;
@@ -361,7 +370,7 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
     }
     const uint32_t mRend = wave_incl_sum(mR);  // end of Gaussian i's rows in the wave's list
     const uint32_t Rw = __builtin_amdgcn_readlane(mRend, kWave - 1);
-    // rows -> (yy, zz) by a float reciprocal below 2^21 rows (see row_run)
+    // rows -> (yy, zz) by a float reciprocal below 2^21 rows (row_yz)
     const bool fdiv = wave_max_uniform(mR) < (1u << 21);
     Record r;
     r.f0 = r.f1 = r.f2 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -390,24 +399,17 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
         fr.f0 = make_float4(bperm_f(src, mrec.f0.x), bperm_f(src, mrec.f0.y), bperm_f(src, mrec.f0.z), 0.0f);
         fr.f1 = make_float4(bperm_f(src, mrec.f1.x), bperm_f(src, mrec.f1.y), bperm_f(src, mrec.f1.z), 0.0f);
         fr.f2 = make_float4(bperm_f(src, mrec.f2.x), bperm_f(src, mrec.f2.y), bperm_f(src, mrec.f2.z), 0.0f);
-        uint32_t start = 0, len = 0, rx0 = 0;
-        float rpy = 0.0f, rpz = 0.0f;
+        uint32_t start = 0, len = 0;
         if (gr < Rw) {
-            const uint32_t row = gr - (f_end - f_R);  // row within its Gaussian
-            const RowRun rr = row_run<GRID>(fr, (int32_t)f_lx, (int32_t)f_ly, (int32_t)f_lz, f_nx, f_ny, row, rx, ry,
-                                            rz, fdiv, q, g, bg, point_off);
-            start = rr.start;
-            len = rr.len;
-            rx0 = rr.x0;
-            rpy = rr.py;
-            rpz = rr.pz;
+            uint32_t yy, zz;
+            row_yz(gr - (f_end - f_R), f_ny, fdiv, yy, zz);  // row within its Gaussian
+            len = plan_row(fr, f_lx, f_nx, f_ly + yy, f_lz + zz, g, bg, point_off, start);
         }
         const uint32_t nrows = (Rw - rb) < (uint32_t)kWave ? (Rw - rb) : (uint32_t)kWave;
         const uint32_t incl = wave_incl_sum(len);   // end of row l in the batch's concatenation
         const uint32_t E = __builtin_amdgcn_readlane(incl, kWave - 1);
         const uint32_t rbeg = incl - len;           // first element of row l
         const uint32_t kofs = start - rbeg;         // element e of row l is point e + kofs
-        const uint32_t xofs = rx0 - rbeg;           // grids: element e of row l has x = e + xofs
         // the Gaussians with rows in this batch, in order
         const uint32_t ia = __builtin_amdgcn_readlane(i, 0), ib = __builtin_amdgcn_readlane(i, nrows - 1);
         for (uint32_t gi = ia; gi <= ib; ++gi) {
@@ -427,22 +429,14 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
             const uint32_t Ea = __builtin_amdgcn_readlane(rbeg, la);
             const uint32_t Eb = lb < (uint32_t)kWave ? __builtin_amdgcn_readlane(rbeg, lb) : E;
             // The element window [e0, e0 + 64): the offset of each lane's row
-            // (ko: element e of the row is point e + ko; grids: x offset xo and
-            // the row's y, z).
-            auto locate = [&](uint32_t e0, uint32_t &ko, uint32_t &xo, float &py, float &pz) {
+            // (ko: element e of the row is point e + ko).
+            auto locate = [&](uint32_t e0, uint32_t &ko) {
                 // rbeg rises with the lane (lanes past nrows hold E), so the
                 // rows starting at or before e0 are a prefix of the lanes and
                 // the last of them holds element e0
                 const uint32_t j0 = (uint32_t)__popcll(mask_le_u(rbeg, e0)) - 1u;
                 const uint32_t e = e0 + lane;
                 ko = __builtin_amdgcn_readlane(kofs, j0);  // row of element e0
-                xo = 0;
-                py = pz = 0.0f;
-                if (GRID) {
-                    xo = __builtin_amdgcn_readlane(xofs, j0);
-                    py = readlane_f(rpy, j0);
-                    pz = readlane_f(rpz, j0);
-                }
                 // rows starting inside the window move the later lanes on, in
                 // row order (an empty row is overridden by the next)
                 uint64_t inw = mask_lt_u(lane, nrows) & mask_lt_u(rbeg - e0 - 1u, (uint32_t)kWave - 1u);
@@ -451,16 +445,11 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
                     inw &= inw - 1;
                     const bool nxt = e >= __builtin_amdgcn_readlane(rbeg, j);
                     ko = nxt ? __builtin_amdgcn_readlane(kofs, j) : ko;
-                    if (GRID) {
-                        xo = nxt ? __builtin_amdgcn_readlane(xofs, j) : xo;
-                        py = nxt ? readlane_f(rpy, j) : py;
-                        pz = nxt ? readlane_f(rpz, j) : pz;
-                    }
                 }
             };
             // The cutoff test of the window's pairs; contributing ones go to
             // the queue, which is processed 64 pairs at a time.
-            auto test = [&](uint32_t e0, uint32_t ko, uint32_t xo, float py, float pz, float4 p) {
+            auto test = [&](uint32_t e0, uint32_t ko, float4 p) {
                 // lanes past the Gaussian's last element read the elements
                 // after it: points of later rows, or past the batch's last
                 // row, whose last point is at most n - 1, up to 63 entries of
@@ -468,13 +457,8 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
                 const uint32_t e = e0 + lane;
                 const bool valid = e < Eb;
                 const uint32_t k = e + ko;
-                float u0, u1, u2, Q;
-                if (GRID) {
-                    const float px = g.lo[0] + ((float)(e + xo) + 0.5f) * q.vsz[0];
-                    Q = whiten(r, px, py, pz, u0, u1, u2);
-                } else {
-                    Q = whiten(r, p.x, p.y, p.z, u0, u1, u2);
-                }
+                float u0, u1, u2;
+                const float Q = whiten(r, p.x, p.y, p.z, u0, u1, u2);
                 const bool hit = valid && Q <= T;
                 const uint64_t mask = mask_le_f(Q, T) & mask_lt_u(e, Eb);
                 if (mask == 0) return;
@@ -533,7 +517,7 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
             // skips the per-lane row search and loads from a uniform base;
             // with short rows the scalar bookkeeping would cost more than it
             // saves.
-            const bool long_rows = !GRID && Eb - Ea >= kLongRow * (lb - la);
+            const bool long_rows = Eb - Ea >= kLongRow * (lb - la);
             for (uint32_t e0 = Ea; e0 < Eb; e0 += kBwdWindows * kWave) {
                 if (long_rows) {
                     if (e0 >= nxt) row_at(e0);
@@ -546,23 +530,172 @@ __global__ __launch_bounds__(kBwdBlock) void k_backward_gauss(QueryParams q, Gri
                         continue;
                     }
                 }
-                uint32_t koA, xoA, koB = 0, xoB = 0;
-                float pyA, pzA, pyB = 0.0f, pzB = 0.0f;
+                uint32_t koA, koB = 0;
                 const uint32_t e1 = e0 + kWave;
                 const bool two = kBwdWindows > 1 && e1 < Eb;
-                float4 pA = make_float4(0.0f, 0.0f, 0.0f, 0.0f), pB = pA;
-                locate(e0, koA, xoA, pyA, pzA);
-                if (!GRID) pA = plan_pos[e0 + lane + koA];
+                float4 pB = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                locate(e0, koA);
+                const float4 pA = plan_pos[e0 + lane + koA];
                 if (two) {
-                    locate(e1, koB, xoB, pyB, pzB);
-                    if (!GRID) pB = plan_pos[e1 + lane + koB];
+                    locate(e1, koB);
+                    pB = plan_pos[e1 + lane + koB];
                 }
-                test(e0, koA, xoA, pyA, pzA, pA);
-                if (two) test(e1, koB, xoB, pyB, pzB, pB);
+                test(e0, koA, pA);
+                if (two) test(e1, koB, pB);
             }
         }
     }
     if (cur < PACK) finish_gauss(r, qu, qk, head, cnt, lane, ab, acc, cur_gid, moments);
+}
+
+// The same for grids, whose rows of voxels along x are short (a few voxels to
+// a few tens) and cut to the cutoff exactly: nearly every pair that is tested
+// contributes (0.99 of them), so pairs are not queued; a window's (alpha,
+// beta) are loaded with its rows' places, before it is tested. A window of 64
+// elements spans many rows: the rows' first elements are marked in LDS, and a
+// max-scan over the lanes hands every element its row (walking the window's
+// rows one by one took most of the kernel's time, as did the rows of the
+// cells of a box that the ellipsoid misses: 128^3 voxels and 131,072
+// Gaussians 560 -> 113 us; one or two Gaussians a wave 128 and 118).
+template <uint32_t PACK>
+__global__ __launch_bounds__(kBwdBlock) void k_backward_grid(QueryParams q, GridParams g, BwdGeom bg,
+                                                             const Record *__restrict__ rec,
+                                                             const CellBox *__restrict__ box,
+                                                             const uint32_t *__restrict__ gorder, int64_t n_gauss,
+                                                             const float2 *__restrict__ ab, float T,
+                                                             float *__restrict__ moments) {
+    static_assert(kBwdWaves == 1, "one wave's marks");
+    __shared__ uint32_t s_mark[kBwdWindows][kWave];
+    const uint32_t lane = threadIdx.x;
+    const uint64_t first = (uint64_t)xcd_group<kXcdWaves>(blockIdx.x, gridDim.x) * PACK;
+    if (first >= (uint64_t)n_gauss) return;
+    const uint32_t nk = (uint64_t)n_gauss - first < PACK ? (uint32_t)((uint64_t)n_gauss - first) : PACK;
+    // lane i < nk describes Gaussian i of the wave
+    uint32_t mgid = 0, mR = 0;
+    Record mrec = {};
+    GridRows mr = {};
+    mr.ny = 1;
+    if (lane < nk) {
+        mgid = gorder[first + lane];
+        mrec = rec[mgid];
+        const CellBox bx = box[mgid];
+        if (bx.hi.x >= bx.lo.x) {
+            mr = grid_rows(mrec, bx, q, g, bg);
+            mR = mr.ny * mr.nz;
+        }
+        // a Gaussian without rows gets zero moments here
+        if (mR == 0) {
+            float4 *m4 = (float4 *)(moments + (size_t)mgid * 12);
+            m4[0] = m4[1] = m4[2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+    }
+    const uint32_t mRend = wave_incl_sum(mR);  // end of Gaussian i's rows in the wave's list
+    const uint32_t Rw = __builtin_amdgcn_readlane(mRend, kWave - 1);
+    const bool fdiv = wave_max_uniform(mR) < (1u << 21);
+    Record r = {};
+    Acc acc;
+    acc_zero(acc);
+    uint32_t cur = PACK, cur_gid = 0;  // the Gaussian being walked (none yet)
+    auto finish = [&]() {
+        const float v[11] = {acc.m1[0], acc.m1[1], acc.m1[2], acc.m2[0], acc.m2[1], acc.m2[2],
+                             acc.m2[3], acc.m2[4], acc.m2[5], acc.dv,    acc.dw};
+        const float tot = reduce11(v, lane);
+        if (lane < 12) moments[(size_t)cur_gid * 12 + lane] = tot;
+    };
+    for (uint32_t rb = 0; rb < Rw; rb += kWave) {
+        // lane l describes row rb + l of the wave's list (of Gaussian i); the
+        // permutes run with every lane active
+        const uint32_t gr = rb + lane;
+        uint32_t i = 0;
+        for (uint32_t t = 0; t < nk; ++t) i += __builtin_amdgcn_readlane(mRend, t) <= gr ? 1u : 0u;
+        const uint32_t src = (i < kWave ? i : 0u) << 2;
+        auto perm = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute((int)src, (int)v); };
+        const uint32_t f_end = perm(mRend), f_R = perm(mR), f_ny = perm(mr.ny);
+        const uint32_t f_x0 = perm(mr.x0), f_x1 = perm(mr.x1), f_y0 = perm(mr.y0), f_z0 = perm(mr.z0);
+        Record fr;
+        fr.f0 = make_float4(bperm_f(src, mrec.f0.x), bperm_f(src, mrec.f0.y), bperm_f(src, mrec.f0.z), 0.0f);
+        fr.f1 = make_float4(bperm_f(src, mrec.f1.x), bperm_f(src, mrec.f1.y), bperm_f(src, mrec.f1.z), 0.0f);
+        fr.f2 = make_float4(bperm_f(src, mrec.f2.x), bperm_f(src, mrec.f2.y), bperm_f(src, mrec.f2.z), 0.0f);
+        uint32_t len = 0, rx0 = 0, start = 0;
+        float rpy = 0.0f, rpz = 0.0f;
+        if (gr < Rw) {
+            uint32_t yy, zz;
+            row_yz(gr - (f_end - f_R), f_ny, fdiv, yy, zz);
+            const uint32_t vy = f_y0 + yy, vz = f_z0 + zz;
+            len = grid_row(fr, f_x0, f_x1, vy, vz, q, g, bg, rx0, rpy, rpz);
+            start = (uint32_t)q.dims[0] * (vy + (uint32_t)q.dims[1] * vz) + rx0;
+        }
+        const uint32_t nrows = (Rw - rb) < (uint32_t)kWave ? (Rw - rb) : (uint32_t)kWave;
+        const uint32_t incl = wave_incl_sum(len);   // end of row l in the batch's concatenation
+        const uint32_t E = __builtin_amdgcn_readlane(incl, kWave - 1);
+        const uint32_t rbeg = incl - len;           // first element of row l
+        const uint32_t kofs = start - rbeg;         // element e of row l is voxel e + kofs
+        const uint32_t xofs = rx0 - rbeg;           // with x = e + xofs
+        // the Gaussians with rows in this batch, in order
+        const uint32_t ia = __builtin_amdgcn_readlane(i, 0), ib = __builtin_amdgcn_readlane(i, nrows - 1);
+        for (uint32_t gi = ia; gi <= ib; ++gi) {
+            const uint32_t gend = __builtin_amdgcn_readlane(mRend, gi), gR = __builtin_amdgcn_readlane(mR, gi);
+            if (gR == 0) continue;  // no rows: its moments are written above
+            if (gi != cur) {
+                if (cur < PACK) finish();
+                acc_zero(acc);
+                cur = gi;
+                cur_gid = __builtin_amdgcn_readlane(mgid, gi);
+                r = load_record_uniform(rec, cur_gid);
+            }
+            // its rows in this batch and their elements [Ea, Eb)
+            const uint32_t la = gend - gR > rb ? gend - gR - rb : 0u;
+            const uint32_t lb = gend - rb < nrows ? gend - rb : nrows;
+            const uint32_t Ea = __builtin_amdgcn_readlane(rbeg, la);
+            const uint32_t Eb = lb < (uint32_t)kWave ? __builtin_amdgcn_readlane(rbeg, lb) : E;
+            // Window [e0, e0 + 64): each lane's voxel and its (alpha, beta).
+            struct Elem {
+                float px, py, pz;
+                float2 c;
+            };
+            auto locate = [&](uint32_t e0, uint32_t *mark) {
+                // the last row starting at or before e0 holds element e0 (rbeg
+                // rises with the lane); the other rows with elements mark the
+                // one where they start
+                const uint32_t j0 = (uint32_t)__popcll(mask_le_u(rbeg, e0)) - 1u;
+                mark[lane] = 0;
+                __builtin_amdgcn_wave_barrier();
+                if (len > 0 && rbeg - e0 - 1u < (uint32_t)kWave - 1u) mark[rbeg - e0] = lane;
+                __builtin_amdgcn_wave_barrier();
+                const uint32_t m = mark[lane];
+                const uint32_t row = wave_incl_max(m > j0 ? m : j0) << 2;
+                const uint32_t e = e0 + lane;
+                Elem o;
+                const uint32_t x = e + (uint32_t)__builtin_amdgcn_ds_bpermute((int)row, (int)xofs);
+                const uint32_t k = e + (uint32_t)__builtin_amdgcn_ds_bpermute((int)row, (int)kofs);
+                o.px = g.lo[0] + ((float)x + 0.5f) * q.vsz[0];
+                o.py = bperm_f(row, rpy);
+                o.pz = bperm_f(row, rpz);
+                o.c = make_float2(0.0f, 0.0f);
+                if (e < Eb) o.c = ab[k];  // lanes past the Gaussian's last element have none
+                return o;
+            };
+            auto add = [&](uint32_t e0, const Elem &o) {
+                float u0, u1, u2;
+                const float Q = whiten(r, o.px, o.py, o.pz, u0, u1, u2);
+                if (e0 + lane < Eb && Q <= T) pair_grad(r, u0, u1, u2, Q, o.c.x, o.c.y, acc);
+            };
+            // two windows at a time: both windows' loads are under way before
+            // either is used
+            for (uint32_t e0 = Ea; e0 < Eb; e0 += kBwdWindows * kWave) {
+                const uint32_t e1 = e0 + kWave;
+                const Elem A = locate(e0, s_mark[0]);
+                if (e1 < Eb) {
+                    const Elem B = locate(e1, s_mark[1]);
+                    add(e0, A);
+                    add(e1, B);
+                } else {
+                    add(e0, A);
+                }
+            }
+        }
+    }
+    if (cur < PACK) finish();
 }
 
 __global__ __launch_bounds__(kBlock) void k_finalize(const float *__restrict__ moments, int64_t n,
@@ -671,7 +804,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const float *__restrict__ m
 }
 
 // Pairs the backward tests, for measurement: per Gaussian the elements of
-// its rows, each cut to its x-range as the backward cuts it (row_run).
+// its rows, each cut to its x-range as the backward cuts it.
 // Summed per block, then into *total with one integer atomic per block (the
 // sum does not depend on its order).
 template <bool GRID>
@@ -686,16 +819,21 @@ __global__ __launch_bounds__(kBlock) void k_count_backward_pairs(QueryParams q, 
     if (i < n_gauss) {
         const CellBox bx = box[i];
         if (bx.hi.x >= bx.lo.x) {
-            const uint32_t rx = GRID ? (uint32_t)(q.dims[0] / g.cells[0]) : 1u;
-            const uint32_t ry = GRID ? (uint32_t)(q.dims[1] / g.cells[1]) : 1u;
-            const uint32_t rz = GRID ? (uint32_t)(q.dims[2] / g.cells[2]) : 1u;
-            const uint32_t nx = (uint32_t)(bx.hi.x - bx.lo.x + 1), ny = (uint32_t)(bx.hi.y - bx.lo.y + 1);
-            const uint32_t nz = (uint32_t)(bx.hi.z - bx.lo.z + 1);
-            const uint32_t R = GRID ? ny * ry * nz * rz : ny * nz;
             const Record r = rec[i];
-            for (uint32_t row = 0; row < R; ++row)
-                c += row_run<GRID>(r, bx.lo.x, bx.lo.y, bx.lo.z, nx, ny, row, rx, ry, rz, false, q, g, bg, point_off)
-                         .len;
+            if (GRID) {
+                const GridRows o = grid_rows(r, bx, q, g, bg);
+                uint32_t first;
+                float py, pz;
+                for (uint32_t zz = 0; zz < o.nz; ++zz)
+                    for (uint32_t yy = 0; yy < o.ny; ++yy)
+                        c += grid_row(r, o.x0, o.x1, o.y0 + yy, o.z0 + zz, q, g, bg, first, py, pz);
+            } else {
+                const uint32_t nx = (uint32_t)(bx.hi.x - bx.lo.x + 1);
+                uint32_t start;
+                for (int32_t cz = bx.lo.z; cz <= bx.hi.z; ++cz)
+                    for (int32_t cy = bx.lo.y; cy <= bx.hi.y; ++cy)
+                        c += plan_row(r, (uint32_t)bx.lo.x, nx, (uint32_t)cy, (uint32_t)cz, g, bg, point_off, start);
+            }
         }
     }
     // block sum in a fixed order, then one atomic per block
@@ -709,21 +847,6 @@ __global__ __launch_bounds__(kBlock) void k_count_backward_pairs(QueryParams q, 
         for (int w = 0; w < kWavesPerBlock; ++w) t += lds[w];
         if (t) atomicAdd(total, t);
     }
-}
-
-template <bool GRID>
-void launch_gauss(uint32_t pack, uint32_t wblocks, hipStream_t s, const QueryParams &q, const GridParams &g,
-                  const BwdGeom &bg, const Record *rec, const CellBox *box, const uint32_t *gorder, int64_t n_gauss,
-                  const uint32_t *point_off, const float4 *plan_pos, const float2 *ab, float T, float *moments) {
-    if (pack == 1)
-        hipLaunchKernelGGL((k_backward_gauss<GRID, 1>), dim3(wblocks), dim3(kBwdBlock), 0, s, q, g, bg, rec, box,
-                           gorder, n_gauss, point_off, plan_pos, ab, T, moments);
-    else if (pack == kPackLarge)
-        hipLaunchKernelGGL((k_backward_gauss<GRID, kPackLarge>), dim3(wblocks), dim3(kBwdBlock), 0, s, q, g, bg, rec,
-                           box, gorder, n_gauss, point_off, plan_pos, ab, T, moments);
-    else
-        hipLaunchKernelGGL((k_backward_gauss<GRID, kPack>), dim3(wblocks), dim3(kBwdBlock), 0, s, q, g, bg, rec, box,
-                           gorder, n_gauss, point_off, plan_pos, ab, T, moments);
 }
 
 }  // namespace
@@ -773,12 +896,19 @@ hipError_t launch_backward(const QueryParams &q, const GridParams &g, const BwdG
         const uint32_t pack = n_gauss < kPackMinGauss ? 1u : (n_pairs >= kLargeBoxCells * n_gauss ? kPackLarge : kPack);
         const uint32_t wblocks = (uint32_t)((n_gauss + pack * kBwdWaves - 1) / (pack * kBwdWaves));
         prof_begin("bwd_gauss", s);
-        if (grid)
-            launch_gauss<true>(pack, wblocks, s, q, g, bg, rec, box, gorder, n_gauss, nullptr, nullptr, b.ab, T,
+        const dim3 wb(wblocks), tb(kBwdBlock);
+        if (grid && pack == 1)
+            hipLaunchKernelGGL(k_backward_grid<1>, wb, tb, 0, s, q, g, bg, rec, box, gorder, n_gauss, b.ab, T,
                                b.moments);
+        else if (grid)
+            hipLaunchKernelGGL(k_backward_grid<kPack>, wb, tb, 0, s, q, g, bg, rec, box, gorder, n_gauss, b.ab, T,
+                               b.moments);
+        else if (pack == 1)
+            hipLaunchKernelGGL(k_backward_gauss<1>, wb, tb, 0, s, g, bg, rec, box, gorder, n_gauss, point_off,
+                               plan_pos, b.ab, T, b.moments);
         else
-            launch_gauss<false>(pack, wblocks, s, q, g, bg, rec, box, gorder, n_gauss, point_off, plan_pos, b.ab, T,
-                                b.moments);
+            hipLaunchKernelGGL(k_backward_gauss<kPack>, wb, tb, 0, s, g, bg, rec, box, gorder, n_gauss, point_off,
+                               plan_pos, b.ab, T, b.moments);
         prof_end("bwd_gauss", s);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {

@@ -469,8 +469,8 @@ struct BwdGeom {
     float T2;          // the cutoff the row bounds use: T (1 + 2^-7)
     float cw[2];       // ordered queries: y, z extent of a cell, 1 / invc
     float slack[2];    // widening of a row's y, z extent (float rounding)
-    float ivsz0;       // grids: voxels per unit along x, 1 / vsz[0]
-    float xslack;      // grids: widening of a row's voxel range, in voxels
+    float ivsz[3];     // grids: voxels per unit, 1 / vsz
+    float vslack[3];   // grids: widening of voxel ranges, in voxels
     uint32_t K;        // kSub cells[0]: quarters of a row of cells
 };
 
