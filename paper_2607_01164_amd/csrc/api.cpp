@@ -440,8 +440,12 @@ gs_status order_queries(const char *who, const QueryParams &qp, const GridParams
     const bool odd = (radix_passes(bits) & 1) != 0;
     uint32_t *ek = odd ? p.keys_alt : p.keys, *ev = odd ? p.order_alt : p.order;
     uint32_t *ak = odd ? p.keys : p.keys_alt, *av = odd ? p.order : p.order_alt;
-    GS_TRY(launch_query_keys(qp, gp, ek, ev, radix_pass0(p.radix_work, nq, bits), stream), "query keys");
-    GS_TRY(radix_sort_pairs(ek, ev, ak, av, nq, bits, p.radix_work, stream, true), "query sort");
+    if (nq <= kSmallSort) {
+        GS_TRY(launch_order_queries_small(qp, gp, bits, p.keys, p.order, stream), "query order");
+    } else {
+        GS_TRY(launch_query_keys(qp, gp, ek, ev, radix_pass0(p.radix_work, nq, bits), stream), "query keys");
+        GS_TRY(radix_sort_pairs(ek, ev, ak, av, nq, bits, p.radix_work, stream, true), "query sort");
+    }
     GS_TRY(key_offsets(p.keys, nq, p.point_off, (int64_t)kSub * gp.ncells + 1, stream), "query ranges");
     // the sort is done with its alternate ids: they take the refined order
     if (boxed_launch(nq, gp.ncells))
@@ -610,11 +614,16 @@ gs_status gs_build_index(const gs_gaussians *gauss, const gs_grid *grid, float t
         const bool godd = (radix_passes(gbits) & 1) != 0;
         uint32_t *k0 = godd ? w.gsort_k : w.gkeys, *v0 = godd ? w.gsort_v : w.gorder;
         uint32_t *k1 = godd ? w.gkeys : w.gsort_k, *v1 = godd ? w.gorder : w.gsort_v;
-        GS_TRY(launch_gauss_keys(w.box, n, gp, gauss_order_shift(grid), k0, v0, radix_pass0(w.gsort_work, n, gbits),
-                                 stream),
-               "gs_build_index: Gaussian keys");
-        GS_TRY(radix_sort_pairs(k0, v0, k1, v1, n, gbits, w.gsort_work, stream, true),
-               "gs_build_index: Gaussian order");
+        if (n <= kSmallSort) {
+            GS_TRY(launch_order_gauss_small(w.box, n, gp, gauss_order_shift(grid), gbits, w.gkeys, w.gorder, stream),
+                   "gs_build_index: Gaussian order");
+        } else {
+            GS_TRY(launch_gauss_keys(w.box, n, gp, gauss_order_shift(grid), k0, v0,
+                                     radix_pass0(w.gsort_work, n, gbits), stream),
+                   "gs_build_index: Gaussian keys");
+            GS_TRY(radix_sort_pairs(k0, v0, k1, v1, n, gbits, w.gsort_work, stream, true),
+                   "gs_build_index: Gaussian order");
+        }
     }
     GS_TRY(hipEventSynchronize(pc->copied), "gs_build_index: waiting for the pair count");
     const uint64_t P = *pc->value;

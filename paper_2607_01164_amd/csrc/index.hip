@@ -210,6 +210,15 @@ __device__ __forceinline__ void walk_rows(uint32_t R, uint32_t lane, uint32_t *a
     }
 }
 
+// The marks and the record counter that the preprocess starts from, cleared by
+// one launch: the cells' marks, then (the thread after them) the counter.
+__global__ __launch_bounds__(kBlock) void k_clear_marks(uint32_t *__restrict__ marks, int64_t words,
+                                                        uint32_t *__restrict__ rtotal) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < words) marks[i] = 0u;
+    if (i == words) *rtotal = 0u;
+}
+
 constexpr int kPreBlock = kWave;  // one wave per workgroup: the row walk is per wave
 
 __global__ __launch_bounds__(kPreBlock) void k_preprocess(const float *__restrict__ mean, const float *__restrict__ scale,
@@ -671,6 +680,13 @@ __global__ __launch_bounds__(kBlock) void k_emit(const uint64_t *__restrict__ pa
 // its box's low corner (ncells for an empty box), shifted right by `shift`
 // so that one radix pass orders it. Tiles of kSortTile Gaussians per
 // workgroup, with the pass's digit counts.
+__device__ __forceinline__ uint32_t gauss_key(const CellBox &b, const GridParams &g, int shift) {
+    uint32_t key = (uint32_t)g.ncells;
+    if (b.hi.x >= b.lo.x)
+        key = (uint32_t)((int64_t)b.lo.x + (int64_t)g.cells[0] * ((int64_t)b.lo.y + (int64_t)g.cells[1] * b.lo.z));
+    return key >> shift;
+}
+
 __global__ __launch_bounds__(kBlock) void k_gauss_keys(const CellBox *__restrict__ box, int64_t n, GridParams g,
                                                        int shift, uint32_t *__restrict__ keys,
                                                        uint32_t *__restrict__ ids, RadixPass0 pass0) {
@@ -680,11 +696,7 @@ __global__ __launch_bounds__(kBlock) void k_gauss_keys(const CellBox *__restrict
     for (int it = 0; it < kSortItems; ++it) {
         const int64_t i = (int64_t)blockIdx.x * kSortTile + (int64_t)it * kBlock + threadIdx.x;
         if (i < n) {
-            const CellBox b = box[i];
-            uint32_t key = (uint32_t)g.ncells;
-            if (b.hi.x >= b.lo.x)
-                key = (uint32_t)((int64_t)b.lo.x + (int64_t)g.cells[0] * ((int64_t)b.lo.y + (int64_t)g.cells[1] * b.lo.z));
-            key >>= shift;
+            const uint32_t key = gauss_key(box[i], g, shift);
             keys[i] = key;
             ids[i] = (uint32_t)i;
             hist.add(key);
@@ -693,7 +705,24 @@ __global__ __launch_bounds__(kBlock) void k_gauss_keys(const CellBox *__restrict
     hist.finish_tile(blockIdx.x);
 }
 
+__global__ __launch_bounds__(kSmallBlock) void k_order_gauss_small(const CellBox *__restrict__ box, int64_t n,
+                                                                   GridParams g, int shift, int bits,
+                                                                   uint32_t *__restrict__ keys,
+                                                                   uint32_t *__restrict__ order) {
+    __shared__ SmallSortLds L;
+    small_sort(L, (uint32_t)n, bits, [&](uint32_t i) { return gauss_key(box[i], g, shift); }, keys, order);
+}
+
 }  // namespace
+
+hipError_t launch_order_gauss_small(const CellBox *box, int64_t n, const GridParams &g, int shift, int bits,
+                                    uint32_t *keys, uint32_t *order, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    prof_begin("order_small", s);
+    hipLaunchKernelGGL(k_order_gauss_small, dim3(1), dim3(kSmallBlock), 0, s, box, n, g, shift, bits, keys, order);
+    prof_end("order_small", s);
+    return hipGetLastError();
+}
 
 hipError_t launch_gauss_keys(const CellBox *box, int64_t n, const GridParams &g, int shift, uint32_t *keys,
                              uint32_t *ids, const RadixPass0 &pass0, hipStream_t s) {
@@ -714,8 +743,10 @@ hipError_t launch_preprocess(const float *mean, const float *scale, const float 
     const int64_t threads = n > 0 ? n : 1;
     const uint32_t blocks = (uint32_t)((threads + kPreBlock - 1) / kPreBlock);
     prof_begin("preprocess", s);
-    hipError_t e = fill_u32(rtotal, 0u, 1, s);
-    if (e == hipSuccess) e = fill_u32((uint32_t *)cell_coarse, 0u, (g.ncells + 3) / 4, s);
+    const int64_t words = (g.ncells + 3) / 4;
+    hipLaunchKernelGGL(k_clear_marks, dim3((uint32_t)((words + kBlock) / kBlock)), dim3(kBlock), 0, s,
+                       (uint32_t *)cell_coarse, words, rtotal);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_preprocess, dim3(blocks), dim3(kPreBlock), 0, s, mean, scale, rot, value, weight, n, g, rci,
                        rec, box, lines, rows, rbase, rtotal, rcap, cell_coarse, count, block_sum);

@@ -400,6 +400,9 @@ __device__ __forceinline__ void query_position(const QueryParams &q, const GridP
         pz = q.points[3 * (uint64_t)pid + 2];
     }
 }
+// Keys and sort in one launch, for at most kSmallSort queries (radix.h).
+hipError_t launch_order_queries_small(const QueryParams &q, const GridParams &g, int bits, uint32_t *keys,
+                                      uint32_t *order, hipStream_t s);
 // Sort key of every query (kSub cell + quarter of the cell along x, kSub
 // ncells outside the domain), identity ids and
 // the first sort digit's tile counts.
@@ -454,6 +457,8 @@ hipError_t launch_count_sample_pairs(const QueryParams &q, const GridParams &g, 
 
 // Gaussians in spatial order: sorted by the cell key of their box's low
 // corner (empty boxes last), so neighbouring work shares cached queries.
+hipError_t launch_order_gauss_small(const CellBox *box, int64_t n, const GridParams &g, int shift, int bits,
+                                    uint32_t *keys, uint32_t *order, hipStream_t s);
 hipError_t launch_gauss_keys(const CellBox *box, int64_t n, const GridParams &g, int shift, uint32_t *keys,
                              uint32_t *ids, const RadixPass0 &pass0, hipStream_t s);
 

@@ -475,6 +475,35 @@ __global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams
     }
 }
 
+// Sort key of query i: kSub cell + quarter of the cell along x, kSub ncells
+// outside the domain.
+__device__ __forceinline__ uint32_t query_key(const QueryParams &q, const GridParams &g, uint32_t i) {
+    float p[3];
+    bool valid;
+    query_position(q, g, i, p[0], p[1], p[2], valid);
+    const uint32_t outside = kSub * (uint32_t)g.ncells;
+    if (!valid) return outside;
+    bool inside = true;
+    int64_t c[3];
+    float tx = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        inside = inside && (p[j] >= g.lo[j]) && (p[j] <= g.hi[j]);
+        const float t = (p[j] - g.lo[j]) * g.invc[j];
+        int64_t ci = (int64_t)floorf(t);
+        ci = ci < 0 ? 0 : ci;
+        ci = ci > g.cells[j] - 1 ? g.cells[j] - 1 : ci;
+        c[j] = ci;
+        if (j == 0) tx = t;
+    }
+    if (!inside) return outside;
+    // the quarter of the cell along x: floor(4 (t - c)), exact in float32 (t -
+    // c is exact, the product by 4 too)
+    const float fq = floorf((tx - (float)c[0]) * (float)kSub);
+    const uint32_t qx = fq < 0.0f ? 0u : (fq > (float)(kSub - 1) ? kSub - 1 : (uint32_t)fq);
+    return kSub * (uint32_t)(c[0] + (int64_t)g.cells[0] * (c[1] + (int64_t)g.cells[1] * c[2])) + qx;
+}
+
 __global__ __launch_bounds__(kBlock) void k_query_keys(QueryParams q, GridParams g, uint32_t *__restrict__ keys,
                                                        uint32_t *__restrict__ ids, RadixPass0 pass0) {
     __shared__ uint32_t hist_lds[kMaxDigits];
@@ -483,38 +512,20 @@ __global__ __launch_bounds__(kBlock) void k_query_keys(QueryParams q, GridParams
     for (int it = 0; it < kSortItems; ++it) {
         const int64_t i = (int64_t)blockIdx.x * kSortTile + (int64_t)it * kBlock + threadIdx.x;
         if (i < q.n) {
-            float p[3];
-            bool valid;
-            query_position(q, g, (uint32_t)i, p[0], p[1], p[2], valid);
-            uint32_t key = kSub * (uint32_t)g.ncells;
-            if (valid) {
-                bool inside = true;
-                int64_t c[3];
-                float tx = 0.0f;
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    inside = inside && (p[j] >= g.lo[j]) && (p[j] <= g.hi[j]);
-                    const float t = (p[j] - g.lo[j]) * g.invc[j];
-                    int64_t ci = (int64_t)floorf(t);
-                    ci = ci < 0 ? 0 : ci;
-                    ci = ci > g.cells[j] - 1 ? g.cells[j] - 1 : ci;
-                    c[j] = ci;
-                    if (j == 0) tx = t;
-                }
-                if (inside) {
-                    // the quarter of the cell along x: floor(4 (t - c)), exact
-                    // in float32 (t - c is exact, the product by 4 too)
-                    const float fq = floorf((tx - (float)c[0]) * (float)kSub);
-                    const uint32_t qx = fq < 0.0f ? 0u : (fq > (float)(kSub - 1) ? kSub - 1 : (uint32_t)fq);
-                    key = kSub * (uint32_t)(c[0] + (int64_t)g.cells[0] * (c[1] + (int64_t)g.cells[1] * c[2])) + qx;
-                }
-            }
+            const uint32_t key = query_key(q, g, (uint32_t)i);
             keys[i] = key;
             ids[i] = (uint32_t)i;
             hist.add(key);
         }
     }
     hist.finish_tile(blockIdx.x);
+}
+
+__global__ __launch_bounds__(kSmallBlock) void k_order_queries_small(QueryParams q, GridParams g, int bits,
+                                                                     uint32_t *__restrict__ keys,
+                                                                     uint32_t *__restrict__ order) {
+    __shared__ SmallSortLds L;
+    small_sort(L, (uint32_t)q.n, bits, [&](uint32_t i) { return query_key(q, g, i); }, keys, order);
 }
 
 // The queries of a quarter of a cell in spatial order, for the dense cells'
@@ -1451,6 +1462,15 @@ hipError_t launch_count_sample_pairs(const QueryParams &q, const GridParams &g, 
     if (e != hipSuccess || q.n <= 0) return e;
     hipLaunchKernelGGL(k_count_sample_pairs, dim3((uint32_t)((q.n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, q, g,
                        rec, gids, cell_off, plan_keys, plan_pos, T, totals);
+    return hipGetLastError();
+}
+
+hipError_t launch_order_queries_small(const QueryParams &q, const GridParams &g, int bits, uint32_t *keys,
+                                      uint32_t *order, hipStream_t s) {
+    if (q.n <= 0) return hipSuccess;
+    prof_begin("order_small", s);
+    hipLaunchKernelGGL(k_order_queries_small, dim3(1), dim3(kSmallBlock), 0, s, q, g, bits, keys, order);
+    prof_end("order_small", s);
     return hipGetLastError();
 }
 
