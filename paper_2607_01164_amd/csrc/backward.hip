@@ -246,15 +246,6 @@ __device__ __forceinline__ float bperm_f(uint32_t src, float v) {
     return __int_as_float(__builtin_amdgcn_ds_bpermute((int)src, __float_as_int(v)));
 }
 
-// Row `row` of `ny` rows a layer as (yy, zz), by a float reciprocal below 2^21
-// rows: (row + 1/2) / ny lies at least 1/(2 ny) from an integer; v_rcp (1 ulp)
-// and the product err by less than 1.5 2^-23 (row + 1/2) / ny, which cannot
-// cross it while row < 2^21.
-__device__ __forceinline__ void row_yz(uint32_t row, uint32_t ny, bool fdiv, uint32_t &yy, uint32_t &zz) {
-    zz = fdiv ? (uint32_t)(((float)row + 0.5f) * __builtin_amdgcn_rcpf((float)ny)) : row / ny;
-    yy = row - zz * ny;
-}
-
 // The voxels a Gaussian's rows can hold on a grid: x0 .. x1 of its box, and
 // the rows y0 .. y0 + ny - 1, z0 .. z0 + nz - 1 that its cutoff ellipsoid
 // reaches. Q >= (U22 dz)^2, and over x and z Q is at least dy^2 U11^2 / (1 +

@@ -12,6 +12,7 @@
 //    same reason: box sizes vary by orders of magnitude in 3D).
 // The pairs are then sorted by key (primitives.hip) and the per-cell ranges
 // taken from the sorted keys.
+#include <algorithm>
 #include "expand.h"
 #include "internal.h"
 #include "radix.h"
@@ -160,15 +161,15 @@ __device__ uint32_t row_cells(const SpanRec &p, const float mu[3], int x0, int x
 // pos and nth being the cells and the rows with cells among lane o's
 // earlier rows (nth only when count_rows, which must be wave-uniform).
 // acc and nrow are the wave's 64 LDS words each; they end holding every
-// lane's totals (nrow only when count_rows).
-template <class Cells, class Visit>
+// lane's totals (nrow, whose words start at 0, only when count_rows, and only
+// for the boxes o with counted(o)).
+template <class Counted, class Cells, class Visit>
 __device__ __forceinline__ void walk_rows(uint32_t R, uint32_t lane, uint32_t *acc, uint32_t *nrow, bool count_rows,
-                                          Cells &&cells, Visit &&visit) {
+                                          Counted &&counted, Cells &&cells, Visit &&visit) {
     const uint32_t incl = wave_incl_sum(R);
     const uint32_t E = __builtin_amdgcn_readlane(incl, kWave - 1);
     const uint32_t excl = incl - R;
     acc[lane] = 0;
-    nrow[lane] = 0;
     __builtin_amdgcn_wave_barrier();
     uint32_t j0 = 0;  // first box whose rows are not finished before the window
     for (uint32_t e0 = 0; e0 < E; e0 += kWave) {
@@ -178,7 +179,7 @@ __device__ __forceinline__ void walk_rows(uint32_t R, uint32_t lane, uint32_t *a
         uint32_t o = j0, base = __builtin_amdgcn_readlane(excl, j0);
         for (uint32_t jb = j0; jb + 1 < (uint32_t)kWave; ++jb) {
             const uint32_t bnd = __builtin_amdgcn_readlane(incl, jb);
-            if (bnd >= e0 + kWave) break;
+            if (bnd >= e0 + kWave || bnd >= E) break;
             if (e >= bnd) {
                 o = jb + 1;
                 base = bnd;
@@ -204,23 +205,28 @@ __device__ __forceinline__ void walk_rows(uint32_t R, uint32_t lane, uint32_t *a
         __builtin_amdgcn_wave_barrier();
         if (last) {
             acc[o] = pos + len;
-            nrow[o] = nth + has;
+            if (count_rows && counted(o)) nrow[o] = nth + has;
         }
         __builtin_amdgcn_wave_barrier();
     }
 }
 
-// The marks and the record counter that the preprocess starts from, cleared by
-// one launch: the cells' marks, then (the thread after them) the counter.
+// What the preprocess starts from, cleared by one launch: the cells' marks,
+// the record counter, and the group sums (where it adds to them).
 __global__ __launch_bounds__(kBlock) void k_clear_marks(uint32_t *__restrict__ marks, int64_t words,
-                                                        uint32_t *__restrict__ rtotal) {
+                                                        uint32_t *__restrict__ rtotal, uint64_t *__restrict__ sums,
+                                                        int64_t nsums) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i < words) marks[i] = 0u;
+    if (i < nsums) sums[i] = 0ull;
     if (i == words) *rtotal = 0u;
 }
 
 constexpr int kPreBlock = kWave;  // one wave per workgroup: the row walk is per wave
+constexpr int kSumGroup = 64;     // Gaussians of one pair-count sum
 
+// PER Gaussians a wave (lanes past PER only walk rows; see preprocess_per).
+template <int PER>
 __global__ __launch_bounds__(kPreBlock) void k_preprocess(const float *__restrict__ mean, const float *__restrict__ scale,
                                                        const float *__restrict__ rot, const float *__restrict__ value,
                                                        const float *__restrict__ weight, int64_t n, GridParams g,
@@ -234,15 +240,20 @@ __global__ __launch_bounds__(kPreBlock) void k_preprocess(const float *__restric
     // that walk their rows
     __shared__ SpanRec s_sp[kPreBlock];
     __shared__ float s_mu[3][kPreBlock];
-    __shared__ int s_box[4][kPreBlock];  // x0, x1, y0, z0
-    __shared__ uint32_t s_ny[kPreBlock];
-    __shared__ uint32_t s_acc[kPreBlock], s_nrow[kPreBlock], s_rb[kPreBlock], s_trim[kPreBlock];
-    // run bytes of the trim-1 boxes, word w of box t holding rows 4w..4w+3
+    __shared__ int s_box[3][kPreBlock];  // x0, y0, z0
+    __shared__ uint32_t s_info[kPreBlock];  // trimmed boxes: nx - 1, ny << 16, trim << 29
+    __shared__ uint32_t s_acc[kPreBlock];
+    // run bytes of the trim-1 boxes, word w of box t holding rows 4w..4w+3;
+    // trim-2 boxes have their first record in word 0 and the rows with cells
+    // in word 1 (the words shared bring a wave's LDS to 10 KB: 16 waves a
+    // compute unit instead of 14)
     __shared__ uint32_t s_code[kLineRows / 4][kPreBlock];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    static_assert(kRecNxMax <= 1u << 16 && kTrimRowsMax < 1u << 13, "s_info's fields");
+    static_assert(kSumGroup % PER == 0, "a wave's Gaussians lie in one group");
     const uint32_t tid = threadIdx.x, lane = tid % kWave;
+    const int64_t i = (int64_t)blockIdx.x * PER + tid;
     if (i == 0) count[n] = 0;  // the element after the last count, for the offsets' scan
-    const bool active = i < n;
+    const bool active = tid < (uint32_t)PER && i < n;
     float mu[3] = {0.0f, 0.0f, 0.0f}, s[3] = {1.0f, 1.0f, 1.0f}, q[4] = {1.0f, 0.0f, 0.0f, 0.0f};
     float v = 0.0f, w = 0.0f;
     if (active) {
@@ -329,47 +340,52 @@ __global__ __launch_bounds__(kPreBlock) void k_preprocess(const float *__restric
         wb = __builtin_amdgcn_readlane(wb, kWave - 1);
         const uint64_t at = (uint64_t)wb + (rincl - need);
         if (trim == 2 && at + need > (uint64_t)rcap) trim = 0;
-        s_rb[tid] = (uint32_t)at;
-        if (trim == 2) rbase[i] = (uint32_t)at;
+#pragma unroll
+        for (uint32_t k = 0; k < kLineRows / 4; ++k) s_code[k][tid] = kRunEmpty * 0x01010101u;
+        if (trim == 2) {
+            rbase[i] = (uint32_t)at;
+            s_code[0][tid] = (uint32_t)at;
+            s_code[1][tid] = 0;
+        }
     }
     if (trim == 0) nrows = 0;
-    s_trim[tid] = trim;
     s_mu[0][tid] = mu[0];
     s_mu[1][tid] = mu[1];
     s_mu[2][tid] = mu[2];
     s_box[0][tid] = lo_c[0];
-    s_box[1][tid] = hi_c[0];
-    s_box[2][tid] = lo_c[1];
-    s_box[3][tid] = lo_c[2];
-    s_ny[tid] = (uint32_t)(hi_c[1] - lo_c[1] + 1);
-#pragma unroll
-    for (uint32_t k = 0; k < kLineRows / 4; ++k) s_code[k][tid] = kRunEmpty * 0x01010101u;
+    s_box[1][tid] = lo_c[1];
+    s_box[2][tid] = lo_c[2];
+    s_info[tid] = trim == 0 ? 0u
+                            : (uint32_t)(hi_c[0] - lo_c[0]) | (uint32_t)(hi_c[1] - lo_c[1] + 1) << 16 | trim << 29;
     __builtin_amdgcn_wave_barrier();
     // the cells and the rows with cells of every trimmed box; the run bytes
     // of the trim-1 boxes, the row records of the trim-2 boxes
     walk_rows(
-        nrows, lane, s_acc, s_nrow, rsum > 0,
+        nrows, lane, s_acc, s_code[1], rsum > 0, [&](uint32_t o) { return s_info[o] >> 29 == 2; },
         [&](uint32_t o, uint32_t r, uint32_t &first) {
             const float mo[3] = {s_mu[0][o], s_mu[1][o], s_mu[2][o]};
-            const uint32_t ny = s_ny[o], zz = r / ny;
-            return row_cells(s_sp[o], mo, s_box[0][o], s_box[1][o], s_box[2][o] + (int)(r - zz * ny),
-                             s_box[3][o] + (int)zz, sg, first);
+            const uint32_t info = s_info[o];
+            uint32_t yy, zz;
+            row_yz(r, (info >> 16) & 0x1FFFu, true, yy, zz);  // at most kTrimRowsMax rows
+            const int x0 = s_box[0][o];
+            return row_cells(s_sp[o], mo, x0, x0 + (int)(info & 0xFFFFu), s_box[1][o] + (int)yy, s_box[2][o] + (int)zz,
+                             sg, first);
         },
         [&](uint32_t o, uint32_t r, uint32_t first, uint32_t len, uint32_t pos, uint32_t nth) {
-            if (s_trim[o] == 1) {
+            if (s_info[o] >> 29 == 1) {
                 ((uint8_t *)&s_code[r >> 2][o])[r & 3] = (uint8_t)(first | ((first + len - 1) << 4));
             } else {
                 RowRec rr;
                 rr.pos = pos;
                 rr.row = (uint16_t)r;
                 rr.first = (uint16_t)first;
-                rows[(size_t)s_rb[o] + nth] = rr;
+                rows[(size_t)s_code[0][o] + nth] = rr;
             }
         });
     __builtin_amdgcn_wave_barrier();
     uint32_t nrec = 0;
     if (trim != 0) cnt = s_acc[tid];
-    if (trim == 2) nrec = s_nrow[tid];
+    if (trim == 2) nrec = s_code[1][tid];
     if (trim == 1) {
         uint4 *dst = (uint4 *)(lines + (size_t)i * kLineRows);
 #pragma unroll
@@ -377,10 +393,17 @@ __global__ __launch_bounds__(kPreBlock) void k_preprocess(const float *__restric
             dst[k] = make_uint4(s_code[4 * k][tid], s_code[4 * k + 1][tid], s_code[4 * k + 2][tid],
                                 s_code[4 * k + 3][tid]);
     }
-    // the workgroup's pair count (one wave), for the offsets' scan
+    // the workgroup's pair count (one wave), for the offsets' scan; several
+    // waves add to a group's sum (integers: the order does not matter)
     {
         const uint64_t tot = wave_incl_sum64(active ? cnt : 0ull);
-        if (lane == kWave - 1) block_sum[blockIdx.x] = tot;
+        if (lane == kWave - 1) {
+            if (PER == kSumGroup)
+                block_sum[blockIdx.x] = tot;
+            else
+                atomicAdd((unsigned long long *)block_sum + (uint64_t)blockIdx.x * PER / kSumGroup,
+                          (unsigned long long)tot);
+        }
     }
     if (!active) return;
     count[i] = cnt;
@@ -407,6 +430,8 @@ __global__ __launch_bounds__(kPreBlock) void k_preprocess(const float *__restric
         Rd[2][2] = 1.0 - 2.0 * (x * x + y * y);
         // the inverse covariance A = R S^-2 R^T and its Cholesky factor U
         // (upper triangular, A = U^T U)
+        const double is2[3] = {1.0 / ((double)s[0] * (double)s[0]), 1.0 / ((double)s[1] * (double)s[1]),
+                               1.0 / ((double)s[2] * (double)s[2])};
         double A[3][3];
 #pragma unroll
         for (int j = 0; j < 3; ++j)
@@ -414,7 +439,7 @@ __global__ __launch_bounds__(kPreBlock) void k_preprocess(const float *__restric
             for (int l = 0; l < 3; ++l) {
                 double acc = 0.0;
 #pragma unroll
-                for (int k = 0; k < 3; ++k) acc += Rd[j][k] * Rd[l][k] / ((double)s[k] * (double)s[k]);
+                for (int k = 0; k < 3; ++k) acc += Rd[j][k] * Rd[l][k] * is2[k];
                 A[j][l] = acc;
             }
         const double u00 = sqrt(A[0][0]);
@@ -734,22 +759,37 @@ hipError_t launch_gauss_keys(const CellBox *box, int64_t n, const GridParams &g,
     return hipGetLastError();
 }
 
+// Gaussians per wave of the preprocess: 64, and fewer in small sets, which
+// would otherwise take one wave or less a SIMD, each walking a long chain of
+// float64 work alone. About 3,000 to 4,000 waves are best (us, with 64 / 32 /
+// 16 / 8 a wave): 4,096 Gaussians 17.5 / 13.1 / 10.2 / 8.5; 50,021 of a point
+// cloud 40.4 / 28.5 / 25.0 / 29.5; 131,072 32.3 / 33.4 / 37.8 / 51.3; 524,288
+// 172 / 191 / 226 / 255. (With one reciprocal per scale in place of the
+// record's 18 float64 divisions and 10 KB of LDS a wave, 262,144 Gaussians
+// take 40 to 44 us at 64 a wave where they took 53.)
+static int preprocess_per(int64_t n) { return n <= 24576 ? 8 : n <= 65536 ? 16 : n <= 98304 ? 32 : kSumGroup; }
+
 hipError_t launch_preprocess(const float *mean, const float *scale, const float *rot, const float *value,
                              const float *weight, int64_t n, const GridParams &g, float rci, Record *rec, CellBox *box,
                              uint8_t *lines, RowRec *rows, uint32_t *rbase, uint32_t *rtotal, int64_t rcap,
                              uint8_t *cell_coarse, uint64_t *count, uint64_t *block_sum, hipStream_t s) {
-    // one thread per Gaussian (thread 0 also writes count[n]): for n a
-    // multiple of 64 the launch fits one round of the chip
+    // thread 0 also writes count[n]
     const int64_t threads = n > 0 ? n : 1;
-    const uint32_t blocks = (uint32_t)((threads + kPreBlock - 1) / kPreBlock);
+    const int per = preprocess_per(n);
+    const uint32_t blocks = (uint32_t)((threads + per - 1) / per);
     prof_begin("preprocess", s);
     const int64_t words = (g.ncells + 3) / 4;
-    hipLaunchKernelGGL(k_clear_marks, dim3((uint32_t)((words + kBlock) / kBlock)), dim3(kBlock), 0, s,
-                       (uint32_t *)cell_coarse, words, rtotal);
+    const int64_t nsums = per < kSumGroup ? (threads + kSumGroup - 1) / kSumGroup : 0;
+    hipLaunchKernelGGL(k_clear_marks, dim3((uint32_t)((std::max(words, nsums) + kBlock) / kBlock)), dim3(kBlock), 0, s,
+                       (uint32_t *)cell_coarse, words, rtotal, block_sum, nsums);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_preprocess, dim3(blocks), dim3(kPreBlock), 0, s, mean, scale, rot, value, weight, n, g, rci,
-                       rec, box, lines, rows, rbase, rtotal, rcap, cell_coarse, count, block_sum);
+    const auto kernel = per == 8    ? k_preprocess<8>
+                        : per == 16 ? k_preprocess<16>
+                        : per == 32 ? k_preprocess<32>
+                                    : k_preprocess<kSumGroup>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kPreBlock), 0, s, mean, scale, rot, value, weight, n, g, rci, rec,
+                       box, lines, rows, rbase, rtotal, rcap, cell_coarse, count, block_sum);
     prof_end("preprocess", s);
     return hipGetLastError();
 }

@@ -400,6 +400,14 @@ __device__ __forceinline__ void query_position(const QueryParams &q, const GridP
         pz = q.points[3 * (uint64_t)pid + 2];
     }
 }
+// Row `row` of `ny` rows a layer as (yy, zz), by a float reciprocal below 2^21
+// rows: (row + 1/2) / ny lies at least 1/(2 ny) from an integer; v_rcp (1 ulp)
+// and the product err by less than 1.5 2^-23 (row + 1/2) / ny, which cannot
+// cross it while row < 2^21.
+__device__ __forceinline__ void row_yz(uint32_t row, uint32_t ny, bool fdiv, uint32_t &yy, uint32_t &zz) {
+    zz = fdiv ? (uint32_t)(((float)row + 0.5f) * __builtin_amdgcn_rcpf((float)ny)) : row / ny;
+    yy = row - zz * ny;
+}
 // Keys and sort in one launch, for at most kSmallSort queries (radix.h).
 hipError_t launch_order_queries_small(const QueryParams &q, const GridParams &g, int bits, uint32_t *keys,
                                       uint32_t *order, hipStream_t s);
