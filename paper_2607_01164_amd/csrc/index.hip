@@ -476,38 +476,28 @@ __global__ __launch_bounds__(kPreBlock) void k_preprocess(const float *__restric
     }
 }
 
-// In-place inclusive max-scan of a tile's kExpandTile marks (kExpandItems
-// consecutive marks per thread, then across the block).
-// Inclusive max-scan of a tile of 64-bit marks in LDS (kExpandItems per
-// thread, then across lanes and waves).
-__device__ void tile_max_scan64(uint64_t *mark, uint64_t *wmax) {
-    const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    uint64_t run = 0;
-    const uint32_t b0 = tid * kExpandItems;
+// The last mark at or before each of a tile's slots, as its place + 1 (the
+// marks' top 12 bits): thread (wave, lane) gets those of slots 64 (wave
+// kExpandItems + i) + lane. Rows of 64 slots are scanned with DPP; wmax holds
+// a word per wave.
+__device__ __forceinline__ void tile_last_marks(const uint64_t *mark, uint32_t *wmax, uint32_t (&last)[kExpandItems]) {
+    const uint32_t wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    uint32_t run = 0;
+#pragma unroll
+    for (int i = 0; i < kExpandItems; ++i)
+        last[i] = (uint32_t)(mark[(wave * kExpandItems + (uint32_t)i) * kWave + lane] >> 52);
 #pragma unroll
     for (int i = 0; i < kExpandItems; ++i) {
-        const uint64_t h = mark[b0 + i];
-        run = h > run ? h : run;
-        mark[b0 + i] = run;
+        const uint32_t x = wave_incl_max(last[i]);
+        last[i] = x > run ? x : run;
+        run = __builtin_amdgcn_readlane(last[i], kWave - 1);
     }
-    uint64_t incl = run;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint64_t y = __shfl_up(incl, o, 64);
-        if (lane >= (uint32_t)o) incl = y > incl ? y : incl;
-    }
-    uint64_t excl = __shfl_up(incl, 1, 64);
-    if (lane == 0) excl = 0;
-    if (lane == kWave - 1) wmax[wave] = incl;
+    if (lane == 0) wmax[wave] = run;
     __syncthreads();
-    uint64_t carry = excl;
+    uint32_t carry = 0;
     for (uint32_t w = 0; w < wave; ++w) carry = wmax[w] > carry ? wmax[w] : carry;
 #pragma unroll
-    for (int i = 0; i < kExpandItems; ++i) {
-        const uint64_t h = mark[b0 + i];
-        mark[b0 + i] = h > carry ? h : carry;
-    }
-    __syncthreads();
+    for (int i = 0; i < kExpandItems; ++i) last[i] = last[i] > carry ? last[i] : carry;
 }
 
 // Pair-parallel emit (Sec. 4.1.2): workgroup t writes pairs
@@ -515,7 +505,7 @@ __device__ void tile_max_scan64(uint64_t *mark, uint64_t *wmax) {
 // of cells (fixed y, z; the whole box row or its run) that reaches into the
 // tile marks its first slot p in the tile with
 //   (p + 1) << 52 | (Gaussian - first Gaussian of the tile) << 32 | key(p),
-// so a max-scan hands every slot the mark of its row, and slot s of that row
+// so a max-scan of the slots hands every slot its row's mark, and slot s of that row
 // holds cell key(p) + s - p (keys grow by one along x). The Gaussian offset
 // takes 20 bits; a tile whose Gaussian range is wider (many Gaussians without
 // cells) finds the Gaussian of each slot by binary search instead.
@@ -526,7 +516,7 @@ __global__ __launch_bounds__(kBlock) void k_emit(const uint64_t *__restrict__ pa
                                                  GridParams g, uint32_t *__restrict__ keys,
                                                  uint32_t *__restrict__ gids, RadixPass0 pass0) {
     __shared__ uint64_t mark[kExpandTile];
-    __shared__ uint64_t wmax[kWavesPerBlock];
+    __shared__ uint32_t wmax[kWavesPerBlock];
     // trim-2 boxes of the current 256 Gaussians that reach into the tile:
     // their records [ja, jb) there, placed by the whole block (up to
     // kEmitTasks of them; a box past those places its records itself)
@@ -680,13 +670,14 @@ __global__ __launch_bounds__(kBlock) void k_emit(const uint64_t *__restrict__ pa
         if (tid == 0) t_n = 0;
     }
     __syncthreads();
-    tile_max_scan64(mark, wmax);
-#pragma unroll 2
+    uint32_t last[kExpandItems];
+    tile_last_marks(mark, wmax, last);
+#pragma unroll
     for (int i = 0; i < kExpandItems; ++i) {
-        const uint32_t slot = (uint32_t)i * kBlock + tid;
+        const uint32_t slot = ((tid / kWave) * kExpandItems + (uint32_t)i) * kWave + tid % kWave;
         if (slot < tile_cnt) {
-            const uint64_t m = mark[slot];
-            const uint32_t p = (uint32_t)(m >> 52) - 1u;
+            const uint32_t p = last[i] > 0 ? last[i] - 1u : 0u;  // (the tile's first slot is marked)
+            const uint64_t m = mark[p];
             const uint32_t key = (uint32_t)m + (slot - p);
             int64_t gg;
             if (fold)
