@@ -104,11 +104,15 @@ __global__ __launch_bounds__(kBlock) void k_radix_upsweep(const uint32_t *__rest
     __syncthreads();
     const uint32_t tile = xcd_block(blockIdx.x, gridDim.x);
     const int64_t base = (int64_t)tile * (kBlock * ITEMS);
+    uint32_t k[ITEMS];  // loaded before the first count
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int64_t idx = base + (int64_t)i * kBlock + threadIdx.x;
-        if (idx < n) atomicAdd(&h[(keys[idx] >> shift) & mask], 1u);
+        k[i] = keys[idx < n ? idx : n - 1];
     }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (base + (int64_t)i * kBlock + threadIdx.x < n) atomicAdd(&h[(k[i] >> shift) & mask], 1u);
     __syncthreads();
     for (uint32_t d = threadIdx.x; d < ndig; d += kBlock) table[(size_t)d * nb + tile] = h[d];
 }
