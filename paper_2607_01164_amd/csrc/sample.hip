@@ -14,9 +14,11 @@
 // hold 16 queries instead of 64.
 //
 // Grid queries (Sec. 4.1.3, Fig. 4 C): one wavefront per (cell, 64 voxels of
-// the cell), the voxels as tiles of 16 (walk_tiles). Measured against the
-// vector form: 2^27 voxels and 2^20 clustered Gaussians 5.28 -> 5.07 ms, 128^3
-// voxels and 131,072 Gaussians 109 -> 96 us.
+// the cell). Cells of at most 48 voxels take them as tiles of 16 (walk_tiles:
+// one voxel a cell 0.50 -> 0.21 ms for 197,579 cells and 529,113 Gaussians);
+// larger ones take a voxel a lane as U (p - mu), whose rounding does not grow
+// with the cell (tiles: 2^27 voxels, 64 a cell, 5.38 -> 5.06 ms, but samples
+// within rounding of the threshold tau change sides more often).
 //
 // Voxel-list, point and jittered queries (Sec. 5.1.2): the queries are first
 // ordered by cell and, inside a cell, by quarter of the cell along x
@@ -418,7 +420,8 @@ __device__ __forceinline__ void walk_tiles(WaveLds &L, uint32_t lane, const Reco
     Vo = tile_sum(V[0], V[1], V[2], V[3]);
 }
 
-// walk_tiles for n <= 64 queries.
+// walk_tiles for n <= kTileQueries queries.
+constexpr uint32_t kTileQueries = 3 * kTile;
 __device__ __forceinline__ void walk_lanes(uint32_t n, WaveLds &L, uint32_t lane, const Record *__restrict__ rec,
                                            const uint32_t *__restrict__ gids, uint32_t ja, uint32_t jb, float ax,
                                            float ay, float az, float ox, float oy, float oz, float T, float &Io,
@@ -427,10 +430,8 @@ __device__ __forceinline__ void walk_lanes(uint32_t n, WaveLds &L, uint32_t lane
         walk_tiles<1>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
     else if (n <= 2 * kTile)
         walk_tiles<2>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
-    else if (n <= 3 * kTile)
-        walk_tiles<3>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
     else
-        walk_tiles<4>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
+        walk_tiles<3>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
 }
 
 __global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams q, GridParams g, const Record *__restrict__ rec,
@@ -459,12 +460,13 @@ __global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams
     const uint32_t j0 = ((ConstU32 *)cell_off)[cell], j1 = ((ConstU32 *)cell_off)[cell + 1];
     float I = 0.0f, V = 0.0f;
     if (j0 < j1) {
-        if (__builtin_amdgcn_readfirstlane(cell_coarse[cell]) != 0) {
+        // (vpc: every chunk of a cell takes the same form)
+        if (vpc > kTileQueries || __builtin_amdgcn_readfirstlane(cell_coarse[cell]) != 0) {
             walk_staged(rec, gids, j0, j1, lane, L.b, px, py, pz, T, I, V);
         } else {
             float ox, oy, oz;
             cell_centre(g, cell, ox, oy, oz);
-            walk_lanes(vpc - chunk * kWave, L, lane, rec, gids, j0, j1, px - ox, py - oy, pz - oz, ox, oy, oz, T, I, V);
+            walk_lanes(vpc, L, lane, rec, gids, j0, j1, px - ox, py - oy, pz - oz, ox, oy, oz, T, I, V);
         }
     }
     if (local < vpc) {
@@ -1003,12 +1005,14 @@ __device__ __forceinline__ void dense_item(uint32_t lane, uint32_t qa, uint32_t 
 // fewer than kLevel2Queries are one box. The level depends on the cell's
 // count only and the boxes on the grid, so a query's sums do not depend on
 // how the queries were split into items.
-// Measured, forward with its query ordering: 10^8 clustered points in 64^3
-// cells (381 a cell) 35.3 ms without boxes and 30.9 with them; 2^21 clustered points in 64^3 (8 a cell)
-// 1.17 ms without boxes and 1.24 with them, most cells having no use for the
-// order by place.
-constexpr int64_t kBoxedMean = 64;
-constexpr uint32_t kLevel2Queries = 320, kLevel4Queries = 1536;
+// A launch whose cells would mostly be one box each has no use for the order
+// by place: the mean is the count from which they are cut. Measured, forward
+// with its query ordering: 10^8 clustered points in 64^3 cells (381 a cell)
+// 35.3 ms without boxes and 30.9 with them; 2^21 clustered points in 64^3 (8 a
+// cell) 1.17 ms without and 1.24 with them; a step on 1.7 M uniform voxels
+// in 25^3 cells (110 a cell) 615 us without and 665 with them.
+constexpr int64_t kBoxedMean = 320;
+constexpr uint32_t kLevel2Queries = (uint32_t)kBoxedMean, kLevel4Queries = 1536;
 constexpr uint32_t kWholeCell = 32;  // no level: one box
 __device__ __forceinline__ uint32_t dense_level(uint32_t n) {
     return n < kLevel2Queries ? kWholeCell : (n < kLevel4Queries ? 2u : 4u);
