@@ -34,15 +34,19 @@ __device__ __forceinline__ float eval_pair(const Record &r, float4 p, float T) {
 
 // Position of every query in plan order (the walk below reads them
 // contiguously); queries outside the domain sit in the outside bucket,
-// which no Gaussian visits.
+// which no Gaussian visits. PLACED: the ordering has written them already
+// (boxed launches), with the places that gs_sample_planned reads in w.
+template <bool PLACED>
 __global__ __launch_bounds__(kBlock) void k_plan_positions(QueryParams q, GridParams g, const uint32_t *order,
                                                            float4 *pos, double *acc) {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= q.n) return;
-    float px, py, pz;
-    bool valid;
-    query_position(q, g, order[k], px, py, pz, valid);
-    pos[k] = make_float4(px, py, pz, 0.0f);
+    if (!PLACED) {
+        float px, py, pz;
+        bool valid;
+        query_position(q, g, order[k], px, py, pz, valid);
+        pos[k] = make_float4(px, py, pz, 0.0f);
+    }
     acc[2 * k] = 0.0;
     acc[2 * k + 1] = 0.0;
 }
@@ -132,7 +136,10 @@ hipError_t launch_sample_gauss_major(const QueryParams &q, const GridParams &g, 
     double *acc = (double *)work;
     const uint32_t nb = (uint32_t)((q.n + kBlock - 1) / kBlock);
     prof_begin("gm_positions", s);
-    hipLaunchKernelGGL(k_plan_positions, dim3(nb), dim3(kBlock), 0, s, q, g, order, pr.pos, acc);
+    if (boxed_launch(q.n, g.ncells))
+        hipLaunchKernelGGL(k_plan_positions<true>, dim3(nb), dim3(kBlock), 0, s, q, g, order, pr.pos, acc);
+    else
+        hipLaunchKernelGGL(k_plan_positions<false>, dim3(nb), dim3(kBlock), 0, s, q, g, order, pr.pos, acc);
     prof_end("gm_positions", s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
