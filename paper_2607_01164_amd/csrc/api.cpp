@@ -726,8 +726,8 @@ gs_status gs_sample(const gs_gaussians *gauss, const gs_index *index, const gs_q
     IndexWork w = index_layout(index->work, index->n_gauss, &index->grid, index->capacity);
     const float T = cutoff_T(index->tau);
     if (query->kind == GS_QUERY_GRID) {
-        GS_TRY(launch_sample_grid(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets, T, index->tau,
-                                  out_value, out_influence, stream),
+        GS_TRY(launch_sample_grid(qp, gp, w.rec, index->gids, index->cell_offsets, T, index->tau, out_value,
+                                  out_influence, stream),
                "gs_sample: grid sampler");
         return GS_OK;
     }
@@ -762,8 +762,8 @@ gs_status gs_sample_planned(const gs_gaussians *gauss, const gs_index *index, co
     const QueryParams qp = query_params(query, &index->grid);
     if (query->kind == GS_QUERY_GRID) {
         IndexWork w = index_layout(index->work, index->n_gauss, &index->grid, index->capacity);
-        GS_TRY(launch_sample_grid(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets,
-                                  cutoff_T(index->tau), index->tau, out_value, out_influence, stream),
+        GS_TRY(launch_sample_grid(qp, gp, w.rec, index->gids, index->cell_offsets, cutoff_T(index->tau), index->tau,
+                                  out_value, out_influence, stream),
                "gs_sample_planned: grid sampler");
         return GS_OK;
     }

@@ -334,8 +334,8 @@ hipError_t launch_preprocess(const float *mean, const float *scale, const float 
                              uint8_t *lines, RowRec *rows, uint32_t *rbase, uint32_t *rtotal, int64_t rcap,
                              uint8_t *cell_coarse, uint64_t *count, uint64_t *block_sum, hipStream_t s);
 // A Gaussian is coarse when the cell diagonal passes kOffsetCells times its
-// largest scale: the forward then evaluates the cells of its box as U (p -
-// mu) instead of by offsets to the cell's centre.
+// largest scale: the forward's dense walks then evaluate the cells of its box
+// as U (p - mu) instead of by offsets to the cell's centre.
 #ifndef GS_OFFSET_CELLS
 #define GS_OFFSET_CELLS 64.0
 #endif
@@ -416,10 +416,9 @@ hipError_t launch_order_queries_small(const QueryParams &q, const GridParams &g,
 // the first sort digit's tile counts.
 hipError_t launch_query_keys(const QueryParams &q, const GridParams &g, uint32_t *keys, uint32_t *ids,
                              const RadixPass0 &pass0, hipStream_t s);
-// cell_coarse: the index's per-cell flags (launch_preprocess).
-hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint8_t *cell_coarse,
-                              const uint32_t *gids, const uint32_t *cell_off, float T, float tau, float *out_v,
-                              float *out_i, hipStream_t s);
+hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint32_t *gids,
+                              const uint32_t *cell_off, float T, float tau, float *out_v, float *out_i,
+                              hipStream_t s);
 // Whether a launch of nq ordered queries in ncells cells is boxed: its plan
 // order is then refined by place inside quarters of cells, and the plan holds
 // the positions in it (PlanResults::pos, the place in w) before the forward.
@@ -448,7 +447,8 @@ struct PlanResults {
 // ordering's last step).
 hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
                              hipStream_t s);
-// order: the plan's, the refined one in boxed launches.
+// cell_coarse: the index's per-cell flags (launch_preprocess). order: the
+// plan's, the refined one in boxed launches.
 hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec,
                                 const uint8_t *cell_coarse, const uint32_t *gids, const uint32_t *cell_off,
                                 const uint32_t *keys, const uint32_t *order, const uint32_t *point_off,

@@ -14,11 +14,8 @@
 // hold 16 queries instead of 64.
 //
 // Grid queries (Sec. 4.1.3, Fig. 4 C): one wavefront per (cell, 64 voxels of
-// the cell). Cells of at most 48 voxels take them as tiles of 16 (walk_tiles:
-// one voxel a cell 0.50 -> 0.21 ms for 197,579 cells and 529,113 Gaussians);
-// larger ones take a voxel a lane as U (p - mu), whose rounding does not grow
-// with the cell (tiles: 2^27 voxels, 64 a cell, 5.38 -> 5.06 ms, but samples
-// within rounding of the threshold tau change sides more often).
+// the cell), a voxel a lane; cells of at most 32 voxels split the list over
+// the lanes that are left (walk_split).
 //
 // Voxel-list, point and jittered queries (Sec. 5.1.2): the queries are first
 // ordered by cell and, inside a cell, by quarter of the cell along x
@@ -49,10 +46,7 @@ namespace {
 // one works through the dense part.
 constexpr int kSampWaves = 1;
 constexpr int kSampBlock = kSampWaves * kWave;
-// Waves per SIMD the samplers are compiled for. (A bound also keeps matrix
-// products' results in ordinary registers: with the whole register file to
-// itself the compiler puts them in accumulation registers and moves each out
-// again.)
+// Waves per SIMD the samplers are compiled for.
 constexpr int kSampPerSimd = 7;
 
 // Q' = Q log2(e) / 2 of a record at a point (record_q), G = 2^-Q'.
@@ -140,7 +134,11 @@ __device__ __forceinline__ void cell_centre(const GridParams &g, uint32_t c, flo
 }
 
 constexpr int kDenseWaves = kWavesPerBlock;  // waves of a dense item's workgroup
-constexpr int kDensePerSimd = 6;            // its LDS holds six workgroups a CU
+// Waves per SIMD (its LDS holds six workgroups a CU). A bound also keeps the
+// matrix products' results in ordinary registers: with the whole register file
+// to itself the compiler puts them in accumulation registers and moves each
+// out again.
+constexpr int kDensePerSimd = 6;
 constexpr uint32_t kTile = 16;              // queries of a matrix tile, and Gaussians
 
 // LDS of a dense item's workgroup. The records of up to kBlock candidates:
@@ -161,13 +159,6 @@ struct DenseLds {
     uint64_t ballot[2][kDenseWaves];
 };
 static_assert(sizeof(float4) * kRecordQuads * kWave * kDenseWaves <= sizeof(DenseLds::b), "staged records fit the rows");
-
-// LDS of a one-wave workgroup: planes of kWave rows (or staged records), the
-// rows' weights w and w v, and what their -c leave when rounded to float32.
-struct WaveLds {
-    float4 b[kRecordQuads * kWave];
-    float w[kWave], v[kWave], c[3][kWave];
-};
 
 __device__ __forceinline__ float4 *wave_records(DenseLds &L, uint32_t wave) {
     return &L.b[0][0] + kRecordQuads * kWave * wave;
@@ -363,83 +354,55 @@ __device__ __forceinline__ void walk_staged_r(const Record *__restrict__ rec, bo
 }
 
 
-// A wave alone against a wave-uniform list [ja, jb): up to 64 queries, one a
-// lane at offsets (ax, ay, az) from o, tile t < NT holding lanes 16 t .. 16 t +
-// 15, with every candidate, 64 staged at a time (their records loaded ahead
-// would cost the registers of a wave in eight). Lane l gets its query's sums. A query's sums depend on its
-// cell's list only: candidate j is always the (j - ja) % 16th of its tile. The
-// products carry what float32 leaves of c: without it u had a quarter more
-// rounding errors at the cutoff than U (p - mu), with it no more (counted
-// against 64-bit sums on grids; 2 % of the walk).
-template <uint32_t NT>
-__device__ __forceinline__ void walk_tiles(WaveLds &L, uint32_t lane, const Record *__restrict__ rec,
-                                           const uint32_t *__restrict__ gids, uint32_t ja, uint32_t jb, float ax,
-                                           float ay, float az, float ox, float oy, float oz, float T, float &Io,
-                                           float &Vo) {
-    const uint32_t k = lane >> 4;
-    float q[NT], I[4] = {0.0f, 0.0f, 0.0f, 0.0f}, V[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (uint32_t t = 0; t < NT; ++t) {
-        const int src = (int)(kTile * t + (lane & 15u));
-        q[t] = tile_operand(k, __shfl(ax, src, kWave), __shfl(ay, src, kWave), __shfl(az, src, kWave));
-    }
-    const float *rows = (const float *)(L.b + (lane & 15u)) + k;
-    constexpr uint32_t plane = 4u * kWave;  // floats from one row's plane to the next
+// walk_staged for a cell of at most 32 voxels: 2^sh lanes a query, lane l
+// taking query l >> sh with the candidates c0 + (l mod 2^sh) + 2^sh t of each
+// 64. With a voxel a lane the lanes past the cell's voxels idle through the
+// whole list (195,112 cells, 529,113 Gaussians: one voxel a cell 583 us, split
+// 185; 16 voxels 528 and 205; 32 voxels 533 and 353). Every lane of a query
+// gets its sums. (Matrix tiles take offsets from a point of the cell, whose
+// rounding grows with the cell against the Gaussians' smallest scales; they
+// took 251, 219 and 309 us.)
+__device__ __forceinline__ void walk_split(const Record *__restrict__ rec, const uint32_t *__restrict__ gids,
+                                           uint32_t ja, uint32_t jb, uint32_t lane, uint32_t sh, float4 *buf, float px,
+                                           float py, float pz, float T, float &I, float &V) {
+    const uint32_t slot = lane & ((1u << sh) - 1u);
     uint32_t gnext = 0;
-    if (ja + lane < jb) gnext = gids[ja + lane];
+    if (ja < jb) gnext = gids[ja + lane < jb ? ja + lane : jb - 1];
     for (uint32_t c0 = ja; c0 < jb; c0 += kWave) {
-        const bool live = c0 + lane < jb;
-        Record r = {};
-        if (live) r = load_record(rec, gnext);
-        float rest[3];
-        stage_rows(L.b + lane, kWave, live, r, ox, oy, oz, rest);
-        L.c[0][lane] = rest[0];
-        L.c[1][lane] = rest[1];
-        L.c[2][lane] = rest[2];
-        L.w[lane] = live ? r.f0.w : 0.0f;
-        L.v[lane] = live ? r.f1.w : 0.0f;
-        if (c0 + kWave + lane < jb) gnext = gids[c0 + kWave + lane];
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t left = jb - c0;
-        const uint32_t groups = left >= (uint32_t)kWave ? kWave / kTile : (left + kTile - 1) / kTile;
-        for (uint32_t gr = 0; gr < groups; ++gr) {
-            const float *p = rows + 4u * kTile * gr;
-            const float g0 = p[0], g1 = p[plane], g2 = p[2 * plane];
-            const float4 w = *(const float4 *)(L.w + kTile * gr + 4u * k);
-            const float4 v = *(const float4 *)(L.v + kTile * gr + 4u * k);
+        const float4 *src = (const float4 *)(rec + gnext);
 #pragma unroll
-            for (uint32_t t = 0; t < NT; ++t)
-                tile_pairs(q[t], g0, g1, g2, w, v, T, I[t], V[t], *(const mfma_f4 *)(L.c[0] + kTile * gr + 4u * k),
-                           *(const mfma_f4 *)(L.c[1] + kTile * gr + 4u * k),
-                           *(const mfma_f4 *)(L.c[2] + kTile * gr + 4u * k));
+        for (int qq = 0; qq < kRecordQuads; ++qq)
+            __builtin_amdgcn_global_load_lds((const void *)(src + qq),
+                                             (__attribute__((address_space(3))) void *)(buf + qq * kWave), 16, 0, 0);
+        if (c0 + kWave < jb) gnext = gids[c0 + kWave + lane < jb ? c0 + kWave + lane : jb - 1];
+        __builtin_amdgcn_s_waitcnt(0);
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t cnt = jb - c0 < (uint32_t)kWave ? jb - c0 : (uint32_t)kWave;
+        for (uint32_t s0 = 0; s0 < cnt; s0 += 1u << sh) {
+            const uint32_t s = s0 + slot;  // < kWave
+            if (s < cnt) {
+                Record a;
+                a.f0 = buf[s];
+                a.f1 = buf[kWave + s];
+                a.f2 = buf[2 * kWave + s];
+                accumulate(a, px, py, pz, T, I, V);
+            }
         }
-        // every lane has read the rows before the next chunk overwrites them
+        // every lane has read the planes before the next chunk overwrites them
         __builtin_amdgcn_wave_barrier();
     }
-    Io = tile_sum(I[0], I[1], I[2], I[3]);
-    Vo = tile_sum(V[0], V[1], V[2], V[3]);
+    for (uint32_t o = 1; o < 1u << sh; o <<= 1) {
+        I += __shfl_xor(I, (int)o, kWave);
+        V += __shfl_xor(V, (int)o, kWave);
+    }
 }
 
-// walk_tiles for n <= kTileQueries queries.
-constexpr uint32_t kTileQueries = 3 * kTile;
-__device__ __forceinline__ void walk_lanes(uint32_t n, WaveLds &L, uint32_t lane, const Record *__restrict__ rec,
-                                           const uint32_t *__restrict__ gids, uint32_t ja, uint32_t jb, float ax,
-                                           float ay, float az, float ox, float oy, float oz, float T, float &Io,
-                                           float &Vo) {
-    if (n <= kTile)
-        walk_tiles<1>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
-    else if (n <= 2 * kTile)
-        walk_tiles<2>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
-    else
-        walk_tiles<3>(L, lane, rec, gids, ja, jb, ax, ay, az, ox, oy, oz, T, Io, Vo);
-}
-
-__global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams q, GridParams g, const Record *__restrict__ rec,
-                                                        const uint8_t *__restrict__ cell_coarse,
+__global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams q, GridParams g, uint32_t sh,
+                                                        const Record *__restrict__ rec,
                                                         const uint32_t *__restrict__ gids,
                                                         const uint32_t *__restrict__ cell_off, float T, float tau,
                                                         float *__restrict__ out_v, float *__restrict__ out_i) {
-    __shared__ WaveLds L;
+    __shared__ float4 s_rec[kRecordQuads * kWave];
     const uint32_t rx = (uint32_t)(q.dims[0] / g.cells[0]);
     const uint32_t ry = (uint32_t)(q.dims[1] / g.cells[1]);
     const uint32_t rz = (uint32_t)(q.dims[2] / g.cells[2]);
@@ -449,7 +412,7 @@ __global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams
     // ncells wpc < 2^32: at most a wave per cell and one per 64 voxels
     const uint32_t cell = blockIdx.x / wpc;
     const uint32_t chunk = blockIdx.x - cell * wpc;
-    const uint32_t local = chunk * kWave + lane;
+    const uint32_t local = (chunk * kWave + lane) >> sh;
     const uint32_t nx = (uint32_t)g.cells[0], ny = (uint32_t)g.cells[1];
     const uint32_t cyz = cell / nx, cx = cell - cyz * nx, cz = cyz / ny, cy = cyz - cz * ny;
     const uint32_t lyz = local / rx, lx = local - lyz * rx, lz = lyz / ry, ly = lyz - lz * ry;
@@ -459,17 +422,11 @@ __global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams
     const float pz = voxel_center(vz, g.lo[2], q.vsz[2]);
     const uint32_t j0 = ((ConstU32 *)cell_off)[cell], j1 = ((ConstU32 *)cell_off)[cell + 1];
     float I = 0.0f, V = 0.0f;
-    if (j0 < j1) {
-        // (vpc: every chunk of a cell takes the same form)
-        if (vpc > kTileQueries || __builtin_amdgcn_readfirstlane(cell_coarse[cell]) != 0) {
-            walk_staged(rec, gids, j0, j1, lane, L.b, px, py, pz, T, I, V);
-        } else {
-            float ox, oy, oz;
-            cell_centre(g, cell, ox, oy, oz);
-            walk_lanes(vpc, L, lane, rec, gids, j0, j1, px - ox, py - oy, pz - oz, ox, oy, oz, T, I, V);
-        }
-    }
-    if (local < vpc) {
+    if (sh == 0)
+        walk_staged(rec, gids, j0, j1, lane, s_rec, px, py, pz, T, I, V);
+    else
+        walk_split(rec, gids, j0, j1, lane, sh, s_rec, px, py, pz, T, I, V);
+    if (local < vpc && (lane & ((1u << sh) - 1u)) == 0) {
         const uint64_t idx = (uint64_t)vx + (uint64_t)q.dims[0] * ((uint64_t)vy + (uint64_t)q.dims[1] * (uint64_t)vz);
         const bool def = I > tau;
         out_v[idx] = def ? V / I : 0.0f;
@@ -1488,16 +1445,18 @@ hipError_t launch_query_keys(const QueryParams &q, const GridParams &g, uint32_t
     return hipGetLastError();
 }
 
-hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint8_t *cell_coarse,
-                              const uint32_t *gids, const uint32_t *cell_off, float T, float tau, float *out_v,
-                              float *out_i, hipStream_t s) {
+hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint32_t *gids,
+                              const uint32_t *cell_off, float T, float tau, float *out_v, float *out_i,
+                              hipStream_t s) {
     const int64_t vpc = (int64_t)(q.dims[0] / g.cells[0]) * (q.dims[1] / g.cells[1]) * (q.dims[2] / g.cells[2]);
     const int64_t wpc = (vpc + kWave - 1) / kWave;
     const int64_t blocks = g.ncells * wpc;
     if (blocks <= 0) return hipSuccess;
+    uint32_t sh = 0;  // lanes of a voxel: 2^sh
+    while (vpc << (sh + 1) <= kWave) ++sh;
     prof_begin("sample_grid", s);
-    hipLaunchKernelGGL(k_sample_grid, dim3((uint32_t)blocks), dim3(kWave), 0, s, q, g, rec, cell_coarse, gids,
-                       cell_off, T, tau, out_v, out_i);
+    hipLaunchKernelGGL(k_sample_grid, dim3((uint32_t)blocks), dim3(kWave), 0, s, q, g, sh, rec, gids, cell_off,
+                       T, tau, out_v, out_i);
     prof_end("sample_grid", s);
     return hipGetLastError();
 }
