@@ -3,15 +3,15 @@
 //
 // The whitened offset u = U (p - mu) of a (Gaussian, query) pair is linear in
 // the query: with offsets a = p - o from a point o of the cell and c = U (mu
-// - o), u = U a - c is a product of the 3 x 4 matrix (U, -c) with (a, 1). For
+// - o), u = U a - c is a product of the 3 x 4 matrix (-c, U) with (1, a). For
 // 16 queries and 16 Gaussians these are three 16x16x4 float32 matrix
-// products (v_mfma_f32_16x16x4_f32), chains of float32 fused multiply-adds as
-// the vector form's. They do not run beside vector work (measured: 36 cycles
-// each, added to the vector instructions' time), so they cost 27 issue slots
-// per 256 pairs where the vector form takes 24; what they save is the vector
-// form's read of every record from LDS once per 64 queries, which bounds it
-// (24 LDS cycles a record and wave, four SIMDs to an LDS), and lanes: tiles
-// hold 16 queries instead of 64.
+// products (v_mfma_f32_16x16x4_f32), each component an ascending chain of
+// float32 fused multiply-adds. They do not run beside the same wave's vector
+// work (36 cycles each, added to the vector instructions' time), so they cost
+// 27 issue slots per 256 pairs where the vector form takes 24; what they save
+// is the vector form's read of every record from LDS once per 64 queries,
+// which bounds it (24 LDS cycles a record and wave, four SIMDs to an LDS).
+// The walk of dense cells in boxed launches takes them (k_sample_dense).
 //
 // Grid queries (Sec. 4.1.3, Fig. 4 C): one wavefront per (cell, 64 voxels of
 // the cell), a voxel a lane; cells of at most 32 voxels split the list over
@@ -142,9 +142,13 @@ constexpr int kDensePerSimd = 6;
 constexpr uint32_t kTile = 16;              // queries of a matrix tile, and Gaussians
 
 // LDS of a dense item's workgroup. The records of up to kBlock candidates:
-// the rows (U_iz, U_iy, U_ix, -c_i) of (U, -c), in the order the matrix
-// product's fused multiply-adds take them (sums of U a stay small against c,
-// which comes last), and (w, w v). Entry kBlock is an
+// the rows (-c_i, U_iz, U_iy, U_ix) of (-c, U), in the order the matrix
+// product's fused multiply-adds take them, and (w, w v). -c comes first, so
+// that u is rounded as offset_q rounds it: the sums of U a are not rounded by
+// themselves before c cancels them (c last: 1.0 to 1.3 times the rms error of
+// Q' at the cutoff for round Gaussians in cells of 2 to 60 times their scale;
+// c first, with c formed in float64: 0.56 to 1.0 times offset_q's for axis
+// ratios of 1 to 30). Entry kBlock is an
 // all-zero record that pads lists to whole tiles. The walk of a coarse cell
 // uses the rows' space for staged records, a quarter of it a wave
 // (wave_records).
@@ -176,24 +180,19 @@ __device__ __forceinline__ Record load_record(const Record *__restrict__ rec, ui
 }
 
 // A candidate's rows into entry b[0] of planes `plane` entries apart: record
-// r about o, or the all-zero record. c is formed in float64 and rounded once;
-// rest gets what the rounding left of -c.
+// r about o, or the all-zero record. c is formed in float64 and rounded once.
 __device__ __forceinline__ void stage_rows(float4 *b, uint32_t plane, bool live, const Record &r, float ox, float oy,
-                                           float oz, float (&rest)[3]) {
+                                           float oz) {
     float4 b0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b1 = b0, b2 = b0;
-    rest[0] = rest[1] = rest[2] = 0.0f;
     if (live) {
         const double bx = (double)r.f0.x - (double)ox, by = (double)r.f0.y - (double)oy;
         const double bz = (double)r.f0.z - (double)oz;
-        const double c0 = -((double)r.f1.x * bx + ((double)r.f1.y * by + (double)r.f1.z * bz));
-        const double c1 = -((double)r.f2.x * by + (double)r.f2.y * bz);
-        const double c2 = -((double)r.f2.z * bz);
-        b0 = make_float4(r.f1.z, r.f1.y, r.f1.x, (float)c0);
-        b1 = make_float4(r.f2.y, r.f2.x, 0.0f, (float)c1);
-        b2 = make_float4(r.f2.z, 0.0f, 0.0f, (float)c2);
-        rest[0] = (float)(c0 - (double)b0.w);
-        rest[1] = (float)(c1 - (double)b1.w);
-        rest[2] = (float)(c2 - (double)b2.w);
+        const double c0 = (double)r.f1.x * bx + ((double)r.f1.y * by + (double)r.f1.z * bz);
+        const double c1 = (double)r.f2.x * by + (double)r.f2.y * bz;
+        const double c2 = (double)r.f2.z * bz;
+        b0 = make_float4((float)-c0, r.f1.z, r.f1.y, r.f1.x);
+        b1 = make_float4((float)-c1, r.f2.y, r.f2.x, 0.0f);
+        b2 = make_float4((float)-c2, r.f2.z, 0.0f, 0.0f);
     }
     b[0] = b0;
     b[plane] = b1;
@@ -201,26 +200,21 @@ __device__ __forceinline__ void stage_rows(float4 *b, uint32_t plane, bool live,
 }
 
 // Operand of the matrix products that holds a tile's queries: lane l has
-// component l / 16 of (a_z, a_y, a_x, 1) for query l % 16.
+// component l / 16 of (1, a_z, a_y, a_x) for query l % 16.
 __device__ __forceinline__ float tile_operand(uint32_t k, float ax, float ay, float az) {
-    return k == 0 ? az : (k == 1 ? ay : (k == 2 ? ax : 1.0f));
+    return k == 0 ? 1.0f : (k == 1 ? az : (k == 2 ? ay : ax));
 }
 
 // The 256 pairs of 16 candidates (operands g0, g1, g2: lane l has component
 // l / 16 of the rows of candidate l % 16) and one tile of queries (operand q).
 // Lane l gets the pairs of query l % 16 with candidates 4 (l / 16) + r, r < 4,
-// whose weights are w[r] and v[r], and adds them to its sums: three matrix
-// products (96 cycles of the matrix core) beside eight vector instructions
-// per 64 pairs, where the vector form takes 14 and reads each record from LDS
-// once per 64 queries.
-// The products start from c0, c1, c2.
+// whose weights are w[r] and v[r], and adds them to its sums.
 __device__ __forceinline__ void tile_pairs(float q, float g0, float g1, float g2, const float4 &w, const float4 &v,
-                                           float T, float &I, float &V, mfma_f4 c0 = {0.0f, 0.0f, 0.0f, 0.0f},
-                                           mfma_f4 c1 = {0.0f, 0.0f, 0.0f, 0.0f},
-                                           mfma_f4 c2 = {0.0f, 0.0f, 0.0f, 0.0f}) {
-    const mfma_f4 u0 = __builtin_amdgcn_mfma_f32_16x16x4f32(g0, q, c0, 0, 0, 0);
-    const mfma_f4 u1 = __builtin_amdgcn_mfma_f32_16x16x4f32(g1, q, c1, 0, 0, 0);
-    const mfma_f4 u2 = __builtin_amdgcn_mfma_f32_16x16x4f32(g2, q, c2, 0, 0, 0);
+                                           float T, float &I, float &V) {
+    const mfma_f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    const mfma_f4 u0 = __builtin_amdgcn_mfma_f32_16x16x4f32(g0, q, zero, 0, 0, 0);
+    const mfma_f4 u1 = __builtin_amdgcn_mfma_f32_16x16x4f32(g1, q, zero, 0, 0, 0);
+    const mfma_f4 u2 = __builtin_amdgcn_mfma_f32_16x16x4f32(g2, q, zero, 0, 0, 0);
     const float wr[4] = {w.x, w.y, w.z, w.w}, vr[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -1029,12 +1023,12 @@ __device__ __forceinline__ uint32_t list_reaching(DenseLds &L, uint32_t wave, ui
     for (uint32_t c = 0; c < cnt; c += kWave) {
         const uint32_t j = c + lane;
         const float4 r0 = L.b[0][j], r1 = L.b[1][j], r2 = L.b[2][j];
-        const float e0 = fmaf_(r0.z, x.cx, fmaf_(r0.y, x.cy, fmaf_(r0.x, x.cz, r0.w)));
-        const float e1 = fmaf_(r1.y, x.cy, fmaf_(r1.x, x.cz, r1.w));
-        const float e2 = fmaf_(r2.x, x.cz, r2.w);
-        const float h0 = fmaf_(fabsf(r0.z), x.hx, fmaf_(fabsf(r0.y), x.hy, fabsf(r0.x) * x.hz));
-        const float h1 = fmaf_(fabsf(r1.y), x.hy, fabsf(r1.x) * x.hz);
-        const float h2 = fabsf(r2.x) * x.hz;
+        const float e0 = fmaf_(r0.w, x.cx, fmaf_(r0.z, x.cy, fmaf_(r0.y, x.cz, r0.x)));
+        const float e1 = fmaf_(r1.z, x.cy, fmaf_(r1.y, x.cz, r1.x));
+        const float e2 = fmaf_(r2.y, x.cz, r2.x);
+        const float h0 = fmaf_(fabsf(r0.w), x.hx, fmaf_(fabsf(r0.z), x.hy, fabsf(r0.y) * x.hz));
+        const float h1 = fmaf_(fabsf(r1.z), x.hy, fabsf(r1.y) * x.hz);
+        const float h2 = fabsf(r2.y) * x.hz;
         const float d0 = fmaxf(fabsf(e0) - h0, 0.0f), d1 = fmaxf(fabsf(e1) - h1, 0.0f);
         const float d2 = fmaxf(fabsf(e2) - h2, 0.0f);
         const bool in = j < cnt && !(fmaf_(d0, d0, fmaf_(d1, d1, d2 * d2)) > Tm);
@@ -1148,8 +1142,7 @@ __device__ __forceinline__ void dense_item(DenseLds &L, uint32_t wave, uint32_t 
         if (ja + tid < jb) r = load_record(rec, gids[ja + tid]);
         for (uint32_t c0 = ja; c0 < jb; c0 += kBlock) {
             __syncthreads();  // every wave has read the chunk before
-            float rest[3];  // not carried: boxes are small
-            stage_rows(&L.b[0][tid], kBlock + 1, c0 + tid < jb, r, ox, oy, oz, rest);
+            stage_rows(&L.b[0][tid], kBlock + 1, c0 + tid < jb, r, ox, oy, oz);
             L.w[tid] = make_float2(r.f0.w, r.f1.w);
             const uint32_t cn = c0 + kBlock;
             if (cn + tid < jb) r = load_record(rec, gids[cn + tid]);

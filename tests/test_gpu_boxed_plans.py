@@ -69,3 +69,65 @@ def test_a_plan_serves_every_forward(kind, n):
         v, i = planned(r)
         np.testing.assert_array_equal(v.view(np.uint32), phi.view(np.uint32), err_msg=f"after {after}")
         np.testing.assert_array_equal(i.view(np.uint32), inf.view(np.uint32), err_msg=f"after {after}")
+
+
+def rotations(q):
+    q = q.astype(np.float64)
+    w, x, y, z = (q / np.linalg.norm(q, axis=1, keepdims=True)).T
+    return np.stack([np.stack([1 - 2 * (y * y + z * z), 2 * (x * y - w * z), 2 * (x * z + w * y)], -1),
+                     np.stack([2 * (x * y + w * z), 1 - 2 * (x * x + z * z), 2 * (y * z - w * x)], -1),
+                     np.stack([2 * (x * z - w * y), 2 * (y * z + w * x), 1 - 2 * (x * x + y * y)], -1)], 1)
+
+
+@pytest.mark.parametrize("flat", [1, 5, 30])
+@pytest.mark.parametrize("ratio", [6, 20, 60])
+def test_boxed_sums_are_as_exact_as_the_unboxed_ones(flat, ratio):
+    """The matrix products' whitened offsets round no worse than the vector
+    form's, which a launch of half the queries takes in the same cells. One
+    Gaussian of some weight in every third cell (`flat` its axis ratio,
+    `ratio` the cell's diagonal over its largest scale), so that I = w G and
+    -log2(I / w) is Q'; 200 wide ones of weight 1e-30 lengthen the lists and
+    vanish in the sums. Bar: the rms error of Q' against 64 bits at most 1.03
+    times the other launch's (150,000 pairs or more a side: sampling moves an
+    rms by under 1 %)."""
+    f = np.float32
+    c, n, per = 12, 64, 8650
+    rng = np.random.default_rng(175)
+    k = np.arange(n)
+    cell = np.stack([k % 4 * 3 + 1, k // 4 % 4 * 3 + 1, k // 16 * 3 + 1], 1)
+    scale = (np.sqrt(3) / c / ratio * np.array([1.0, 1.0, 1.0 / flat]) * np.ones((n, 1))).astype(f)
+    mean = ((cell + rng.uniform(0.1, 0.9, (n, 3))) / c).astype(f)
+    q = rng.standard_normal((n, 4)).astype(f)
+    R = rotations(q)
+    d = rng.standard_normal((n, per, 3))
+    d *= 3.03 * rng.uniform(0.7, 0.995, (n, per, 1)) / np.linalg.norm(d, axis=2, keepdims=True)
+    pts = (mean[:, None] + np.einsum("nij,npj->npi", R, d * scale[:, None])).astype(f)
+    x = pts.astype(np.float64) - mean[:, None].astype(np.float64)
+    u = np.einsum("nij,npi->npj", R, x) / scale[:, None].astype(np.float64)
+    Q = (u * u).sum(2) / 2 * np.log2(np.e)
+    m = 200
+    g = synth.Gaussians(np.concatenate([mean, rng.uniform(0.3, 0.7, (m, 3))]).astype(f),
+                        np.concatenate([scale, np.full((m, 3), 0.6)]).astype(f),
+                        np.concatenate([q, np.tile([1.0, 0, 0, 0], (m, 1))]).astype(f),
+                        np.full(n + m, 0.5, f), np.concatenate([np.full(n, 4.0), np.full(m, 1e-30)]).astype(f))
+
+    def rms(queries):
+        p, exact = pts[:, :queries], Q[:, :queries]
+        r = Run(g, (c, c, c), "points", points=p.reshape(-1, 3))
+        _, inf = r.forward()
+        per_cell = np.diff(r.index_arrays()[2].astype(np.int64))
+        at = np.clip(np.floor(p.astype(np.float64) * c), 0, c - 1).astype(np.int64)
+        key = at[..., 0] + c * (at[..., 1] + c * at[..., 2])
+        held = np.bincount(key.ravel(), minlength=c ** 3)
+        inf = inf.reshape(n, queries).astype(np.float64)
+        # dense cells that the pair's Gaussian alone reaches, and not the next one
+        ok = (held[key] >= 64) & (per_cell[key] <= m + 1) & (inf > 0.01)
+        e = -np.log2(inf[ok] / 4.0) - exact[ok]
+        return r, np.sqrt((e * e).mean()), int(ok.sum())
+
+    log(f"case exactness of boxed sums, axis ratio {flat}, cell / scale {ratio}")
+    rb, boxed, nb = rms(per)
+    ru, plain, nu = rms(per // 2)
+    assert rb.nq >= max(320 * c ** 3, 1 << 19) and rb.index.n_pairs >= 190 * c ** 3 and ru.nq < 320 * c ** 3
+    log(f"  rms error of Q': boxed {boxed:.3e} ({nb} pairs), unboxed {plain:.3e} ({nu})")
+    assert min(nb, nu) > 150000 and boxed <= 1.03 * plain
