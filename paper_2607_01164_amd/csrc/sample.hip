@@ -1059,6 +1059,7 @@ __device__ __forceinline__ uint32_t list_reaching(DenseLds &L, uint32_t wave, ui
 // a time; each wave lists the ones that reach its tiles' box, and takes the
 // list 16 candidates at a time.
 constexpr uint32_t kSlots = 4;
+constexpr int64_t kDenseLaunch = (int64_t)1 << 23;  // items of one launch
 __device__ __forceinline__ void dense_item(DenseLds &L, uint32_t wave, uint32_t lane, uint32_t qa, uint32_t qn,
                                            uint32_t n, uint32_t ja, uint32_t jb, uint32_t c, const GridParams &g,
                                            const Record *__restrict__ rec, const uint32_t *__restrict__ gids,
@@ -1197,8 +1198,9 @@ __device__ __forceinline__ CellItem cell_item(uint32_t w, uint32_t ncells, const
     return it;
 }
 
+// first: the launch's first item (a multiple of the XCD grouping's window).
 __global__ __launch_bounds__(kBlock, kDensePerSimd) void k_sample_dense(
-    GridParams g, const Record *__restrict__ rec, const uint8_t *__restrict__ cell_coarse,
+    GridParams g, uint32_t first, const Record *__restrict__ rec, const uint8_t *__restrict__ cell_coarse,
     const uint32_t *__restrict__ gids, const uint32_t *__restrict__ cell_off, const uint32_t *__restrict__ point_off,
     const uint32_t *__restrict__ keys, const uint32_t *__restrict__ order, const uint32_t *__restrict__ item_off,
     const uint32_t *__restrict__ items, float T, float tau, float *__restrict__ out_v, float *__restrict__ out_i,
@@ -1207,7 +1209,7 @@ __global__ __launch_bounds__(kBlock, kDensePerSimd) void k_sample_dense(
     const uint32_t lane = threadIdx.x % kWave;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t ncells = (uint32_t)g.ncells;
-    const uint32_t w = xcd_group<kXcdDense>(blockIdx.x, gridDim.x);
+    const uint32_t w = first + xcd_group<kXcdDense>(blockIdx.x, gridDim.x);
     if (w >= ((ConstU32 *)item_off)[ncells + 2]) return;
     const CellItem it = cell_item(w, ncells, cell_coarse, cell_off, point_off, item_off, items);
     const uint32_t nit = (it.n + kBoxedQ - 1) / kBoxedQ;
@@ -1503,13 +1505,17 @@ hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const
     if (q.n <= 0) return hipSuccess;
     const bool boxed = boxed_launch(q.n, g.ncells);
     prof_begin("sample_points", s);
-    // dense cells hold at least 64 queries
-    if (boxed && q.n >= 2 * (int64_t)kDenseMin) {
-        hipLaunchKernelGGL(k_sample_dense, dim3((uint32_t)(q.n / (2 * kDenseMin))), dim3(kBlock), 0, s, g, rec,
-                           cell_coarse, gids, cell_off, point_off, keys, order, it.item_off, it.items, T, tau, out_v,
-                           out_i, pr.pos, pr.out);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    if (boxed) {
+        // dense cells hold at least 64 queries; a launch holds fewer than 2^32 threads
+        const int64_t items = q.n / (2 * kDenseMin);
+        for (int64_t first = 0; first < items; first += kDenseLaunch) {
+            const int64_t blocks = items - first < kDenseLaunch ? items - first : kDenseLaunch;
+            hipLaunchKernelGGL(k_sample_dense, dim3((uint32_t)blocks), dim3(kBlock), 0, s, g, (uint32_t)first, rec,
+                               cell_coarse, gids, cell_off, point_off, keys, order, it.item_off, it.items, T, tau,
+                               out_v, out_i, pr.pos, pr.out);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
     }
     const int64_t waves = boxed ? g.ncells + 1 : it.max_items;
     hipLaunchKernelGGL(k_sample_cells, dim3((uint32_t)((waves + kSampWaves - 1) / kSampWaves)), dim3(kSampBlock), 0, s,

@@ -131,3 +131,37 @@ def test_boxed_sums_are_as_exact_as_the_unboxed_ones(flat, ratio):
     assert rb.nq >= max(320 * c ** 3, 1 << 19) and rb.index.n_pairs >= 190 * c ** 3 and ru.nq < 320 * c ** 3
     log(f"  rms error of Q': boxed {boxed:.3e} ({nb} pairs), unboxed {plain:.3e} ({nu})")
     assert min(nb, nu) > 150000 and boxed <= 1.03 * plain
+
+
+def test_boxed_launch_of_more_than_2_30_queries():
+    """A launch takes fewer than 2^32 threads, and the boxed walk gives 256 to
+    every 64 queries: 2^30 + 2^20 queries, 2^20 points over and over, give
+    the 2^20 points' bits over and over (their cells hold 16,384, the level of
+    the larger counts too). About 70 GB of device memory."""
+    import torch
+    import paper_2607_01164_amd as gs
+    from harness import dev_gauss
+    if torch.cuda.get_device_properties(0).total_memory < 100 << 30:
+        pytest.skip("needs 100 GB")
+    log("case 2^30 + 2^20 queries")
+    g = synth.random_gaussians(176, 250, log_mu=np.log(0.4), log_sd=0.3)
+    base = torch.from_numpy(synth.random_points(177, 1 << 20)).cuda()
+    dg, grid = dev_gauss(g), gs.make_grid((4, 4, 4))
+    index = gs.build_index(dg, grid, 0.01)
+    assert index.n_pairs >= 190 * 64
+    out = []
+    for repeats in (1, (1 << 10) + 1):
+        pts = base.repeat(repeats, 1)
+        query = gs.Query.pts(pts)
+        v = torch.empty(len(pts), dtype=torch.float32, device="cuda")
+        i = torch.empty_like(v)
+        plan = gs.alloc_plan(query, grid, "cuda")
+        gs.gs_sample(dg, index, query, v, i, plan)
+        torch.cuda.synchronize()
+        out.append((v.view(repeats, -1), i.view(repeats, -1)))
+        del pts, query, plan
+    assert bool((out[0][1] > 0).any())
+    for a, b in zip(*out):
+        assert bool((b.view(torch.int32) == a.view(torch.int32)).all())
+    del out, base, index
+    torch.cuda.empty_cache()
