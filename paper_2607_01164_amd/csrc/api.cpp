@@ -20,8 +20,8 @@ hipError_t launch_loss(int64_t n, const float *value, const float *influence, co
                        float *grad_value, float *grad_influence, gs_loss_terms *terms, void *work, hipStream_t s);
 hipError_t launch_sample_gauss_major(const QueryParams &q, const GridParams &g, const BwdGeom &bg, const Record *rec,
                                      const CellBox *box, const uint32_t *gorder,
-                                     int64_t n_gauss, const uint32_t *order, const uint32_t *point_off, float T,
-                                     float tau, float *out_v, float *out_i, const PlanResults &pr, void *work,
+                                     int64_t n_gauss, const uint32_t *order, const uint32_t *point_off, bool placed,
+                                     float T, float tau, float *out_v, float *out_i, const PlanResults &pr, void *work,
                                      hipStream_t s);
 size_t gauss_major_work_bytes(int64_t nq);
 hipError_t launch_densify(const gs_params &in, int64_t n_in, const float *weight, float tau2, const QueryParams &q,
@@ -191,14 +191,12 @@ struct Plan {
     uint32_t *keys;      // [n] sorted cell keys (ncells = outside)
     uint32_t *order;     // [n] query ids in cell order
     uint32_t *keys_alt;  // [n]
-    uint32_t *order_alt; // [n] the sort's, then the refined order (launch_refine_order)
+    uint32_t *order_alt; // [n]
     uint32_t *point_off; // [kSub ncells + 2]
     void *radix_work;
     PointItems items;
     PlanResults res;
     size_t bytes;
-    // the order the forward and the backward take the queries in
-    const uint32_t *walk_order(int64_t n, int64_t ncells) const { return boxed_launch(n, ncells) ? order_alt : order; }
 };
 
 Plan plan_layout(void *base, int64_t n, int64_t ncells) {
@@ -447,9 +445,6 @@ gs_status order_queries(const char *who, const QueryParams &qp, const GridParams
         GS_TRY(radix_sort_pairs(ek, ev, ak, av, nq, bits, p.radix_work, stream, true), "query sort");
     }
     GS_TRY(key_offsets(p.keys, nq, p.point_off, (int64_t)kSub * gp.ncells + 1, stream), "query ranges");
-    // the sort is done with its alternate ids: they take the refined order
-    if (boxed_launch(nq, gp.ncells))
-        GS_TRY(launch_refine_order(qp, gp, p.keys, p.order, p.order_alt, p.res.pos, stream), "query places");
     *out = p;
     return GS_OK;
 }
@@ -707,8 +702,11 @@ static gs_status plan_queries(const char *who, const QueryParams &qp, const Grid
 static gs_status sample_ordered(const char *who, const gs_index *index, const QueryParams &qp, const GridParams &gp,
                                 const Plan &p, float *out_value, float *out_influence, hipStream_t stream) {
     IndexWork w = index_layout(index->work, index->n_gauss, &index->grid, index->capacity);
-    GS_TRY(launch_sample_points(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets, p.keys,
-                                p.walk_order(qp.n, gp.ncells), p.point_off, p.items, cutoff_T(index->tau), index->tau, out_value, out_influence, p.res, stream),
+    const bool boxed = boxed_launch(qp.n, gp.ncells, index->n_pairs);
+    if (boxed) GS_TRY(launch_refine_order(qp, gp, p.keys, p.order, p.res.pos, stream), who);
+    GS_TRY(launch_sample_points(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets, p.keys, p.order,
+                                p.point_off, p.items, boxed, cutoff_T(index->tau), index->tau, out_value,
+                                out_influence, p.res, stream),
            who);
     return GS_OK;
 }
@@ -802,9 +800,13 @@ gs_status gs_sample_gaussian_major(const gs_gaussians *gauss, const gs_index *in
     Plan p;
     if ((st = order_queries("gs_sample_gaussian_major", qp, gp, nq, plan, plan_bytes, &p, stream)) != GS_OK)
         return st;
+    // the order by place also brings the queries a Gaussian meets together
+    // (2^24 clustered points 69.6 -> 54.4 ms)
+    const bool boxed = boxed_launch(nq, gp.ncells, index->n_pairs);
+    if (boxed) GS_TRY(launch_refine_order(qp, gp, p.keys, p.order, p.res.pos, stream), "gs_sample_gaussian_major");
     GS_TRY(launch_sample_gauss_major(qp, gp, bwd_geom(gp, qp, cutoff_T(index->tau)), w.rec, w.box, w.gorder,
-                                     index->n_gauss, p.walk_order(nq, gp.ncells), p.point_off,
-                                     cutoff_T(index->tau), index->tau, out_value, out_influence, p.res, work, stream),
+                                     index->n_gauss, p.order, p.point_off, boxed, cutoff_T(index->tau), index->tau,
+                                     out_value, out_influence, p.res, work, stream),
            "gs_sample_gaussian_major");
     return GS_OK;
 }
@@ -845,8 +847,7 @@ gs_status gs_sample_backward(const gs_gaussians *gauss, const gs_index *index, c
     IndexWork w = index_layout(index->work, n, &index->grid, index->capacity);
     BwdWork bw = bwd_layout(work, index, query);
     const float T = cutoff_T(index->tau);
-    GS_TRY(launch_backward(qp, gp, bwd_geom(gp, qp, T), w.rec, w.box, w.gorder, n, index->n_pairs,
-                           p.walk_order(nq, gp.ncells),
+    GS_TRY(launch_backward(qp, gp, bwd_geom(gp, qp, T), w.rec, w.box, w.gorder, n, index->n_pairs, p.order,
                            p.point_off, p.res.pos, p.res.out, value, influence, grad_value, grad_influence, T, bw.b,
                            gauss->scale, gauss->rot, d_mean, d_scale, d_rot, d_value, d_weight, stream),
            "gs_sample_backward");

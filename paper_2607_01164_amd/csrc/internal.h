@@ -419,12 +419,13 @@ hipError_t launch_query_keys(const QueryParams &q, const GridParams &g, uint32_t
 hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint32_t *gids,
                               const uint32_t *cell_off, float T, float tau, float *out_v, float *out_i,
                               hipStream_t s);
-// Whether a launch of nq ordered queries in ncells cells is boxed: its plan
-// order is then refined by place inside quarters of cells, and the plan holds
-// the positions in it (PlanResults::pos, the place in w) before the forward.
-bool boxed_launch(int64_t nq, int64_t ncells);
-hipError_t launch_refine_order(const QueryParams &q, const GridParams &g, const uint32_t *keys, const uint32_t *order,
-                               uint32_t *refined, float4 *pos, hipStream_t s);
+// Whether the forward of nq ordered queries in ncells cells with n_pairs pairs
+// is boxed: it first refines the plan's order by place inside quarters of cells
+// (in place; the same order comes out whether or not it is refined already) and
+// writes the positions in that order, the place in w.
+bool boxed_launch(int64_t nq, int64_t ncells, int64_t n_pairs);
+hipError_t launch_refine_order(const QueryParams &q, const GridParams &g, const uint32_t *keys, uint32_t *order,
+                               float4 *pos, hipStream_t s);
 // Work items of the ordered-query sampler (kept in the plan).
 struct PointItems {
     uint32_t *item_off;   // [ncells + 3]
@@ -447,12 +448,12 @@ struct PlanResults {
 // ordering's last step).
 hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
                              hipStream_t s);
-// cell_coarse: the index's per-cell flags (launch_preprocess). order: the
-// plan's, the refined one in boxed launches.
+// cell_coarse: the index's per-cell flags (launch_preprocess). boxed: the
+// order is refined and pr.pos written.
 hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec,
                                 const uint8_t *cell_coarse, const uint32_t *gids, const uint32_t *cell_off,
                                 const uint32_t *keys, const uint32_t *order, const uint32_t *point_off,
-                                const PointItems &it, float T, float tau, float *out_v, float *out_i,
+                                const PointItems &it, bool boxed, float T, float tau, float *out_v, float *out_i,
                                 const PlanResults &pr, hipStream_t s);
 
 // Pairs the forward tests and those passing the cutoff (measurement), into

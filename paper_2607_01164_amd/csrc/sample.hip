@@ -20,9 +20,9 @@
 // Voxel-list, point and jittered queries (Sec. 5.1.2): the queries are first
 // ordered by cell and, inside a cell, by quarter of the cell along x
 // (query_keys + radix sort, kept in the plan), and the work is split by cell
-// (see k_sample_cells). Where cells hold many queries on average, these are
-// also ordered by place inside the quarter (k_refine_order), and dense cells
-// are cut into boxes that meet only the candidates reaching them
+// (see k_sample_cells). Where many queries meet long lists (boxed_launch), the
+// forward also orders them by place inside the quarter (k_refine_order) and
+// cuts dense cells into boxes that meet only the candidates reaching them
 // (k_sample_dense).
 #include "expand.h"
 #include "internal.h"
@@ -564,9 +564,8 @@ __device__ __forceinline__ void block_split(const uint32_t (&d)[kRefineItems], i
 }
 
 __global__ __launch_bounds__(kBlock) void k_refine_order(QueryParams q, GridParams g,
-                                                         const uint32_t *__restrict__ keys,
-                                                         const uint32_t *__restrict__ order,
-                                                         uint32_t *__restrict__ refined, float4 *__restrict__ pos) {
+                                                         const uint32_t *__restrict__ keys, uint32_t *order,
+                                                         float4 *__restrict__ pos) {
     __shared__ float4 s_pos[kRefineTile];
     __shared__ uint32_t s_pid[kRefineTile];
     __shared__ uint32_t s_cnt[kWavesPerBlock * kRefineTile];  // up to kRefineTile runs
@@ -605,7 +604,6 @@ __global__ __launch_bounds__(kBlock) void k_refine_order(QueryParams q, GridPara
         for (int i = 0; i < kRefineItems; ++i) {
             const uint32_t e = wave * (kWave * kRefineItems) + (uint32_t)i * kWave + lane;
             if (e < have) {
-                refined[base + e] = pid[i];
                 pos[base + e] = p[i];
             }
         }
@@ -654,7 +652,7 @@ __global__ __launch_bounds__(kBlock) void k_refine_order(QueryParams q, GridPara
         const uint32_t e = (uint32_t)i * kBlock + tid;
         if (e < have) {
             const uint32_t at = s_at[e];
-            refined[base + e] = s_pid[at];
+            order[base + e] = s_pid[at];
             pos[base + e] = s_pos[at];
         }
     }
@@ -946,23 +944,32 @@ __device__ __forceinline__ void dense_item(uint32_t lane, uint32_t qa, uint32_t 
                       out_v, out_i, pr);
 }
 
-// A launch is boxed when its cells hold kBoxedMean queries or more on
-// average: the queries are ordered by place too (k_refine_order) and dense
-// cells are cut into boxes, prefixes of the place code (dense_level: how many
-// of its bits; quarters of the cell along x at 0). A tile holds queries of
-// one box, and meets only the candidates whose ellipsoid can reach the box.
-// The more queries a cell has, the finer its boxes: each level tests about
-// half the pairs of the one before, and a box should fill a tile; cells of
-// fewer than kLevel2Queries are one box. The level depends on the cell's
-// count only and the boxes on the grid, so a query's sums do not depend on
-// how the queries were split into items.
-// A launch whose cells would mostly be one box each has no use for the order
-// by place: the mean is the count from which they are cut. Measured, forward
-// with its query ordering: 10^8 clustered points in 64^3 cells (381 a cell)
-// 35.3 ms without boxes and 30.9 with them; 2^21 clustered points in 64^3 (8 a
-// cell) 1.17 ms without and 1.24 with them; a step on 1.7 M uniform voxels
-// in 25^3 cells (110 a cell) 615 us without and 665 with them.
-constexpr int64_t kBoxedMean = 320;
+// A boxed launch orders its queries by place too (k_refine_order) and cuts
+// dense cells into boxes, prefixes of the place code (dense_level: how many of
+// its bits; quarters of the cell along x at 0). A tile holds queries of one
+// box, and meets only the candidates whose ellipsoid can reach the box. The
+// more queries a cell has, the finer its boxes: each level tests about half
+// the pairs of the one before, and a box should fill a tile; cells of fewer
+// than kLevel2Queries are one box. The level depends on the cell's count only
+// and the boxes on the grid, so a query's sums do not depend on how the
+// queries were split into items.
+// What the boxes save grows with the cells' lists; what they cost, the order
+// by place (22 to 28 ps a query) and the list tests, does not. So a launch is
+// boxed from kBoxedList pairs a cell on average, where even uniform points
+// gain about what they pay, and from kBoxedMean queries a cell, below which
+// cells would mostly be one box, and kBoxedQueries queries, below which the
+// longer items leave the chip idle at the end. Forward with its ordering,
+// boxed over unboxed time. Uniform points by pairs a cell: 330 queries a cell,
+// 4.6 M queries 1.48 at 122, 1.11 at 181, 1.03 at 243, 0.98 at 268, 0.95 at
+// 291, 0.87 at 449; 1,000 a cell, 8 M queries 1.38 at 120, 1.18 at 179, 1.06 to
+// 1.13 at 210, 0.98 to 1.05 at 242, 0.92 at 304, 0.76 at 443; 0.57 M queries
+// 1.05 at 254, 1.01 at 356. Clustered points, whose queries meet lists several
+// times the average: 0.98 to 1.43 at 63 to 70, 0.75 to 1.21 at 107 to 113, 0.66
+// to 0.91 at 239 to 251; 10^8 points at 254 0.89. Launches of 15 M queries or
+// more have two queries a lane otherwise: of 25.6 M, uniform ones break even at
+// 325 only (1.12 to 1.14 at 249, 1.05 at 318), clustered ones at 110 to 220,
+// and the line stays where it is for them.
+constexpr int64_t kBoxedMean = 320, kBoxedQueries = (int64_t)1 << 20, kBoxedList = 240;
 constexpr uint32_t kLevel2Queries = (uint32_t)kBoxedMean, kLevel4Queries = 1536;
 constexpr uint32_t kWholeCell = 32;  // no level: one box
 __device__ __forceinline__ uint32_t dense_level(uint32_t n) {
@@ -1212,7 +1219,9 @@ __global__ __launch_bounds__(kBlock, kDensePerSimd) void k_sample_dense(
     const uint32_t w = first + xcd_group<kXcdDense>(blockIdx.x, gridDim.x);
     if (w >= ((ConstU32 *)item_off)[ncells + 2]) return;
     const CellItem it = cell_item(w, ncells, cell_coarse, cell_off, point_off, item_off, items);
+    // the list's items are of 64 or 128 queries: the first ones of a cell take it
     const uint32_t nit = (it.n + kBoxedQ - 1) / kBoxedQ;
+    if (it.chunk >= nit) return;
     const uint32_t per = (it.n + nit - 1) / nit;
     const uint32_t qa = it.pa + it.chunk * per;
     const uint32_t left = it.pa + it.n - qa, qn = left < per ? left : per;
@@ -1456,14 +1465,14 @@ hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const R
     return hipGetLastError();
 }
 
-bool boxed_launch(int64_t nq, int64_t ncells) { return nq >= kBoxedMean * ncells; }
+bool boxed_launch(int64_t nq, int64_t ncells, int64_t n_pairs) {
+    return nq >= kBoxedMean * ncells && nq >= kBoxedQueries && n_pairs >= kBoxedList * ncells;
+}
 
-// Queries per dense work item for nq ordered queries in ncells cells on the
-// current device: kBoxedQ in a boxed launch; else 128 (two a lane) from
-// kDenseBalance items per wave slot of the chip at 64, else 64. The item list
-// and the sampler both take it from nq and the grid, so they agree.
-static uint32_t dense_item_queries(int64_t nq, int64_t ncells) {
-    if (boxed_launch(nq, ncells)) return kBoxedQ;
+// Queries per dense work item for nq ordered queries on the current device:
+// 128 (two a lane) from kDenseBalance items per wave slot of the chip at 64,
+// else 64. The item list and the sampler both take it from nq, so they agree.
+static uint32_t dense_item_queries(int64_t nq) {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
@@ -1477,7 +1486,7 @@ static uint32_t dense_item_queries(int64_t nq, int64_t ncells) {
 hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
                              hipStream_t s) {
     if (nq <= 0) return hipSuccess;
-    const uint32_t dense_q = dense_item_queries(nq, g.ncells);
+    const uint32_t dense_q = dense_item_queries(nq);
     const int64_t nbuckets = g.ncells + 1;  // cells and the outside bucket
     // buckets 0..nbuckets-1 and one empty element after them (its offset is the total)
     const int64_t ngroups = (nbuckets + 1 + kItemGroup - 1) / kItemGroup;
@@ -1500,14 +1509,15 @@ hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *po
 hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec,
                                 const uint8_t *cell_coarse, const uint32_t *gids, const uint32_t *cell_off,
                                 const uint32_t *keys, const uint32_t *order, const uint32_t *point_off,
-                                const PointItems &it, float T, float tau, float *out_v, float *out_i,
+                                const PointItems &it, bool boxed, float T, float tau, float *out_v, float *out_i,
                                 const PlanResults &pr, hipStream_t s) {
     if (q.n <= 0) return hipSuccess;
-    const bool boxed = boxed_launch(q.n, g.ncells);
+    const uint32_t dense_q = dense_item_queries(q.n);
     prof_begin("sample_points", s);
     if (boxed) {
-        // dense cells hold at least 64 queries; a launch holds fewer than 2^32 threads
-        const int64_t items = q.n / (2 * kDenseMin);
+        // the dense cells' items (the kernel leaves at their number); a launch
+        // holds fewer than 2^32 threads
+        const int64_t items = q.n / dense_q + g.ncells + 1;
         for (int64_t first = 0; first < items; first += kDenseLaunch) {
             const int64_t blocks = items - first < kDenseLaunch ? items - first : kDenseLaunch;
             hipLaunchKernelGGL(k_sample_dense, dim3((uint32_t)blocks), dim3(kBlock), 0, s, g, (uint32_t)first, rec,
@@ -1520,17 +1530,17 @@ hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const
     const int64_t waves = boxed ? g.ncells + 1 : it.max_items;
     hipLaunchKernelGGL(k_sample_cells, dim3((uint32_t)((waves + kSampWaves - 1) / kSampWaves)), dim3(kSampBlock), 0, s,
                        q, g, rec, cell_coarse, gids, cell_off, point_off, order, it.item_off, it.items, it.max_items,
-                       dense_item_queries(q.n, g.ncells), boxed, T, tau, out_v, out_i, pr);
+                       dense_q, boxed, T, tau, out_v, out_i, pr);
     prof_end("sample_points", s);
     return hipGetLastError();
 }
 
-hipError_t launch_refine_order(const QueryParams &q, const GridParams &g, const uint32_t *keys, const uint32_t *order,
-                               uint32_t *refined, float4 *pos, hipStream_t s) {
+hipError_t launch_refine_order(const QueryParams &q, const GridParams &g, const uint32_t *keys, uint32_t *order,
+                               float4 *pos, hipStream_t s) {
     if (q.n <= 0) return hipSuccess;
     prof_begin("refine_order", s);
     hipLaunchKernelGGL(k_refine_order, dim3((uint32_t)((q.n + kRefineTile - 1) / kRefineTile)), dim3(kBlock), 0, s, q,
-                       g, keys, order, refined, pos);
+                       g, keys, order, pos);
     prof_end("refine_order", s);
     return hipGetLastError();
 }

@@ -28,6 +28,23 @@ def dev_gauss(g: synth.Gaussians, device="cuda"):
     return gs.Gaussians(t(g.mean), t(g.scale), t(g.rot), t(g.value), t(g.weight))
 
 
+def with_long_lists(g: synth.Gaussians, m=260, mean=(0.5, 0.5, 0.5), scale=(0.6, 0.6, 0.6)):
+    """g and m Gaussians of weight 1e-30 that vanish in float32 sums: they only
+    lengthen the lists of the cells they reach (all of the unit box with the
+    defaults), as boxed launches (240 pairs a cell or more) need them."""
+    f = np.float32
+    rep = lambda a: np.tile(np.asarray(a, f), (m, 1))
+    cat = lambda a, b: np.concatenate([a, b]).astype(f)
+    return synth.Gaussians(cat(g.mean, rep(mean)), cat(g.scale, rep(scale)), cat(g.rot, rep((1, 0, 0, 0))),
+                           cat(g.value, np.full(m, 0.5)), cat(g.weight, np.full(m, 1e-30)))
+
+
+def is_boxed(run) -> bool:
+    """The library's rule for boxed launches of ordered queries."""
+    nc = run.cells[0] * run.cells[1] * run.cells[2]
+    return run.nq >= max(320 * nc, 1 << 20) and run.index.n_pairs >= 240 * nc
+
+
 class Run:
     """One index + forward (+ backward) on the GPU."""
 

@@ -1,29 +1,30 @@
-"""Plans of boxed launches (320 queries a cell or more on average), whose
-order is refined by place and whose positions carry the places: every way of
-filling and using them, for points, voxel lists and jitter, with gs_sample's
-outputs as the reference, bit for bit."""
+"""Boxed launches (2^20 queries and 320 a cell or more, on lists of 240 pairs a
+cell or more on average), whose plans are refined by place and whose positions
+carry the places: every way of filling and using the plan, for points, voxel
+lists and jitter, with gs_sample's outputs as the reference, bit for bit; their
+exactness; coarse cells; and more queries than a launch has threads."""
 import numpy as np
 import pytest
 
 import synth
-from harness import Run, check_forward, log
+from harness import TAU, Run, check_forward, is_boxed, log, with_long_lists
 
 pytestmark = pytest.mark.gpu
 
-CELLS = (3, 2, 2)  # 12 cells
-DIMS = (42, 40, 38)
+DIMS = (110, 104, 106)
+N = (1 << 20) + 5003
 
 
-def boxed_run(kind, n):
-    """n queries, some of them outside the domain."""
-    g = synth.random_gaussians(171, 1200, log_mu=np.log(0.05), log_sd=0.6)
+def boxed_run(kind, cells):
+    """N queries, some of them outside the domain."""
+    g = with_long_lists(synth.random_gaussians(171, 1200, log_mu=np.log(0.03), log_sd=0.6))
     if kind == "points":
-        return Run(g, CELLS, kind, points=synth.random_points(172, n, -0.01, 1.01))
+        return Run(g, cells, kind, points=synth.random_points(172, N, -0.01, 1.01))
     nvox = DIMS[0] * DIMS[1] * DIMS[2]
-    ids = np.random.default_rng(173).choice(nvox, size=n, replace=False).astype(np.uint32)
+    ids = np.random.default_rng(173).choice(nvox, size=N, replace=False).astype(np.uint32)
     ids[:5] = [nvox, nvox + 1, 0xFFFFFFFF, nvox * 2, nvox + 7]
-    u = synth.jitter_offsets(174, n) if kind == "jitter" else None
-    return Run(g, CELLS, kind, dims=DIMS, ids=ids, offsets=u)
+    u = synth.jitter_offsets(174, N) if kind == "jitter" else None
+    return Run(g, cells, kind, dims=DIMS, ids=ids, offsets=u)
 
 
 def planned(r):
@@ -34,26 +35,25 @@ def planned(r):
     return v.cpu().numpy(), i.cpu().numpy()
 
 
-def places(r):
-    """keys, refined order and positions (with the places in w) of the plan."""
+def plan_parts(r):
+    """keys, order and positions (with the places in w) of the plan."""
     n = r.nq
     a = (4 * n + 255) // 256 * 256
     p = r.plan.cpu().numpy()
-    at = p.tobytes()
-    end = len(at) - ((8 * n + 255) // 256 * 256) - ((16 * (n + 64) + 255) // 256 * 256)
-    return p[:4 * n], p[3 * a:3 * a + 4 * n], p[end:end + 16 * n]
+    at = len(p) - ((8 * n + 255) // 256 * 256) - ((16 * (n + 64) + 255) // 256 * 256)
+    return p[:4 * n], p[a:a + 4 * n], p[at:at + 16 * n]
 
 
-@pytest.mark.parametrize("n", [6000, 30000])  # 500 and 2,500 a cell: both box sizes
+@pytest.mark.parametrize("cells", [(13, 12, 11), (3, 2, 2)])  # 614 and 87,798 a cell: both box sizes
 @pytest.mark.parametrize("kind", ["points", "voxels", "jitter"])
-def test_a_plan_serves_every_forward(kind, n):
-    log(f"case boxed plans, {n} {kind}")
-    r = boxed_run(kind, n)
-    assert r.nq >= 320 * 12
+def test_a_plan_serves_every_forward(kind, cells):
+    log(f"case boxed plans, {kind}, cells {cells}")
+    r = boxed_run(kind, cells)
+    assert is_boxed(r)
     phi, inf = r.forward()
-    sel = np.arange(5, n) if kind != "points" else None
+    sel = np.sort(np.random.default_rng(178).choice(np.arange(5, N), 20000, replace=False))
     check_forward(r, phi, inf, sel=sel, label=f"boxed {kind}")
-    want = places(r)
+    want = plan_parts(r)
     assert len(np.unique(want[2].view(np.uint32).reshape(-1, 4)[:, 3])) > 8, "the places are in w"
 
     r.plan.zero_()
@@ -61,14 +61,43 @@ def test_a_plan_serves_every_forward(kind, n):
     for after in ("gs_plan_queries", "gs_sample_planned", "gs_sample_gaussian_major"):
         if after == "gs_sample_gaussian_major":
             r.forward_gm()
-            sel = np.arange(5, n) if kind != "points" else None
             check_forward(r, r.phi_np, r.inf_np, sel=sel, label="gaussian-major")
         if after != "gs_plan_queries":  # (that fills a plan for a forward, which writes the rest)
-            for a, b in zip(want, places(r)):
+            for a, b in zip(want, plan_parts(r)):
                 np.testing.assert_array_equal(a, b, err_msg=f"the plan after {after}")
         v, i = planned(r)
         np.testing.assert_array_equal(v.view(np.uint32), phi.view(np.uint32), err_msg=f"after {after}")
         np.testing.assert_array_equal(i.view(np.uint32), inf.view(np.uint32), err_msg=f"after {after}")
+
+
+@pytest.mark.parametrize("cells", [(13, 12, 11), (8, 8, 8)])
+def test_boxed_coarse_cells_keep_small_gaussians_exact(cells):
+    """Cells that list a Gaussian far smaller than they are keep U (p - mu) in
+    boxed launches too: tiny Gaussians with 300 or more points each on their
+    cutoff surfaces, under wide ones that make every point defined. Every
+    output within the oracle's bar."""
+    rng = np.random.default_rng(179)
+    nt, per = 3400, 310
+    mean = rng.uniform(0.1, 0.9, (nt, 3))
+    scale = 0.0003 * rng.uniform(1.0, 2.0, (nt, 3))
+    q = rng.standard_normal((nt, 4))
+    d = rng.standard_normal((nt, per, 3))
+    d *= np.sqrt(2.0 * np.log(1.0 / TAU)) * (1.0 + rng.uniform(-1e-4, 1e-4, (nt, per, 1))) / \
+        np.linalg.norm(d, axis=2, keepdims=True)
+    pts = (mean[:, None] + np.einsum("nij,npj->npi", rotations(q), d * scale[:, None])).reshape(-1, 3)
+    f = np.float32
+    nw = 8
+    g = synth.Gaussians(np.concatenate([mean, rng.uniform(0.2, 0.8, (nw, 3))]).astype(f),
+                        np.concatenate([scale, np.full((nw, 3), 0.4)]).astype(f),
+                        np.concatenate([q, np.tile([1.0, 0, 0, 0], (nw, 1))]).astype(f), rng.random(nt + nw).astype(f),
+                        np.concatenate([rng.uniform(0.5, 1.0, nt), np.ones(nw)]).astype(f))
+    log(f"case boxed coarse cells {cells}")
+    r = Run(with_long_lists(g), cells, "points", points=pts)
+    assert is_boxed(r)
+    phi, inf = r.forward()
+    sel = np.sort(rng.choice(len(pts), 200000, replace=False))
+    _, stats = check_forward(r, phi, inf, sel=sel, label="boxed coarse cells")
+    assert stats["defined"] > 0.9 * len(sel)
 
 
 def rotations(q):
@@ -86,12 +115,12 @@ def test_boxed_sums_are_as_exact_as_the_unboxed_ones(flat, ratio):
     form's, which a launch of half the queries takes in the same cells. One
     Gaussian of some weight in every third cell (`flat` its axis ratio,
     `ratio` the cell's diagonal over its largest scale), so that I = w G and
-    -log2(I / w) is Q'; 200 wide ones of weight 1e-30 lengthen the lists and
-    vanish in the sums. Bar: the rms error of Q' against 64 bits at most 1.03
+    -log2(I / w) is Q'; the wide ones that lengthen the lists vanish in the
+    sums. Bar: the rms error of Q' against 64 bits at most 1.03
     times the other launch's (150,000 pairs or more a side: sampling moves an
     rms by under 1 %)."""
     f = np.float32
-    c, n, per = 12, 64, 8650
+    c, n, per = 12, 64, 16400
     rng = np.random.default_rng(175)
     k = np.arange(n)
     cell = np.stack([k % 4 * 3 + 1, k // 4 % 4 * 3 + 1, k // 16 * 3 + 1], 1)
@@ -105,11 +134,8 @@ def test_boxed_sums_are_as_exact_as_the_unboxed_ones(flat, ratio):
     x = pts.astype(np.float64) - mean[:, None].astype(np.float64)
     u = np.einsum("nij,npi->npj", R, x) / scale[:, None].astype(np.float64)
     Q = (u * u).sum(2) / 2 * np.log2(np.e)
-    m = 200
-    g = synth.Gaussians(np.concatenate([mean, rng.uniform(0.3, 0.7, (m, 3))]).astype(f),
-                        np.concatenate([scale, np.full((m, 3), 0.6)]).astype(f),
-                        np.concatenate([q, np.tile([1.0, 0, 0, 0], (m, 1))]).astype(f),
-                        np.full(n + m, 0.5, f), np.concatenate([np.full(n, 4.0), np.full(m, 1e-30)]).astype(f))
+    m = 260
+    g = with_long_lists(synth.Gaussians(mean, scale, q, np.full(n, 0.5, f), np.full(n, 4.0, f)), m)
 
     def rms(queries):
         p, exact = pts[:, :queries], Q[:, :queries]
@@ -128,7 +154,7 @@ def test_boxed_sums_are_as_exact_as_the_unboxed_ones(flat, ratio):
     log(f"case exactness of boxed sums, axis ratio {flat}, cell / scale {ratio}")
     rb, boxed, nb = rms(per)
     ru, plain, nu = rms(per // 2)
-    assert rb.nq >= max(320 * c ** 3, 1 << 19) and rb.index.n_pairs >= 190 * c ** 3 and ru.nq < 320 * c ** 3
+    assert is_boxed(rb) and not is_boxed(ru)
     log(f"  rms error of Q': boxed {boxed:.3e} ({nb} pairs), unboxed {plain:.3e} ({nu})")
     assert min(nb, nu) > 150000 and boxed <= 1.03 * plain
 
@@ -144,11 +170,11 @@ def test_boxed_launch_of_more_than_2_30_queries():
     if torch.cuda.get_device_properties(0).total_memory < 100 << 30:
         pytest.skip("needs 100 GB")
     log("case 2^30 + 2^20 queries")
-    g = synth.random_gaussians(176, 250, log_mu=np.log(0.4), log_sd=0.3)
+    g = with_long_lists(synth.random_gaussians(176, 250, log_mu=np.log(0.1), log_sd=0.3))
     base = torch.from_numpy(synth.random_points(177, 1 << 20)).cuda()
     dg, grid = dev_gauss(g), gs.make_grid((4, 4, 4))
     index = gs.build_index(dg, grid, 0.01)
-    assert index.n_pairs >= 190 * 64
+    assert index.n_pairs >= 240 * 64
     out = []
     for repeats in (1, (1 << 10) + 1):
         pts = base.repeat(repeats, 1)

@@ -1,13 +1,13 @@
-"""The forward's matrix tiles (16 queries x 16 candidates) at their edges: grid
-cells whose voxels do not fill tiles or waves, and boxed launches (320
-queries a cell or more on average), whose dense cells are cut into boxes by their
-query count. Every output against the oracle, with the bar the parity tests
-use."""
+"""The forward's matrix tiles (16 queries x 16 candidates) at their edges, in
+boxed launches (2^20 queries, 320 a cell and lists of 240 pairs a cell or more),
+whose dense cells are cut into boxes by their query count; and grid cells whose
+voxels do not fill a wave. Every output against the oracle, with the bar the
+parity tests use."""
 import numpy as np
 import pytest
 
 import synth
-from harness import Run, check_backward, check_forward, log, masked_cotangents
+from harness import Run, check_backward, check_forward, is_boxed, log, masked_cotangents, with_long_lists
 
 pytestmark = pytest.mark.gpu
 
@@ -45,16 +45,18 @@ def test_boxed_launch_at_its_counts(counts):
     pts = [cell_points(rng, (k & 1, (k >> 1) & 1, k >> 2), cells, n) for k, n in enumerate(counts)]
     pts.append(np.array([[1.0, 1.0, 1.0], [1.0001, 0.5, 0.5], [0.0, 0.0, 0.0], [-0.1, 0.2, 0.3]]))
     pts = np.concatenate(pts)
-    # queries outside the domain bring the launch to the mean that is boxed
-    pts = np.concatenate([pts, np.full((max(0, 320 * 8 - len(pts)), 3), 1.5)]).astype(np.float32)
+    # queries outside the domain bring the launch to the number that is boxed
+    pts = np.concatenate([pts, np.full(((1 << 20) - len(pts), 3), 1.5)]).astype(np.float32)
     rng.shuffle(pts)
     log(f"case boxed launch {counts}")
-    r = Run(g, cells, "points", points=pts)
+    r = Run(with_long_lists(g), cells, "points", points=pts)
+    assert is_boxed(r)
     phi, inf = r.forward()
     ref, _ = check_forward(r, phi, inf, label=f"boxed {counts}")
     gv, gi = synth.random_normal(123, r.nq), synth.random_normal(124, r.nq)
     gv, gi, _ = masked_cotangents(ref, gv, gi)
-    check_backward(r, r.backward(gv, gi), np.arange(g.n), np.arange(r.nq), gv, gi, label="boxed")
+    sup = np.nonzero(pts[:, 0] < 1.4)[0]
+    check_backward(r, r.backward(gv, gi), np.arange(g.n), sup, gv[sup], gi[sup], label="boxed")
 
 
 def test_boxed_lists_of_many_chunks_and_empty_cells():
@@ -62,11 +64,14 @@ def test_boxed_lists_of_many_chunks_and_empty_cells():
     record, and Gaussians whose boxes reach single corners of the cells."""
     rng = np.random.default_rng(125)
     g = synth.random_gaussians(126, 5000, log_mu=np.log(0.02), log_sd=0.8, lo=0.0, hi=0.49)
-    pts = np.concatenate([rng.random((3000, 3)) * 0.5, rng.random((2000, 3)), np.full((320 * 64, 3), 1.5)])
+    pts = np.concatenate([rng.random((3000, 3)) * 0.5, rng.random((2000, 3)), np.full(((1 << 20) - 5000, 3), 1.5)])
     pts = pts.astype(np.float32)
     log("case boxed lists")
-    r = Run(g, (4, 4, 4), "points", points=pts)
-    assert r.index.n_pairs > 256 * 8
+    # long lists in the half x < 0.5 only
+    r = Run(with_long_lists(g, 520, (0.25, 0.5, 0.5), (0.05, 0.6, 0.6)), (4, 4, 4), "points", points=pts)
+    assert is_boxed(r)
+    per = np.diff(r.index_arrays()[2].astype(np.int64))
+    assert (per == 0).any() and (per > 3 * 256).any()
     phi, inf = r.forward()
     check_forward(r, phi, inf, label="boxed lists")
 
@@ -74,12 +79,14 @@ def test_boxed_lists_of_many_chunks_and_empty_cells():
 def test_boxed_sums_do_not_depend_on_the_batch():
     """A query's sums are formed from its cell's list alone: two batches of one
     level (1,536 queries a cell or more) give the same bits."""
-    g = synth.random_gaussians(127, 2000, log_mu=np.log(0.04), log_sd=0.7)
-    pts = synth.random_points(128, 40000)
+    g = synth.random_gaussians(127, 9000, log_mu=np.log(0.04), log_sd=0.7)
+    pts = synth.random_points(128, 2500000)
     log("case boxed batches")
-    a = Run(g, (2, 2, 2), "points", points=pts)
-    b = Run(g, (2, 2, 2), "points", points=pts[:20000])
+    n = 1200000
+    a = Run(g, (4, 4, 4), "points", points=pts)
+    b = Run(g, (4, 4, 4), "points", points=pts[:n])
+    assert is_boxed(a) and is_boxed(b)
     pa, ia = a.forward()
     pb, ib = b.forward()
-    np.testing.assert_array_equal(pa[:20000].view(np.uint32), pb.view(np.uint32))
-    np.testing.assert_array_equal(ia[:20000].view(np.uint32), ib.view(np.uint32))
+    np.testing.assert_array_equal(pa[:n].view(np.uint32), pb.view(np.uint32))
+    np.testing.assert_array_equal(ia[:n].view(np.uint32), ib.view(np.uint32))
