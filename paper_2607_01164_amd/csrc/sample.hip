@@ -14,8 +14,8 @@
 // The walk of dense cells in boxed launches takes them (k_sample_dense).
 //
 // Grid queries (Sec. 4.1.3, Fig. 4 C): one wavefront per (cell, 64 voxels of
-// the cell), a voxel a lane; cells of at most 32 voxels split the list over
-// the lanes that are left (walk_split).
+// the cell), a voxel a lane; cells of at most 64 voxels split the list over
+// the lanes (walk_split).
 //
 // Voxel-list, point and jittered queries (Sec. 5.1.2): the queries are first
 // ordered by cell and, inside a cell, by quarter of the cell along x
@@ -348,18 +348,22 @@ __device__ __forceinline__ void walk_staged_r(const Record *__restrict__ rec, bo
 }
 
 
-// walk_staged for a cell of at most 32 voxels: 2^sh lanes a query, lane l
-// taking query l >> sh with the candidates c0 + (l mod 2^sh) + 2^sh t of each
-// 64. With a voxel a lane the lanes past the cell's voxels idle through the
-// whole list (195,112 cells, 529,113 Gaussians: one voxel a cell 583 us, split
-// 185; 16 voxels 528 and 205; 32 voxels 533 and 353). Every lane of a query
-// gets its sums. (Matrix tiles take offsets from a point of the cell, whose
-// rounding grows with the cell against the Gaussians' smallest scales; they
-// took 251, 219 and 309 us.)
+// walk_staged for a cell of at most 64 voxels: SL lanes a voxel and R voxels a
+// lane, lane l taking voxels l / SL + (64 / SL) t, t < R, with the candidates
+// c0 + l mod SL + SL i of each 64. With a voxel a lane the lanes past the
+// cell's voxels idle through the whole list, and every candidate's record is
+// read from LDS for one voxel a lane, which bounds the walk. 529,113 Gaussians
+// in 58^3 cells, us, a voxel a lane and split: 1 voxel a cell 601 and 188, 8
+// voxels 529 and 198, 16 543 and 204, 32 544 and 259, 48 575 and 381, 64 560
+// and 464. The lanes of a voxel get its sums. (Matrix tiles take offsets from a
+// point of the cell, whose rounding grows with the cell against the Gaussians'
+// smallest scales, and took 264, 228, 226, 309 and 420 us up to 48 voxels.)
+template <uint32_t SL, uint32_t R>
 __device__ __forceinline__ void walk_split(const Record *__restrict__ rec, const uint32_t *__restrict__ gids,
-                                           uint32_t ja, uint32_t jb, uint32_t lane, uint32_t sh, float4 *buf, float px,
-                                           float py, float pz, float T, float &I, float &V) {
-    const uint32_t slot = lane & ((1u << sh) - 1u);
+                                           uint32_t ja, uint32_t jb, uint32_t lane, float4 *buf, const float (&px)[R],
+                                           const float (&py)[R], const float (&pz)[R], float T, float (&I)[R],
+                                           float (&V)[R]) {
+    const uint32_t slot = lane % SL;
     uint32_t gnext = 0;
     if (ja < jb) gnext = gids[ja + lane < jb ? ja + lane : jb - 1];
     for (uint32_t c0 = ja; c0 < jb; c0 += kWave) {
@@ -372,26 +376,33 @@ __device__ __forceinline__ void walk_split(const Record *__restrict__ rec, const
         __builtin_amdgcn_s_waitcnt(0);
         __builtin_amdgcn_wave_barrier();
         const uint32_t cnt = jb - c0 < (uint32_t)kWave ? jb - c0 : (uint32_t)kWave;
-        for (uint32_t s0 = 0; s0 < cnt; s0 += 1u << sh) {
+        for (uint32_t s0 = 0; s0 < cnt; s0 += SL) {
             const uint32_t s = s0 + slot;  // < kWave
             if (s < cnt) {
                 Record a;
                 a.f0 = buf[s];
                 a.f1 = buf[kWave + s];
                 a.f2 = buf[2 * kWave + s];
-                accumulate(a, px, py, pz, T, I, V);
+#pragma unroll
+                for (uint32_t t = 0; t < R; ++t) accumulate(a, px[t], py[t], pz[t], T, I[t], V[t]);
             }
         }
         // every lane has read the planes before the next chunk overwrites them
         __builtin_amdgcn_wave_barrier();
     }
-    for (uint32_t o = 1; o < 1u << sh; o <<= 1) {
-        I += __shfl_xor(I, (int)o, kWave);
-        V += __shfl_xor(V, (int)o, kWave);
-    }
+#pragma unroll
+    for (uint32_t t = 0; t < R; ++t)
+#pragma unroll
+        for (uint32_t o = 1; o < SL; o <<= 1) {
+            I[t] += __shfl_xor(I[t], (int)o, kWave);
+            V[t] += __shfl_xor(V[t], (int)o, kWave);
+        }
 }
 
-__global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams q, GridParams g, uint32_t sh,
+// A wave's voxels of a grid cell: SL lanes a voxel and R voxels a lane
+// (walk_split), or a voxel a lane, 64 of the cell's (SL 1, walk_staged).
+template <uint32_t SL, uint32_t R>
+__global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams q, GridParams g,
                                                         const Record *__restrict__ rec,
                                                         const uint32_t *__restrict__ gids,
                                                         const uint32_t *__restrict__ cell_off, float T, float tau,
@@ -401,30 +412,38 @@ __global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams
     const uint32_t ry = (uint32_t)(q.dims[1] / g.cells[1]);
     const uint32_t rz = (uint32_t)(q.dims[2] / g.cells[2]);
     const uint32_t vpc = rx * ry * rz;
-    const uint32_t wpc = (vpc + kWave - 1) / kWave;
+    const uint32_t wpc = SL > 1 ? 1u : (vpc + kWave - 1) / kWave;
     const uint32_t lane = threadIdx.x;
     // ncells wpc < 2^32: at most a wave per cell and one per 64 voxels
     const uint32_t cell = blockIdx.x / wpc;
-    const uint32_t chunk = blockIdx.x - cell * wpc;
-    const uint32_t local = (chunk * kWave + lane) >> sh;
+    const uint32_t first = (blockIdx.x - cell * wpc) * kWave + lane / SL;
     const uint32_t nx = (uint32_t)g.cells[0], ny = (uint32_t)g.cells[1];
     const uint32_t cyz = cell / nx, cx = cell - cyz * nx, cz = cyz / ny, cy = cyz - cz * ny;
-    const uint32_t lyz = local / rx, lx = local - lyz * rx, lz = lyz / ry, ly = lyz - lz * ry;
-    const int32_t vx = (int32_t)(cx * rx + lx), vy = (int32_t)(cy * ry + ly), vz = (int32_t)(cz * rz + lz);
-    const float px = voxel_center(vx, g.lo[0], q.vsz[0]);
-    const float py = voxel_center(vy, g.lo[1], q.vsz[1]);
-    const float pz = voxel_center(vz, g.lo[2], q.vsz[2]);
+    float px[R], py[R], pz[R], I[R], V[R];
+    uint64_t idx[R];
+#pragma unroll
+    for (uint32_t t = 0; t < R; ++t) {
+        const uint32_t local = first + kWave / SL * t;
+        const uint32_t lyz = local / rx, lx = local - lyz * rx, lz = lyz / ry, ly = lyz - lz * ry;
+        const int32_t vx = (int32_t)(cx * rx + lx), vy = (int32_t)(cy * ry + ly), vz = (int32_t)(cz * rz + lz);
+        px[t] = voxel_center(vx, g.lo[0], q.vsz[0]);
+        py[t] = voxel_center(vy, g.lo[1], q.vsz[1]);
+        pz[t] = voxel_center(vz, g.lo[2], q.vsz[2]);
+        idx[t] = (uint64_t)vx + (uint64_t)q.dims[0] * ((uint64_t)vy + (uint64_t)q.dims[1] * (uint64_t)vz);
+        I[t] = V[t] = 0.0f;
+    }
     const uint32_t j0 = ((ConstU32 *)cell_off)[cell], j1 = ((ConstU32 *)cell_off)[cell + 1];
-    float I = 0.0f, V = 0.0f;
-    if (sh == 0)
-        walk_staged(rec, gids, j0, j1, lane, s_rec, px, py, pz, T, I, V);
+    if constexpr (SL == 1)
+        walk_staged(rec, gids, j0, j1, lane, s_rec, px[0], py[0], pz[0], T, I[0], V[0]);
     else
-        walk_split(rec, gids, j0, j1, lane, sh, s_rec, px, py, pz, T, I, V);
-    if (local < vpc && (lane & ((1u << sh) - 1u)) == 0) {
-        const uint64_t idx = (uint64_t)vx + (uint64_t)q.dims[0] * ((uint64_t)vy + (uint64_t)q.dims[1] * (uint64_t)vz);
-        const bool def = I > tau;
-        out_v[idx] = def ? V / I : 0.0f;
-        out_i[idx] = def ? I : 0.0f;
+        walk_split<SL, R>(rec, gids, j0, j1, lane, s_rec, px, py, pz, T, I, V);
+#pragma unroll
+    for (uint32_t t = 0; t < R; ++t) {
+        if (first + kWave / SL * t < vpc && lane % SL == 0) {
+            const bool def = I[t] > tau;
+            out_v[idx[t]] = def ? V[t] / I[t] : 0.0f;
+            out_i[idx[t]] = def ? I[t] : 0.0f;
+        }
     }
 }
 
@@ -1456,11 +1475,18 @@ hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const R
     const int64_t wpc = (vpc + kWave - 1) / kWave;
     const int64_t blocks = g.ncells * wpc;
     if (blocks <= 0) return hipSuccess;
-    uint32_t sh = 0;  // lanes of a voxel: 2^sh
-    while (vpc << (sh + 1) <= kWave) ++sh;
+    // as many voxels a wave as the cell has, the list split over the lanes left
+    const auto kernel = vpc > 64   ? k_sample_grid<1, 1>
+                        : vpc > 48 ? k_sample_grid<4, 4>
+                        : vpc > 32 ? k_sample_grid<4, 3>
+                        : vpc > 16 ? k_sample_grid<4, 2>
+                        : vpc > 8  ? k_sample_grid<4, 1>
+                        : vpc > 4  ? k_sample_grid<8, 1>
+                        : vpc > 1  ? k_sample_grid<16, 1>
+                                   : k_sample_grid<64, 1>;
     prof_begin("sample_grid", s);
-    hipLaunchKernelGGL(k_sample_grid, dim3((uint32_t)blocks), dim3(kWave), 0, s, q, g, sh, rec, gids, cell_off,
-                       T, tau, out_v, out_i);
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), dim3(kWave), 0, s, q, g, rec, gids, cell_off, T,
+                       tau, out_v, out_i);
     prof_end("sample_grid", s);
     return hipGetLastError();
 }
