@@ -83,13 +83,21 @@ __device__ __forceinline__ void accumulate(const Record &r, float px, float py, 
 // lane take it too so that both give the same bits. The grid cells' walk
 // and the query rows are bound by their LDS reads; the rewrite made them
 // 1-3 % slower, and they keep U (p - mu).
+__device__ __forceinline__ void centre_offset(const Record &r, float ox, float oy, float oz, float (&c)[3]) {
+    const double bx = (double)r.f0.x - (double)ox, by = (double)r.f0.y - (double)oy, bz = (double)r.f0.z - (double)oz;
+    c[0] = (float)((double)r.f1.x * bx + ((double)r.f1.y * by + (double)r.f1.z * bz));
+    c[1] = (float)((double)r.f2.x * by + (double)r.f2.y * bz);
+    c[2] = (float)((double)r.f2.z * bz);
+}
+
 __device__ __forceinline__ void offset_planes(float4 *buf, uint32_t lane, float ox, float oy, float oz) {
-    const float4 f0 = buf[lane], f1 = buf[kWave + lane], f2 = buf[2 * kWave + lane];
-    const float bx = f0.x - ox, by = f0.y - oy, bz = f0.z - oz;
-    const float c0 = fmaf_(f1.x, bx, fmaf_(f1.y, by, f1.z * bz));
-    const float c1 = fmaf_(f2.x, by, f2.y * bz);
-    const float c2 = f2.z * bz;
-    buf[lane] = make_float4(-c0, -c1, -c2, f0.w);
+    Record r;
+    r.f0 = buf[lane];
+    r.f1 = buf[kWave + lane];
+    r.f2 = buf[2 * kWave + lane];
+    float c[3];
+    centre_offset(r, ox, oy, oz, c);
+    buf[lane] = make_float4(-c[0], -c[1], -c[2], r.f0.w);
 }
 
 // Q' of a rewritten record (f0 = (-c, w)) at the offset a = p - o.
@@ -185,14 +193,11 @@ __device__ __forceinline__ void stage_rows(float4 *b, uint32_t plane, bool live,
                                            float oz) {
     float4 b0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b1 = b0, b2 = b0;
     if (live) {
-        const double bx = (double)r.f0.x - (double)ox, by = (double)r.f0.y - (double)oy;
-        const double bz = (double)r.f0.z - (double)oz;
-        const double c0 = (double)r.f1.x * bx + ((double)r.f1.y * by + (double)r.f1.z * bz);
-        const double c1 = (double)r.f2.x * by + (double)r.f2.y * bz;
-        const double c2 = (double)r.f2.z * bz;
-        b0 = make_float4((float)-c0, r.f1.z, r.f1.y, r.f1.x);
-        b1 = make_float4((float)-c1, r.f2.y, r.f2.x, 0.0f);
-        b2 = make_float4((float)-c2, r.f2.z, 0.0f, 0.0f);
+        float c[3];
+        centre_offset(r, ox, oy, oz, c);
+        b0 = make_float4(-c[0], r.f1.z, r.f1.y, r.f1.x);
+        b1 = make_float4(-c[1], r.f2.y, r.f2.x, 0.0f);
+        b2 = make_float4(-c[2], r.f2.z, 0.0f, 0.0f);
     }
     b[0] = b0;
     b[plane] = b1;
