@@ -694,7 +694,7 @@ static gs_status plan_queries(const char *who, const QueryParams &qp, const Grid
                               size_t plan_bytes, Plan *out, hipStream_t stream) {
     gs_status st = order_queries(who, qp, gp, nq, plan, plan_bytes, out, stream);
     if (st != GS_OK) return st;
-    GS_TRY(launch_cell_items(nq, gp, out->point_off, out->items, stream), "work items");
+    GS_TRY(launch_cell_items(nq, gp, out->point_off, out->items, false, stream), "work items");
     return GS_OK;
 }
 
@@ -703,9 +703,17 @@ static gs_status sample_ordered(const char *who, const gs_index *index, const Qu
                                 const Plan &p, float *out_value, float *out_influence, hipStream_t stream) {
     IndexWork w = index_layout(index->work, index->n_gauss, &index->grid, index->capacity);
     const bool boxed = boxed_launch(qp.n, gp.ncells, index->n_pairs);
-    if (boxed) GS_TRY(launch_refine_order(qp, gp, p.keys, p.order, p.res.pos, stream), who);
+    PointItems items = p.items;
+    if (boxed) {
+        // its items are larger ones, kept where the sort has its alternates (n
+        // words each; 320 queries a cell or more)
+        items.item_off = p.keys_alt;
+        items.items = p.order_alt;
+        GS_TRY(launch_refine_order(qp, gp, p.keys, p.order, p.res.pos, stream), who);
+        GS_TRY(launch_cell_items(qp.n, gp, p.point_off, items, true, stream), who);
+    }
     GS_TRY(launch_sample_points(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets, p.keys, p.order,
-                                p.point_off, p.items, boxed, cutoff_T(index->tau), index->tau, out_value,
+                                p.point_off, items, boxed, cutoff_T(index->tau), index->tau, out_value,
                                 out_influence, p.res, stream),
            who);
     return GS_OK;

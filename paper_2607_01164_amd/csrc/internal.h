@@ -445,11 +445,11 @@ struct PlanResults {
 };
 
 // The forward's work items from the plan's per-quarter ranges (the query
-// ordering's last step).
+// ordering's last step), or a boxed forward's.
 hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
-                             hipStream_t s);
+                             bool boxed, hipStream_t s);
 // cell_coarse: the index's per-cell flags (launch_preprocess). boxed: the
-// order is refined and pr.pos written.
+// order is refined, pr.pos written and the items a boxed forward's.
 hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec,
                                 const uint8_t *cell_coarse, const uint32_t *gids, const uint32_t *cell_off,
                                 const uint32_t *keys, const uint32_t *order, const uint32_t *point_off,

@@ -1243,9 +1243,7 @@ __global__ __launch_bounds__(kBlock, kDensePerSimd) void k_sample_dense(
     const uint32_t w = first + xcd_group<kXcdDense>(blockIdx.x, gridDim.x);
     if (w >= ((ConstU32 *)item_off)[ncells + 2]) return;
     const CellItem it = cell_item(w, ncells, cell_coarse, cell_off, point_off, item_off, items);
-    // the list's items are of 64 or 128 queries: the first ones of a cell take it
     const uint32_t nit = (it.n + kBoxedQ - 1) / kBoxedQ;
-    if (it.chunk >= nit) return;
     const uint32_t per = (it.n + nit - 1) / nit;
     const uint32_t qa = it.pa + it.chunk * per;
     const uint32_t left = it.pa + it.n - qa, qn = left < per ? left : per;
@@ -1515,9 +1513,9 @@ static uint32_t dense_item_queries(int64_t nq) {
 }
 
 hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
-                             hipStream_t s) {
+                             bool boxed, hipStream_t s) {
     if (nq <= 0) return hipSuccess;
-    const uint32_t dense_q = dense_item_queries(nq);
+    const uint32_t dense_q = boxed ? kBoxedQ : dense_item_queries(nq);
     const int64_t nbuckets = g.ncells + 1;  // cells and the outside bucket
     // buckets 0..nbuckets-1 and one empty element after them (its offset is the total)
     const int64_t ngroups = (nbuckets + 1 + kItemGroup - 1) / kItemGroup;
@@ -1543,12 +1541,11 @@ hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const
                                 const PointItems &it, bool boxed, float T, float tau, float *out_v, float *out_i,
                                 const PlanResults &pr, hipStream_t s) {
     if (q.n <= 0) return hipSuccess;
-    const uint32_t dense_q = dense_item_queries(q.n);
     prof_begin("sample_points", s);
     if (boxed) {
-        // the dense cells' items (the kernel leaves at their number); a launch
-        // holds fewer than 2^32 threads
-        const int64_t items = q.n / dense_q + g.ncells + 1;
+        // at least the dense cells' items (the kernel leaves at their number);
+        // a launch holds fewer than 2^32 threads
+        const int64_t items = q.n / kBoxedQ + g.ncells + 2;
         for (int64_t first = 0; first < items; first += kDenseLaunch) {
             const int64_t blocks = items - first < kDenseLaunch ? items - first : kDenseLaunch;
             hipLaunchKernelGGL(k_sample_dense, dim3((uint32_t)blocks), dim3(kBlock), 0, s, g, (uint32_t)first, rec,
@@ -1561,7 +1558,7 @@ hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const
     const int64_t waves = boxed ? g.ncells + 1 : it.max_items;
     hipLaunchKernelGGL(k_sample_cells, dim3((uint32_t)((waves + kSampWaves - 1) / kSampWaves)), dim3(kSampBlock), 0, s,
                        q, g, rec, cell_coarse, gids, cell_off, point_off, order, it.item_off, it.items, it.max_items,
-                       dense_q, boxed, T, tau, out_v, out_i, pr);
+                       dense_item_queries(q.n), boxed, T, tau, out_v, out_i, pr);
     prof_end("sample_points", s);
     return hipGetLastError();
 }
