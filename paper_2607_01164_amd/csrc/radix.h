@@ -71,6 +71,13 @@ template <class Key>
 __device__ __forceinline__ void small_sort(SmallSortLds &L, uint32_t n, int bits, Key key,
                                            uint32_t *__restrict__ keys, uint32_t *__restrict__ vals) {
     const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    if (n == 1) {
+        if (tid == 0) {
+            keys[0] = key(0u);
+            vals[0] = 0;
+        }
+        return;
+    }
     const uint32_t items = (n + kSmallBlock - 1) / kSmallBlock;
     const uint32_t e0 = wave * kWave * items + lane;  // item i is element e0 + 64 i
     uint32_t k[kSmallItems], v[kSmallItems];
