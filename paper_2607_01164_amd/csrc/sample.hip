@@ -514,24 +514,20 @@ __global__ __launch_bounds__(kSmallBlock) void k_order_queries_small(QueryParams
 constexpr int kRefineItems = 4;
 constexpr int kRefineTile = kBlock * kRefineItems;  // 1024
 // The place of a query in its quarter of a cell, bits from the top: halves
-// of the cell along z and y, quarters along z and y, the half of the quarter
-// along x, eighths along z and y. A prefix of 2 bits names a box of 1/4 x
-// 1/2 x 1/2 of the cell, one of 4 bits a cube of side 1/4.
-constexpr int kPlaceBits = 7;
+// of the cell along z and y, quarters along z and y. A prefix of 2 bits names a
+// box of 1/4 x 1/2 x 1/2 of the cell, all four a cube of side 1/4.
+constexpr int kPlaceBits = 4;
 // A block is left as it is when no run of one quarter is longer than this.
 constexpr int kRefineRun = 16;
 
-__device__ __forceinline__ uint32_t place_code(const GridParams &g, uint32_t key, float px, float py, float pz) {
-    const uint32_t c = key / kSub, nx = (uint32_t)g.cells[0], ny = (uint32_t)g.cells[1];
-    const uint32_t cyz = c / nx, cx = c - cyz * nx, cz = cyz / ny, cy = cyz - cz * ny;
-    // eighths of the cell along each axis, 0..7 (of a quarter along x: 0, 1)
-    const float tx = (px - g.lo[0]) * g.invc[0] - (float)cx, ty = (py - g.lo[1]) * g.invc[1] - (float)cy;
-    const float tz = (pz - g.lo[2]) * g.invc[2] - (float)cz;
-    const uint32_t ex = (uint32_t)fminf(fmaxf(tx * 8.0f - 2.0f * (float)(key % kSub), 0.0f), 1.0f);
-    const uint32_t ey = (uint32_t)fminf(fmaxf(ty * 8.0f, 0.0f), 7.0f);
-    const uint32_t ez = (uint32_t)fminf(fmaxf(tz * 8.0f, 0.0f), 7.0f);
-    return ((ez >> 2) << 6) | ((ey >> 2) << 5) | (((ez >> 1) & 1u) << 4) | (((ey >> 1) & 1u) << 3) | (ex << 2) |
-           ((ez & 1u) << 1) | (ey & 1u);
+__device__ __forceinline__ uint32_t place_code(const GridParams &g, uint32_t key, float py, float pz) {
+    const uint32_t cyz = key / kSub / (uint32_t)g.cells[0], ny = (uint32_t)g.cells[1];
+    const uint32_t cz = cyz / ny, cy = cyz - cz * ny;
+    const float ty = (py - g.lo[1]) * g.invc[1] - (float)cy, tz = (pz - g.lo[2]) * g.invc[2] - (float)cz;
+    // quarters of the cell, 0..3
+    const uint32_t iy = (uint32_t)fminf(fmaxf(ty * 4.0f, 0.0f), 3.0f);
+    const uint32_t iz = (uint32_t)fminf(fmaxf(tz * 4.0f, 0.0f), 3.0f);
+    return ((iz >> 1) << 3) | ((iy >> 1) << 2) | ((iz & 1u) << 1) | (iy & 1u);
 }
 
 // Stable places of the block's kRefineTile elements by digit (< 2^bits):
@@ -616,7 +612,7 @@ __global__ __launch_bounds__(kBlock) void k_refine_order(QueryParams q, GridPara
             longrun = longrun || (e + kRefineRun < have && keys[base + e + kRefineRun] == key);
             bool valid;
             query_position(q, g, pid[i], p[i].x, p[i].y, p[i].z, valid);
-            if (key < kSub * (uint32_t)g.ncells) code[i] = place_code(g, key, p[i].x, p[i].y, p[i].z);
+            if (key < kSub * (uint32_t)g.ncells) code[i] = place_code(g, key, p[i].y, p[i].z);
             p[i].w = __uint_as_float(code[i]);
         } else {
             first[i] = e == have;  // the elements past the end are a last run
