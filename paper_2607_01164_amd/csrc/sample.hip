@@ -64,6 +64,14 @@ __device__ __forceinline__ void accumulate(const Record &r, float px, float py, 
     }
 }
 
+// c = U (mu - o) of a record, formed in float64 and rounded once.
+__device__ __forceinline__ void centre_offset(const Record &r, float ox, float oy, float oz, float (&c)[3]) {
+    const double bx = (double)r.f0.x - (double)ox, by = (double)r.f0.y - (double)oy, bz = (double)r.f0.z - (double)oz;
+    c[0] = (float)((double)r.f1.x * bx + ((double)r.f1.y * by + (double)r.f1.z * bz));
+    c[1] = (float)((double)r.f2.x * by + (double)r.f2.y * bz);
+    c[2] = (float)((double)r.f2.z * bz);
+}
+
 // Records staged for the queries of one cell are rewritten relative to a
 // point o of the cell (its centre): the first quarter of candidate s holds
 // (-c, w) with c = U (mu - o), so that a query at a = p - o has u = U a - c,
@@ -79,17 +87,11 @@ __device__ __forceinline__ void accumulate(const Record &r, float px, float py, 
 // evaluates a marked cell as U (p - mu).
 // Lane s rewrites candidate s of the wave's planes. The dense cells' walk
 // takes it: with two queries a lane it is bound by VALU issue (10^8
-// clustered points: the forward 6.6 % faster), and the items of one query a
-// lane take it too so that both give the same bits. The grid cells' walk
-// and the query rows are bound by their LDS reads; the rewrite made them
-// 1-3 % slower, and they keep U (p - mu).
-__device__ __forceinline__ void centre_offset(const Record &r, float ox, float oy, float oz, float (&c)[3]) {
-    const double bx = (double)r.f0.x - (double)ox, by = (double)r.f0.y - (double)oy, bz = (double)r.f0.z - (double)oz;
-    c[0] = (float)((double)r.f1.x * bx + ((double)r.f1.y * by + (double)r.f1.z * bz));
-    c[1] = (float)((double)r.f2.x * by + (double)r.f2.y * bz);
-    c[2] = (float)((double)r.f2.z * bz);
-}
-
+// clustered points, before they were boxed: the forward 6.6 % faster), and the
+// items of one query a lane take it too so that both give the same bits, which
+// are also the boxed walk's (stage_rows). The grid cells' walk and the query
+// rows are bound by their LDS reads; the rewrite made them 1-3 % slower, and
+// they keep U (p - mu).
 __device__ __forceinline__ void offset_planes(float4 *buf, uint32_t lane, float ox, float oy, float oz) {
     Record r;
     r.f0 = buf[lane];
@@ -188,7 +190,7 @@ __device__ __forceinline__ Record load_record(const Record *__restrict__ rec, ui
 }
 
 // A candidate's rows into entry b[0] of planes `plane` entries apart: record
-// r about o, or the all-zero record. c is formed in float64 and rounded once.
+// r about o, or the all-zero record.
 __device__ __forceinline__ void stage_rows(float4 *b, uint32_t plane, bool live, const Record &r, float ox, float oy,
                                            float oz) {
     float4 b0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b1 = b0, b2 = b0;
@@ -353,22 +355,33 @@ __device__ __forceinline__ void walk_staged_r(const Record *__restrict__ rec, bo
 }
 
 
-// walk_staged for a cell of at most 64 voxels: SL lanes a voxel and R voxels a
-// lane, lane l taking voxels l / SL + (64 / SL) t, t < R, with the candidates
-// c0 + l mod SL + SL i of each 64. With a voxel a lane the lanes past the
-// cell's voxels idle through the whole list, and every candidate's record is
-// read from LDS for one voxel a lane, which bounds the walk. 529,113 Gaussians
-// in 58^3 cells, us, a voxel a lane and split: 1 voxel a cell 601 and 188, 8
-// voxels 529 and 198, 16 543 and 204, 32 544 and 259, 48 575 and 381, 64 560
-// and 464. The lanes of a voxel get its sums. (Matrix tiles take offsets from a
-// point of the cell, whose rounding grows with the cell against the Gaussians'
-// smallest scales, and took 264, 228, 226, 309 and 420 us up to 48 voxels.)
+// walk_staged for a cell of at most 64 voxels, lane l at (px, py, pz) of voxel
+// l: SL lanes a voxel and R voxels a lane, lane l testing voxels l / SL + (64 /
+// SL) t, t < R, with the candidates c0 + l mod SL + SL i of each 64. With a
+// voxel a lane the lanes past the cell's voxels idle through the whole list,
+// and every candidate's record is read from LDS for one voxel a lane, which
+// bounds the walk. 529,113 Gaussians in 58^3 cells, us, a voxel a lane and
+// split: 1 voxel a cell 581 and 185, 8 voxels 523 and 202, 16 526 and 192, 32
+// 528 and 260, 48 537 and 359, 64 533 and 450. (Matrix tiles take offsets from
+// a point of the cell, whose rounding grows with the cell against the
+// Gaussians' smallest scales, and took 248, 221, 216, 305 and 392 us up to 48
+// voxels.)
 template <uint32_t SL, uint32_t R>
 __device__ __forceinline__ void walk_split(const Record *__restrict__ rec, const uint32_t *__restrict__ gids,
-                                           uint32_t ja, uint32_t jb, uint32_t lane, float4 *buf, const float (&px)[R],
-                                           const float (&py)[R], const float (&pz)[R], float T, float (&I)[R],
-                                           float (&V)[R]) {
+                                           uint32_t ja, uint32_t jb, uint32_t lane, float4 *buf, float px0, float py0,
+                                           float pz0, float T, float &Io, float &Vo) {
+    static_assert(R <= SL, "a lane of each voxel for each of a lane's voxels");
+    constexpr uint32_t N = kWave / SL;  // voxels of one t
     const uint32_t slot = lane % SL;
+    float px[R], py[R], pz[R], I[R], V[R];
+#pragma unroll
+    for (uint32_t t = 0; t < R; ++t) {
+        const int src = (int)(lane / SL + N * t);
+        px[t] = __shfl(px0, src, kWave);
+        py[t] = __shfl(py0, src, kWave);
+        pz[t] = __shfl(pz0, src, kWave);
+        I[t] = V[t] = 0.0f;
+    }
     uint32_t gnext = 0;
     if (ja < jb) gnext = gids[ja + lane < jb ? ja + lane : jb - 1];
     for (uint32_t c0 = ja; c0 < jb; c0 += kWave) {
@@ -395,17 +408,25 @@ __device__ __forceinline__ void walk_split(const Record *__restrict__ rec, const
         // every lane has read the planes before the next chunk overwrites them
         __builtin_amdgcn_wave_barrier();
     }
+    // lane l's sums of voxel l / SL + N (l mod SL), then voxel l's to lane l
+    float Is = 0.0f, Vs = 0.0f;
 #pragma unroll
-    for (uint32_t t = 0; t < R; ++t)
+    for (uint32_t t = 0; t < R; ++t) {
 #pragma unroll
         for (uint32_t o = 1; o < SL; o <<= 1) {
             I[t] += __shfl_xor(I[t], (int)o, kWave);
             V[t] += __shfl_xor(V[t], (int)o, kWave);
         }
+        Is = slot == t ? I[t] : Is;
+        Vs = slot == t ? V[t] : Vs;
+    }
+    const int from = (int)((lane % N) * SL + lane / N) & (kWave - 1);
+    Io = __shfl(Is, from, kWave);
+    Vo = __shfl(Vs, from, kWave);
 }
 
-// A wave's voxels of a grid cell: SL lanes a voxel and R voxels a lane
-// (walk_split), or a voxel a lane, 64 of the cell's (SL 1, walk_staged).
+// A wave's voxels of a grid cell, voxel first + l in lane l: all of the cell's,
+// walk_split's way, or 64 of them a lane each (SL 1, walk_staged).
 template <uint32_t SL, uint32_t R>
 __global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams q, GridParams g,
                                                         const Record *__restrict__ rec,
@@ -421,34 +442,25 @@ __global__ __launch_bounds__(kWave, kSampPerSimd) void k_sample_grid(QueryParams
     const uint32_t lane = threadIdx.x;
     // ncells wpc < 2^32: at most a wave per cell and one per 64 voxels
     const uint32_t cell = blockIdx.x / wpc;
-    const uint32_t first = (blockIdx.x - cell * wpc) * kWave + lane / SL;
+    const uint32_t local = (blockIdx.x - cell * wpc) * kWave + lane;
     const uint32_t nx = (uint32_t)g.cells[0], ny = (uint32_t)g.cells[1];
     const uint32_t cyz = cell / nx, cx = cell - cyz * nx, cz = cyz / ny, cy = cyz - cz * ny;
-    float px[R], py[R], pz[R], I[R], V[R];
-    uint64_t idx[R];
-#pragma unroll
-    for (uint32_t t = 0; t < R; ++t) {
-        const uint32_t local = first + kWave / SL * t;
-        const uint32_t lyz = local / rx, lx = local - lyz * rx, lz = lyz / ry, ly = lyz - lz * ry;
-        const int32_t vx = (int32_t)(cx * rx + lx), vy = (int32_t)(cy * ry + ly), vz = (int32_t)(cz * rz + lz);
-        px[t] = voxel_center(vx, g.lo[0], q.vsz[0]);
-        py[t] = voxel_center(vy, g.lo[1], q.vsz[1]);
-        pz[t] = voxel_center(vz, g.lo[2], q.vsz[2]);
-        idx[t] = (uint64_t)vx + (uint64_t)q.dims[0] * ((uint64_t)vy + (uint64_t)q.dims[1] * (uint64_t)vz);
-        I[t] = V[t] = 0.0f;
-    }
+    const uint32_t lyz = local / rx, lx = local - lyz * rx, lz = lyz / ry, ly = lyz - lz * ry;
+    const int32_t vx = (int32_t)(cx * rx + lx), vy = (int32_t)(cy * ry + ly), vz = (int32_t)(cz * rz + lz);
+    const float px = voxel_center(vx, g.lo[0], q.vsz[0]);
+    const float py = voxel_center(vy, g.lo[1], q.vsz[1]);
+    const float pz = voxel_center(vz, g.lo[2], q.vsz[2]);
     const uint32_t j0 = ((ConstU32 *)cell_off)[cell], j1 = ((ConstU32 *)cell_off)[cell + 1];
+    float I = 0.0f, V = 0.0f;
     if constexpr (SL == 1)
-        walk_staged(rec, gids, j0, j1, lane, s_rec, px[0], py[0], pz[0], T, I[0], V[0]);
-    else
+        walk_staged(rec, gids, j0, j1, lane, s_rec, px, py, pz, T, I, V);
+    else if (j0 < j1)
         walk_split<SL, R>(rec, gids, j0, j1, lane, s_rec, px, py, pz, T, I, V);
-#pragma unroll
-    for (uint32_t t = 0; t < R; ++t) {
-        if (first + kWave / SL * t < vpc && lane % SL == 0) {
-            const bool def = I[t] > tau;
-            out_v[idx[t]] = def ? V[t] / I[t] : 0.0f;
-            out_i[idx[t]] = def ? I[t] : 0.0f;
-        }
+    if (local < vpc) {
+        const uint64_t idx = (uint64_t)vx + (uint64_t)q.dims[0] * ((uint64_t)vy + (uint64_t)q.dims[1] * (uint64_t)vz);
+        const bool def = I > tau;
+        out_v[idx] = def ? V / I : 0.0f;
+        out_i[idx] = def ? I : 0.0f;
     }
 }
 
@@ -690,9 +702,11 @@ constexpr uint32_t kDenseMin = 32;
 // against 13 VALU operations), but make half as many items, each twice as
 // long: a launch with few items per wave slot of the chip then ends with
 // long items running alone. Two a lane are taken from kDenseBalance items
-// per wave slot at one a lane (measured: 4.6 per slot, a 2^21-point batch
-// of clustered points, runs 11 % faster with one; 218, 10^8 points, 19 %
-// faster with two).
+// per wave slot at one a lane (measured, one and two a lane: 4.6 per slot, a
+// 2^21-point batch of clustered points, 11 % faster with one; 33 per slot, 15 M
+// points in 40^3 cells, 1.10 and 0.98 ms uniform, 2.99 and 2.47 clustered; 218
+// per slot, 10^8 points in 64^3 cells, 11.3 and 11.5 uniform, 17.0 and 14.3
+// clustered).
 constexpr uint32_t kDenseBalance = 32;
 // Queries of a boxed launch's dense items, each taken by a workgroup whose
 // waves share the cell's records in LDS. Sixteen tiles, one pass of four
