@@ -6,11 +6,11 @@
 // - o), u = U a - c is a product of the 3 x 4 matrix (-c, U) with (1, a). For
 // 16 queries and 16 Gaussians these are three 16x16x4 float32 matrix
 // products (v_mfma_f32_16x16x4_f32), each component an ascending chain of
-// float32 fused multiply-adds. They do not run beside the same wave's vector
-// work (36 cycles each, added to the vector instructions' time), so they cost
-// 27 issue slots per 256 pairs where the vector form takes 24; what they save
-// is the vector form's read of every record from LDS once per 64 queries,
-// which bounds it (24 LDS cycles a record and wave, four SIMDs to an LDS).
+// float32 fused multiply-adds. They do not run beside vector work (measured: 36
+// cycles each, added to the vector instructions' time), so they cost 27 issue
+// slots per 256 pairs where the vector form takes 24; what they save is the
+// vector form's read of every record from LDS once per 64 queries, which bounds
+// it (24 LDS cycles a record and wave, four SIMDs to an LDS).
 // The walk of dense cells in boxed launches takes them (k_sample_dense).
 //
 // Grid queries (Sec. 4.1.3, Fig. 4 C): one wavefront per (cell, 64 voxels of
@@ -154,13 +154,11 @@ constexpr uint32_t kTile = 16;              // queries of a matrix tile, and Gau
 // LDS of a dense item's workgroup. The records of up to kBlock candidates:
 // the rows (-c_i, U_iz, U_iy, U_ix) of (-c, U), in the order the matrix
 // product's fused multiply-adds take them, and (w, w v). -c comes first, so
-// that u is rounded as offset_q rounds it: the sums of U a are not rounded by
-// themselves before c cancels them (c last: 1.0 to 1.3 times the rms error of
-// Q' at the cutoff for round Gaussians in cells of 2 to 60 times their scale;
-// c first, with c formed in float64: 0.56 to 1.0 times offset_q's for axis
-// ratios of 1 to 30). Entry kBlock is an
-// all-zero record that pads lists to whole tiles. The walk of a coarse cell
-// uses the rows' space for staged records, a quarter of it a wave
+// that Q' has offset_q's bits. (c last, the sums of U a are rounded by
+// themselves before c cancels them: 1.0 to 1.4 times the rms error of Q' at the
+// cutoff, round Gaussians in cells of 6 to 60 times their scale.) Entry kBlock
+// is an all-zero record that pads lists to whole tiles. The walk of a coarse
+// cell uses the rows' space for staged records, a quarter of it a wave
 // (wave_records).
 struct DenseLds {
     float4 b[3][kBlock + 1];
@@ -1093,10 +1091,9 @@ __device__ __forceinline__ uint32_t list_reaching(DenseLds &L, uint32_t wave, ui
 }
 
 // A dense cell's work item of a boxed launch: queries [qa, qa + qn) of the
-// plan, qn <= kBoxedQ,
-// by the whole workgroup. The queries are cut into tiles of up to 16 that do
-// not cross a box (found with ballots over the queries' bins), at most
-// kSlots of them to a wave and pass. The cell's records are staged kBlock at
+// plan, qn <= kBoxedQ, by the whole workgroup. The queries are cut into tiles
+// of up to 16 that do not cross a box (found with ballots over the queries'
+// bins), at most kSlots of them to a wave and pass. The cell's records are staged kBlock at
 // a time; each wave lists the ones that reach its tiles' box, and takes the
 // list 16 candidates at a time.
 constexpr uint32_t kSlots = 4;

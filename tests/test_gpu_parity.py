@@ -15,8 +15,8 @@ import pytest
 
 import oracle
 import synth
-from harness import (TAU, Run, check_backward, check_forward, check_index, check_index_arrays, gpu_boxes, log,
-                     masked_cotangents)
+from harness import (TAU, Run, check_backward, check_forward, check_index, check_index_arrays, gpu_boxes, is_boxed,
+                     log, masked_cotangents)
 
 pytestmark = pytest.mark.gpu
 
@@ -283,6 +283,7 @@ def test_dense_items_of_two_queries_a_lane():
     pts = synth.random_points(98, n)
     log(f"case dense items: {g.n} Gaussians, {n} uniform points, cells (16, 16, 16)")
     r = Run(g, (16, 16, 16), "points", points=pts)
+    assert not is_boxed(r)
     phi, inf = r.forward()
     check_forward(r, phi, inf, sel=np.sort(np.random.default_rng(99).choice(n, 2048, replace=False)),
                   label="two a lane")
@@ -332,6 +333,7 @@ def test_dense_walk_keeps_small_gaussians_in_coarse_cells_exact():
                         rng.random(nt + nw).astype(f), np.concatenate([rng.uniform(0.5, 1.0, nt), np.ones(nw)]).astype(f))
     log(f"case coarse cells: {nt} tiny and {nw} wide Gaussians, {len(pts)} points on cutoff surfaces, cells (8, 8, 8)")
     r = Run(g, (8, 8, 8), "points", points=pts.astype(f))
+    assert not is_boxed(r)
     phi, inf = r.forward()
     ref, stats = check_forward(r, phi, inf, label="coarse cells")
     assert stats["defined"] > 0.9 * len(pts)
@@ -359,6 +361,7 @@ def test_dense_cells_every_output():
     per = np.bincount(c[:, 0] + 8 * (c[:, 1] + 8 * c[:, 2]), minlength=512)
     log(f"  queries per cell: max {per.max()}, cells with >= 128: {int((per >= 128).sum())}")
     assert per.max() > 2000 and (per >= 128).sum() > 20
+    assert not is_boxed(r)
     phi, inf = r.forward()
     ref, _ = check_forward(r, phi, inf, label="dense cells")
     gv, gi = synth.random_normal(103, r.nq), synth.random_normal(104, r.nq)
