@@ -20,8 +20,9 @@ hipError_t launch_loss(int64_t n, const float *value, const float *influence, co
                        float *grad_value, float *grad_influence, gs_loss_terms *terms, void *work, hipStream_t s);
 hipError_t launch_sample_gauss_major(const QueryParams &q, const GridParams &g, const BwdGeom &bg, const Record *rec,
                                      const CellBox *box, const uint32_t *gorder,
-                                     int64_t n_gauss, const uint32_t *order, const uint32_t *point_off, bool placed,
-                                     float T, float tau, float *out_v, float *out_i, const PlanResults &pr, void *work,
+                                     int64_t n_gauss, const uint32_t *order, const uint32_t *point_off,
+                                     const uint32_t *boxed, float T, float tau, float *out_v, float *out_i,
+                                     const PlanResults &pr, void *work,
                                      hipStream_t s);
 size_t gauss_major_work_bytes(int64_t nq);
 hipError_t launch_densify(const gs_params &in, int64_t n_in, const float *weight, float tau2, const QueryParams &q,
@@ -209,7 +210,7 @@ Plan plan_layout(void *base, int64_t n, int64_t ncells) {
     p.order_alt = c.take<uint32_t>(m);
     p.point_off = c.take<uint32_t>((size_t)kSub * ncells + 2);
     p.radix_work = c.take<char>(radix_work_bytes(n > 0 ? n : 1, bits_for((int64_t)kSub * ncells + 1)));
-    p.items.item_off = c.take<uint32_t>((size_t)ncells + 3);
+    p.items.item_off = c.take<uint32_t>((size_t)ncells + 2);
     p.items.max_items = ncells + 1 + (n > 0 ? n : 0) / 64 + 1;
     p.items.items = c.take<uint32_t>((size_t)p.items.max_items);
     p.items.group_sum = c.take<uint64_t>((size_t)item_groups(ncells + 1) + 1);
@@ -694,7 +695,27 @@ static gs_status plan_queries(const char *who, const QueryParams &qp, const Grid
                               size_t plan_bytes, Plan *out, hipStream_t stream) {
     gs_status st = order_queries(who, qp, gp, nq, plan, plan_bytes, out, stream);
     if (st != GS_OK) return st;
-    GS_TRY(launch_cell_items(nq, gp, out->point_off, out->items, false, stream), "work items");
+    GS_TRY(launch_cell_items(nq, gp, out->point_off, out->items, stream), "work items");
+    return GS_OK;
+}
+
+// The boxed forward's items and refined order for queries in order (no items,
+// *boxed null, where it is not tried). Its items lie where the sort has its
+// alternates, n words each (320 queries a cell or more).
+static gs_status plan_boxes(const char *who, const QueryParams &qp, const GridParams &gp, const gs_index *index,
+                            const Plan &p, BoxedItems *b, hipStream_t stream) {
+    *b = BoxedItems{};
+    const int64_t list = boxed_list(qp.n, gp.ncells, index->n_pairs);
+    if (list < 0) return GS_OK;
+    Carver c(p.keys_alt);
+    b->item_off = c.take<uint32_t>((size_t)gp.ncells + 2);
+    b->flags = c.take<uint32_t>(2);
+    b->group_vote = c.take<uint64_t>((size_t)item_groups(gp.ncells + 1) + 1);
+    b->items = p.order_alt;
+    b->max_items = qp.n;
+    GS_TRY(launch_boxed_items(qp, gp, index->cell_offsets, p.keys, p.point_off, list, p.items, *b, p.order, p.res.pos,
+                              stream),
+           who);
     return GS_OK;
 }
 
@@ -702,18 +723,11 @@ static gs_status plan_queries(const char *who, const QueryParams &qp, const Grid
 static gs_status sample_ordered(const char *who, const gs_index *index, const QueryParams &qp, const GridParams &gp,
                                 const Plan &p, float *out_value, float *out_influence, hipStream_t stream) {
     IndexWork w = index_layout(index->work, index->n_gauss, &index->grid, index->capacity);
-    const bool boxed = boxed_launch(qp.n, gp.ncells, index->n_pairs);
-    PointItems items = p.items;
-    if (boxed) {
-        // its items are larger ones, kept where the sort has its alternates (n
-        // words each; 320 queries a cell or more)
-        items.item_off = p.keys_alt;
-        items.items = p.order_alt;
-        GS_TRY(launch_refine_order(qp, gp, p.keys, p.order, p.res.pos, stream), who);
-        GS_TRY(launch_cell_items(qp.n, gp, p.point_off, items, true, stream), who);
-    }
+    BoxedItems boxed;
+    const gs_status st = plan_boxes(who, qp, gp, index, p, &boxed, stream);
+    if (st != GS_OK) return st;
     GS_TRY(launch_sample_points(qp, gp, w.rec, w.cell_coarse, index->gids, index->cell_offsets, p.keys, p.order,
-                                p.point_off, items, boxed, cutoff_T(index->tau), index->tau, out_value,
+                                p.point_off, p.items, boxed, cutoff_T(index->tau), index->tau, out_value,
                                 out_influence, p.res, stream),
            who);
     return GS_OK;
@@ -810,11 +824,11 @@ gs_status gs_sample_gaussian_major(const gs_gaussians *gauss, const gs_index *in
         return st;
     // the order by place also brings the queries a Gaussian meets together
     // (2^24 clustered points 69.6 -> 54.4 ms)
-    const bool boxed = boxed_launch(nq, gp.ncells, index->n_pairs);
-    if (boxed) GS_TRY(launch_refine_order(qp, gp, p.keys, p.order, p.res.pos, stream), "gs_sample_gaussian_major");
+    BoxedItems boxed;
+    if ((st = plan_boxes("gs_sample_gaussian_major", qp, gp, index, p, &boxed, stream)) != GS_OK) return st;
     GS_TRY(launch_sample_gauss_major(qp, gp, bwd_geom(gp, qp, cutoff_T(index->tau)), w.rec, w.box, w.gorder,
-                                     index->n_gauss, p.order, p.point_off, boxed, cutoff_T(index->tau), index->tau,
-                                     out_value, out_influence, p.res, work, stream),
+                                     index->n_gauss, p.order, p.point_off, boxed.flags, cutoff_T(index->tau),
+                                     index->tau, out_value, out_influence, p.res, work, stream),
            "gs_sample_gaussian_major");
     return GS_OK;
 }

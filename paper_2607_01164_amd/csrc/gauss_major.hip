@@ -34,14 +34,13 @@ __device__ __forceinline__ float eval_pair(const Record &r, float4 p, float T) {
 
 // Position of every query in plan order (the walk below reads them
 // contiguously); queries outside the domain sit in the outside bucket,
-// which no Gaussian visits. PLACED: the plan holds them already
-// (launch_refine_order).
-template <bool PLACED>
+// which no Gaussian visits. Where boxed is given and not 0 the plan holds them
+// already (BoxedItems::flags).
 __global__ __launch_bounds__(kBlock) void k_plan_positions(QueryParams q, GridParams g, const uint32_t *order,
-                                                           float4 *pos, double *acc) {
+                                                           const uint32_t *boxed, float4 *pos, double *acc) {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= q.n) return;
-    if (!PLACED) {
+    if (!boxed || *boxed == 0) {
         float px, py, pz;
         bool valid;
         query_position(q, g, order[k], px, py, pz, valid);
@@ -129,17 +128,15 @@ size_t gauss_major_work_bytes(int64_t nq) { return (size_t)(nq > 0 ? nq : 1) * 2
 
 hipError_t launch_sample_gauss_major(const QueryParams &q, const GridParams &g, const BwdGeom &bg, const Record *rec,
                                      const CellBox *box, const uint32_t *gorder,
-                                     int64_t n_gauss, const uint32_t *order, const uint32_t *point_off, bool placed,
-                                     float T, float tau, float *out_v, float *out_i, const PlanResults &pr, void *work,
+                                     int64_t n_gauss, const uint32_t *order, const uint32_t *point_off,
+                                     const uint32_t *boxed, float T, float tau, float *out_v, float *out_i,
+                                     const PlanResults &pr, void *work,
                                      hipStream_t s) {
     if (q.n <= 0) return hipSuccess;
     double *acc = (double *)work;
     const uint32_t nb = (uint32_t)((q.n + kBlock - 1) / kBlock);
     prof_begin("gm_positions", s);
-    if (placed)
-        hipLaunchKernelGGL(k_plan_positions<true>, dim3(nb), dim3(kBlock), 0, s, q, g, order, pr.pos, acc);
-    else
-        hipLaunchKernelGGL(k_plan_positions<false>, dim3(nb), dim3(kBlock), 0, s, q, g, order, pr.pos, acc);
+    hipLaunchKernelGGL(k_plan_positions, dim3(nb), dim3(kBlock), 0, s, q, g, order, boxed, pr.pos, acc);
     prof_end("gm_positions", s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

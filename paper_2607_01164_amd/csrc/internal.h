@@ -419,16 +419,9 @@ hipError_t launch_query_keys(const QueryParams &q, const GridParams &g, uint32_t
 hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const Record *rec, const uint32_t *gids,
                               const uint32_t *cell_off, float T, float tau, float *out_v, float *out_i,
                               hipStream_t s);
-// Whether the forward of nq ordered queries in ncells cells with n_pairs pairs
-// is boxed: it first refines the plan's order by place inside quarters of cells
-// (in place; the same order comes out whether or not it is refined already) and
-// writes the positions in that order, the place in w.
-bool boxed_launch(int64_t nq, int64_t ncells, int64_t n_pairs);
-hipError_t launch_refine_order(const QueryParams &q, const GridParams &g, const uint32_t *keys, uint32_t *order,
-                               float4 *pos, hipStream_t s);
 // Work items of the ordered-query sampler (kept in the plan).
 struct PointItems {
-    uint32_t *item_off;   // [ncells + 3]
+    uint32_t *item_off;   // [ncells + 2]
     uint32_t *items;      // [max_items]
     int64_t max_items;    // ncells + 1 + n / 64 + 1
     uint64_t *group_sum;  // [item_groups(ncells + 1) + 1] work items per 1024 buckets, (dense << 32) | sparse
@@ -445,16 +438,33 @@ struct PlanResults {
 };
 
 // The forward's work items from the plan's per-quarter ranges (the query
-// ordering's last step), or a boxed forward's.
+// ordering's last step).
 hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
-                             bool boxed, hipStream_t s);
-// cell_coarse: the index's per-cell flags (launch_preprocess). boxed: the
-// order is refined, pr.pos written and the items a boxed forward's.
+                             hipStream_t s);
+// A boxed forward's work items.
+struct BoxedItems {
+    uint32_t *item_off;    // [ncells + 2], null where boxes are not tried
+    uint32_t *flags;       // [2]: the dense items, 0 where the launch is not boxed; the next of them to take
+    uint64_t *group_vote;  // [item_groups(ncells + 1) + 1] pairs tested per 1024 buckets
+    uint32_t *items;       // [max_items]
+    int64_t max_items;
+};
+// The pairs a query of the domain has to test on average for the forward of nq
+// ordered queries in ncells cells with n_pairs pairs to be boxed; -1: it is not.
+int64_t boxed_list(int64_t nq, int64_t ncells, int64_t n_pairs);
+// Takes that decision on the device. A boxed launch gets its items (it: the
+// plan's, for scratch), its order refined by place inside quarters of cells (in
+// place; the same order comes out whether or not it is refined already) and the
+// positions in that order, the place in w.
+hipError_t launch_boxed_items(const QueryParams &q, const GridParams &g, const uint32_t *cell_off,
+                              const uint32_t *keys, const uint32_t *point_off, int64_t list, const PointItems &it,
+                              const BoxedItems &b, uint32_t *order, float4 *pos, hipStream_t s);
+// cell_coarse: the index's per-cell flags (launch_preprocess).
 hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec,
                                 const uint8_t *cell_coarse, const uint32_t *gids, const uint32_t *cell_off,
                                 const uint32_t *keys, const uint32_t *order, const uint32_t *point_off,
-                                const PointItems &it, bool boxed, float T, float tau, float *out_v, float *out_i,
-                                const PlanResults &pr, hipStream_t s);
+                                const PointItems &it, const BoxedItems &boxed, float T, float tau, float *out_v,
+                                float *out_i, const PlanResults &pr, hipStream_t s);
 
 // Pairs the forward tests and those passing the cutoff (measurement), into
 // totals[0] and totals[1] (device, 16 bytes); plan_keys and plan_pos are

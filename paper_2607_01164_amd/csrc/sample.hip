@@ -20,7 +20,7 @@
 // Voxel-list, point and jittered queries (Sec. 5.1.2): the queries are first
 // ordered by cell and, inside a cell, by quarter of the cell along x
 // (query_keys + radix sort, kept in the plan), and the work is split by cell
-// (see k_sample_cells). Where many queries meet long lists (boxed_launch), the
+// (see k_sample_cells). Where many queries meet long lists (boxed_list), the
 // forward also orders them by place inside the quarter (k_refine_order) and
 // cuts dense cells into boxes that meet only the candidates reaching them
 // (k_sample_dense).
@@ -131,7 +131,7 @@ __device__ __forceinline__ void accumulate_off_sel(const Record &r, float ax, fl
 
 // Four consecutive work items per XCD (xcd_group): the items of one cell
 // share that XCD's L2 (C5's forward 1.6 % faster, C4's unchanged).
-constexpr uint32_t kXcdItems = 4, kXcdDense = 2;
+constexpr uint32_t kXcdItems = 4;
 
 // The centre of cell c (float32; any point of the cell would do), for a
 // wave-uniform c: kept in scalar registers.
@@ -169,6 +169,7 @@ struct DenseLds {
     float lw[kDenseWaves][kBlock + kTile], lv[kDenseWaves][kBlock + kTile];
     uint16_t tile_start[kBlock], tile_bin[kBlock];
     uint64_t ballot[2][kDenseWaves];
+    uint32_t next;
 };
 static_assert(sizeof(float4) * kRecordQuads * kWave * kDenseWaves <= sizeof(DenseLds::b), "staged records fit the rows");
 
@@ -594,8 +595,10 @@ __device__ __forceinline__ void block_split(const uint32_t (&d)[kRefineItems], i
 }
 
 __global__ __launch_bounds__(kBlock) void k_refine_order(QueryParams q, GridParams g,
+                                                         const uint32_t *__restrict__ boxed,
                                                          const uint32_t *__restrict__ keys, uint32_t *order,
                                                          float4 *__restrict__ pos) {
+    if (boxed[0] == 0) return;
     __shared__ float4 s_pos[kRefineTile];
     __shared__ uint32_t s_pid[kRefineTile];
     __shared__ uint32_t s_cnt[kWavesPerBlock * kRefineTile];  // up to kRefineTile runs
@@ -739,8 +742,11 @@ constexpr int kItemGroup = kBlock * kItemsPerThread;  // 1024
 // total after them).
 constexpr int64_t kInlineGroups = 1024;
 
+// With cell_off also the pairs the group's queries test (queries times list).
 __global__ __launch_bounds__(kBlock) void k_item_sums(const uint32_t *__restrict__ point_off, int64_t nbuckets,
-                                                      uint32_t dense_q, uint64_t *__restrict__ group_sum) {
+                                                      uint32_t dense_q, uint64_t *__restrict__ group_sum,
+                                                      const uint32_t *__restrict__ cell_off,
+                                                      uint64_t *__restrict__ group_vote) {
     __shared__ uint64_t lds[kWavesPerBlock];
     const int64_t base = (int64_t)blockIdx.x * kItemGroup + (int64_t)threadIdx.x * kItemsPerThread;
     uint64_t s = 0;
@@ -749,17 +755,32 @@ __global__ __launch_bounds__(kBlock) void k_item_sums(const uint32_t *__restrict
     uint64_t tot;
     (void)block_excl_scan(s, lds, &tot);
     if (threadIdx.x == 0) group_sum[blockIdx.x] = tot;
+    if (!cell_off) return;
+    uint64_t p = 0;
+#pragma unroll
+    for (int i = 0; i < kItemsPerThread; ++i) {
+        const int64_t c = base + i;
+        if (c + 1 < nbuckets)
+            p += (uint64_t)(point_off[kSub * (c + 1)] - point_off[kSub * c]) * (cell_off[c + 1] - cell_off[c]);
+    }
+    (void)block_excl_scan(p, lds, &tot);
+    if (threadIdx.x == 0) group_vote[blockIdx.x] = tot;
 }
 
 // item_off[c] for c <= nbuckets: the first item of bucket c (item_off[nbuckets]
-// = the total, followed by the dense buckets' total), and the item list: item_off[c] .. item_off[c] + items(c) - 1
+// = the total), and the item list: item_off[c] .. item_off[c] + items(c) - 1
 // name bucket c. group_sum: the groups' sums, or (scanned) their exclusive
-// prefixes followed by the total.
+// prefixes followed by the total. With flags, the items of a launch that is
+// boxed if its queries in the domain test `list` pairs or more on average
+// (group_vote: as group_sum): flags[0] is then the dense items' number, else 0,
+// without any items, and flags[1] 0.
 __global__ __launch_bounds__(kBlock) void k_item_offsets(const uint32_t *__restrict__ point_off, int64_t nbuckets,
                                                          uint32_t dense_q, const uint64_t *__restrict__ group_sum,
                                                          int64_t ngroups,
                                                          bool scanned, uint32_t *__restrict__ item_off,
-                                                         uint32_t *__restrict__ items, int64_t max_items) {
+                                                         uint32_t *__restrict__ items, int64_t max_items,
+                                                         const uint64_t *__restrict__ group_vote, uint32_t list,
+                                                         uint32_t *__restrict__ flags) {
     __shared__ uint64_t lds[kWavesPerBlock];
     uint64_t prefix, total;
     if (scanned) {
@@ -779,6 +800,23 @@ __global__ __launch_bounds__(kBlock) void k_item_offsets(const uint32_t *__restr
         total = t;
     }
     const uint32_t dense_total = (uint32_t)(total >> 32);
+    if (flags) {
+        uint64_t vote = 0;
+        if (scanned) {
+            vote = group_vote[ngroups];
+        } else {
+            for (uint32_t j = threadIdx.x; j < (uint32_t)ngroups; j += kBlock) vote += group_vote[j];
+            uint64_t t;
+            (void)block_excl_scan(vote, lds, &t);
+            vote = t;
+        }
+        const bool boxed = vote >= (uint64_t)list * point_off[kSub * (nbuckets - 1)];
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            flags[0] = boxed ? dense_total : 0u;
+            flags[1] = 0;
+        }
+        if (!boxed) return;
+    }
     const int64_t base = (int64_t)blockIdx.x * kItemGroup + (int64_t)threadIdx.x * kItemsPerThread;
     uint64_t v[kItemsPerThread];
     uint64_t s = 0;
@@ -796,10 +834,7 @@ __global__ __launch_bounds__(kBlock) void k_item_offsets(const uint32_t *__restr
         const uint32_t first = dense ? (uint32_t)(run >> 32) : dense_total + (uint32_t)run;
         const uint32_t cnt = dense ? (uint32_t)(v[i] >> 32) : (uint32_t)v[i];
         if (c < nbuckets) item_off[c] = first;
-        if (c == nbuckets) {
-            item_off[c] = dense_total + (uint32_t)total;
-            item_off[c + 1] = dense_total;
-        }
+        if (c == nbuckets) item_off[c] = dense_total + (uint32_t)total;
         for (uint32_t k = 0; k < cnt; ++k)
             if ((int64_t)(first + k) < max_items) items[first + k] = (uint32_t)c;
         run += v[i];
@@ -985,23 +1020,26 @@ __device__ __forceinline__ void dense_item(uint32_t lane, uint32_t qa, uint32_t 
 // than kLevel2Queries are one box. The level depends on the cell's count only
 // and the boxes on the grid, so a query's sums do not depend on how the
 // queries were split into items.
-// What the boxes save grows with the cells' lists; what they cost, the order
-// by place (22 to 28 ps a query) and the list tests, does not. So a launch is
-// boxed from kBoxedList pairs a cell on average, where even uniform points
-// gain about what they pay, and from kBoxedMean queries a cell, below which
-// cells would mostly be one box, and kBoxedQueries queries, below which the
-// longer items leave the chip idle at the end. Forward with its ordering,
-// boxed over unboxed time. Uniform points by pairs a cell: 330 queries a cell,
-// 4.6 M queries 1.48 at 122, 1.11 at 181, 1.03 at 243, 0.98 at 268, 0.95 at
-// 291, 0.87 at 449; 1,000 a cell, 8 M queries 1.38 at 120, 1.18 at 179, 1.06 to
-// 1.13 at 210, 0.98 to 1.05 at 242, 0.92 at 304, 0.76 at 443; 0.57 M queries
-// 1.05 at 254, 1.01 at 356. Clustered points, whose queries meet lists several
-// times the average: 0.98 to 1.43 at 63 to 70, 0.75 to 1.21 at 107 to 113, 0.66
-// to 0.91 at 239 to 251; 10^8 points at 254 0.89. Launches of 15 M queries or
-// more have two queries a lane otherwise: of 25.6 M, uniform ones break even at
-// 325 only (1.12 to 1.14 at 249, 1.05 at 318), clustered ones at 110 to 220,
-// and the line stays where it is for them.
-constexpr int64_t kBoxedMean = 320, kBoxedQueries = (int64_t)1 << 20, kBoxedList = 240;
+// What the boxes save grows with the lists that the queries meet; what they
+// cost, the order by place (22 to 28 ps a query) and the list tests, does not.
+// So a launch is boxed when its queries test kBoxedList1 pairs or more on
+// average, kBoxedList2 where the other walk has two queries a lane. The device
+// decides (k_item_offsets), as the average list of a cell, which the host
+// knows, says little: clustered queries meet lists of several times that. Only
+// launches of kBoxedMean queries a cell and kBoxedQueries queries ask: below,
+// cells would mostly be one box, and the longer items leave the chip idle at
+// the end; and none whose cells list fewer than kVoteList pairs on average.
+// Forward with its ordering, boxed over unboxed time, uniform and clustered
+// points in 4^3 to 64^3 cells, by the pairs a query tests: 2 to 4 M queries
+// 1.24 to 1.47 at 100 to 200, 0.84 to 1.16 at 240 to 310, 0.73 to 0.93 from 348;
+// 4 to 8 M 1.13 to 1.64 at 89 to 220, 0.90 to 1.08 at 250 to 315, 0.62 to 1.02
+// from 330; 8 to 14.7 M 1.19 to 1.48 to 177, 0.93 to 1.13 at 238 to 297, 0.63 to
+// 0.94 from 325. 15 to 35 M (two a lane) 1.02 to 1.60 to 348, 0.96 to 1.13 at 450
+// to 566, 0.60 to 1.00 from 725; 10^8 0.90 at 829. 1 to 2 M: 1.20 at 371, 0.74 to
+// 1.02 from 489. Asking costs a launch that is not boxed some 15 us (4 M uniform
+// points in 20^3 cells 335 -> 344 us; from 8 M less than the runs differ).
+constexpr int64_t kBoxedMean = 320, kBoxedQueries = (int64_t)1 << 21, kVoteList = 60;
+constexpr int64_t kBoxedList1 = 320, kBoxedList2 = 600;
 constexpr uint32_t kLevel2Queries = (uint32_t)kBoxedMean, kLevel4Queries = 1536;
 constexpr uint32_t kWholeCell = 32;  // no level: one box
 __device__ __forceinline__ uint32_t dense_level(uint32_t n) {
@@ -1097,7 +1135,6 @@ __device__ __forceinline__ uint32_t list_reaching(DenseLds &L, uint32_t wave, ui
 // a time; each wave lists the ones that reach its tiles' box, and takes the
 // list 16 candidates at a time.
 constexpr uint32_t kSlots = 4;
-constexpr int64_t kDenseLaunch = (int64_t)1 << 23;  // items of one launch
 __device__ __forceinline__ void dense_item(DenseLds &L, uint32_t wave, uint32_t lane, uint32_t qa, uint32_t qn,
                                            uint32_t n, uint32_t ja, uint32_t jb, uint32_t c, const GridParams &g,
                                            const Record *__restrict__ rec, const uint32_t *__restrict__ gids,
@@ -1213,62 +1250,60 @@ __device__ __forceinline__ void dense_item(DenseLds &L, uint32_t wave, uint32_t 
     }
 }
 
-struct CellItem {
-    uint32_t c, chunk, pa, n, ja, jb;
-    bool coarse;
-};
-
-__device__ __forceinline__ CellItem cell_item(uint32_t w, uint32_t ncells, const uint8_t *cell_coarse,
-                                              const uint32_t *cell_off, const uint32_t *point_off,
-                                              const uint32_t *item_off, const uint32_t *items) {
-    CellItem it;
-    it.c = ((ConstU32 *)items)[w];
-    it.chunk = w - ((ConstU32 *)item_off)[it.c];
-    it.pa = ((ConstU32 *)point_off)[kSub * it.c];
-    it.n = ((ConstU32 *)point_off)[it.c < ncells ? kSub * (it.c + 1) : kSub * it.c + 1] - it.pa;
-    it.ja = it.jb = 0;
-    it.coarse = false;
-    if (it.c < ncells) {
-        it.ja = ((ConstU32 *)cell_off)[it.c];
-        it.jb = ((ConstU32 *)cell_off)[it.c + 1];
-        it.coarse = __builtin_amdgcn_readfirstlane(cell_coarse[it.c]) != 0;
-    }
-    return it;
-}
-
-// first: the launch's first item (a multiple of the XCD grouping's window).
+// The dense items of a boxed launch: workgroups that fill the chip take two at
+// a time (a cell's items follow one another) until none is left. (So a launch
+// that turns out not to be boxed costs the workgroups that look and leave, not
+// one for every item.)
+constexpr uint32_t kDenseTake = 2;
 __global__ __launch_bounds__(kBlock, kDensePerSimd) void k_sample_dense(
-    GridParams g, uint32_t first, const Record *__restrict__ rec, const uint8_t *__restrict__ cell_coarse,
+    GridParams g, const Record *__restrict__ rec, const uint8_t *__restrict__ cell_coarse,
     const uint32_t *__restrict__ gids, const uint32_t *__restrict__ cell_off, const uint32_t *__restrict__ point_off,
     const uint32_t *__restrict__ keys, const uint32_t *__restrict__ order, const uint32_t *__restrict__ item_off,
-    const uint32_t *__restrict__ items, float T, float tau, float *__restrict__ out_v, float *__restrict__ out_i,
-    const float4 *__restrict__ pos, float2 *__restrict__ plan_out) {
+    const uint32_t *__restrict__ items, uint32_t *flags, float T, float tau, float *__restrict__ out_v,
+    float *__restrict__ out_i, const float4 *__restrict__ pos, float2 *__restrict__ plan_out) {
     __shared__ DenseLds L;
-    const uint32_t lane = threadIdx.x % kWave;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t tid = threadIdx.x, lane = tid % kWave;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const uint32_t ncells = (uint32_t)g.ncells;
-    const uint32_t w = first + xcd_group<kXcdDense>(blockIdx.x, gridDim.x);
-    if (w >= ((ConstU32 *)item_off)[ncells + 2]) return;
-    const CellItem it = cell_item(w, ncells, cell_coarse, cell_off, point_off, item_off, items);
-    const uint32_t nit = (it.n + kBoxedQ - 1) / kBoxedQ;
-    const uint32_t per = (it.n + nit - 1) / nit;
-    const uint32_t qa = it.pa + it.chunk * per;
-    const uint32_t left = it.pa + it.n - qa, qn = left < per ? left : per;
-    if (!it.coarse && it.ja < it.jb) {
-        if (threadIdx.x == 0) {  // the record that pads the lists
+    const uint32_t total = __builtin_amdgcn_readfirstlane(flags[0]);
+    if (total == 0) return;
+    for (;;) {
+        if (tid == 0) {
+            L.next = atomicAdd(flags + 1, kDenseTake);
+            // the record that pads the lists (a coarse cell's records may lie on it)
             L.b[0][kBlock] = L.b[1][kBlock] = L.b[2][kBlock] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
-        dense_item(L, wave, lane, qa, qn, it.n, it.ja, it.jb, it.c, g, rec, gids, keys, order, pos, T, tau, out_v,
-                   out_i, plan_out);
-        return;
+        __syncthreads();
+        const uint32_t w0 = __builtin_amdgcn_readfirstlane(L.next);
+        if (w0 >= total) return;
+        for (uint32_t w = w0; w < w0 + kDenseTake && w < total; ++w) {
+            const uint32_t c = ((ConstU32 *)items)[w], chunk = w - ((ConstU32 *)item_off)[c];
+            const uint32_t pa = ((ConstU32 *)point_off)[kSub * c];
+            const uint32_t n = ((ConstU32 *)point_off)[c < ncells ? kSub * (c + 1) : kSub * c + 1] - pa;
+            uint32_t ja = 0, jb = 0;
+            bool coarse = false;
+            if (c < ncells) {
+                ja = ((ConstU32 *)cell_off)[c];
+                jb = ((ConstU32 *)cell_off)[c + 1];
+                coarse = __builtin_amdgcn_readfirstlane(cell_coarse[c]) != 0;
+            }
+            const uint32_t nit = (n + kBoxedQ - 1) / kBoxedQ, per = (n + nit - 1) / nit;
+            const uint32_t qa = pa + chunk * per, left = pa + n - qa, qn = left < per ? left : per;
+            if (!coarse && ja < jb) {
+                dense_item(L, wave, lane, qa, qn, n, ja, jb, c, g, rec, gids, keys, order, pos, T, tau, out_v, out_i,
+                           plan_out);
+            } else {
+                // lanes are queries (an empty list leaves their sums at 0)
+                float4 p = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (tid < qn) p = pos[qa + tid];
+                float I = 0.0f, V = 0.0f;
+                if (kWave * wave < qn)
+                    walk_staged(rec, gids, ja, jb, lane, wave_records(L, wave), p.x, p.y, p.z, T, I, V);
+                if (tid < qn) write_out(I, V, tau, order[qa + tid], qa + tid, out_v, out_i, plan_out);
+            }
+            __syncthreads();  // every wave is done with the item's LDS
+        }
     }
-    // lanes are queries (an empty list leaves their sums at 0)
-    const uint32_t i = threadIdx.x;
-    float4 p = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (i < qn) p = pos[qa + i];
-    float I = 0.0f, V = 0.0f;
-    if (kWave * wave < qn) walk_staged(rec, gids, it.ja, it.jb, lane, wave_records(L, wave), p.x, p.y, p.z, T, I, V);
-    if (i < qn) write_out(I, V, tau, order[qa + i], qa + i, out_v, out_i, plan_out);
 }
 
 // One wavefront per item, by the queries n of the cell:
@@ -1290,7 +1325,9 @@ __global__ __launch_bounds__(kSampBlock, kSampPerSimd) void k_sample_cells(Query
                                                          const uint32_t *__restrict__ order,
                                                          const uint32_t *__restrict__ item_off,
                                                          const uint32_t *__restrict__ items, int64_t max_items,
-                                                         uint32_t dense_q, bool boxed, float T, float tau,
+                                                         uint32_t dense_q, const uint32_t *__restrict__ boxed_off,
+                                                         const uint32_t *__restrict__ boxed_items,
+                                                         const uint32_t *__restrict__ boxed_flags, float T, float tau,
                                                          float *__restrict__ out_v, float *__restrict__ out_i,
                                                          PlanResults pr) {
     // per wave: the records of 64 candidates, as three 1 KiB planes of
@@ -1299,9 +1336,14 @@ __global__ __launch_bounds__(kSampBlock, kSampPerSimd) void k_sample_cells(Query
     const uint32_t lane = threadIdx.x % kWave;
     const uint32_t ncells = (uint32_t)g.ncells;
     const uint32_t bid = xcd_group<kXcdItems>(blockIdx.x, gridDim.x);
-    // a boxed launch's dense items, the first of the list, are k_sample_dense's
-    const uint64_t w =
-        (uint64_t)bid * kSampWaves + threadIdx.x / kWave + (boxed ? ((ConstU32 *)item_off)[ncells + 2] : 0u);
+    // a boxed launch has its own items; the dense ones, the first of the list,
+    // are k_sample_dense's
+    const uint32_t dense = boxed_flags ? ((ConstU32 *)boxed_flags)[0] : 0u;
+    if (dense > 0) {
+        item_off = boxed_off;
+        items = boxed_items;
+    }
+    const uint64_t w = (uint64_t)bid * kSampWaves + threadIdx.x / kWave + dense;
     const uint32_t tot = ((ConstU32 *)item_off)[ncells + 1];
     const uint64_t total = tot < (uint64_t)max_items ? tot : (uint64_t)max_items;
     if (w >= total) return;
@@ -1501,82 +1543,95 @@ hipError_t launch_sample_grid(const QueryParams &q, const GridParams &g, const R
     return hipGetLastError();
 }
 
-bool boxed_launch(int64_t nq, int64_t ncells, int64_t n_pairs) {
-    return nq >= kBoxedMean * ncells && nq >= kBoxedQueries && n_pairs >= kBoxedList * ncells;
-}
-
-// Queries per dense work item for nq ordered queries on the current device:
-// 128 (two a lane) from kDenseBalance items per wave slot of the chip at 64,
-// else 64. The item list and the sampler both take it from nq, so they agree.
-static uint32_t dense_item_queries(int64_t nq) {
+static int compute_units() {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
         (void)hipGetLastError();
         cus = 256;
     }
-    const int64_t slots = (int64_t)cus * 4 * kSampPerSimd;  // 4 SIMDs a CU
+    return cus;
+}
+
+// Queries per dense work item for nq ordered queries on the current device:
+// 128 (two a lane) from kDenseBalance items per wave slot of the chip at 64,
+// else 64. The item list and the sampler both take it from nq, so they agree.
+static uint32_t dense_item_queries(int64_t nq) {
+    const int64_t slots = (int64_t)compute_units() * 4 * kSampPerSimd;  // 4 SIMDs a CU
     return nq / kWave >= (int64_t)kDenseBalance * slots ? 2u * kWave : (uint32_t)kWave;
 }
 
-hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
-                             bool boxed, hipStream_t s) {
-    if (nq <= 0) return hipSuccess;
-    const uint32_t dense_q = boxed ? kBoxedQ : dense_item_queries(nq);
+int64_t boxed_list(int64_t nq, int64_t ncells, int64_t n_pairs) {
+    if (nq < kBoxedMean * ncells || nq < kBoxedQueries || n_pairs < kVoteList * ncells) return -1;
+    return dense_item_queries(nq) == (uint32_t)kWave ? kBoxedList1 : kBoxedList2;
+}
+
+// The items of buckets of `dense_q` queries an item, into item_off and items;
+// with cell_off those of a boxed launch, if it is one.
+static hipError_t list_items(const GridParams &g, const uint32_t *point_off, uint32_t dense_q, const PointItems &it,
+                             uint32_t *item_off, uint32_t *items, int64_t max_items, const uint32_t *cell_off,
+                             uint64_t *group_vote, uint32_t list, uint32_t *flags, hipStream_t s) {
     const int64_t nbuckets = g.ncells + 1;  // cells and the outside bucket
     // buckets 0..nbuckets-1 and one empty element after them (its offset is the total)
     const int64_t ngroups = (nbuckets + 1 + kItemGroup - 1) / kItemGroup;
     const bool scanned = ngroups > kInlineGroups;
     prof_begin("cell_items", s);
     hipLaunchKernelGGL(k_item_sums, dim3((uint32_t)ngroups), dim3(kBlock), 0, s, point_off, nbuckets, dense_q,
-                       it.group_sum);
+                       it.group_sum, cell_off, group_vote);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && scanned)
         e = exclusive_scan_u64_total(it.group_sum, it.group_sum, ngroups, it.group_sum + ngroups, it.scan_work, s);
+    if (e == hipSuccess && scanned && group_vote)
+        e = exclusive_scan_u64_total(group_vote, group_vote, ngroups, group_vote + ngroups, it.scan_work, s);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_item_offsets, dim3((uint32_t)ngroups), dim3(kBlock), 0, s, point_off, nbuckets,
-                           dense_q, it.group_sum, ngroups, scanned, it.item_off, it.items, it.max_items);
+                           dense_q, it.group_sum, ngroups, scanned, item_off, items, max_items, group_vote, list,
+                           flags);
         e = hipGetLastError();
     }
     prof_end("cell_items", s);
     return e;
 }
 
-hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec,
-                                const uint8_t *cell_coarse, const uint32_t *gids, const uint32_t *cell_off,
-                                const uint32_t *keys, const uint32_t *order, const uint32_t *point_off,
-                                const PointItems &it, bool boxed, float T, float tau, float *out_v, float *out_i,
-                                const PlanResults &pr, hipStream_t s) {
-    if (q.n <= 0) return hipSuccess;
-    prof_begin("sample_points", s);
-    if (boxed) {
-        // at least the dense cells' items (the kernel leaves at their number);
-        // a launch holds fewer than 2^32 threads
-        const int64_t items = q.n / kBoxedQ + g.ncells + 2;
-        for (int64_t first = 0; first < items; first += kDenseLaunch) {
-            const int64_t blocks = items - first < kDenseLaunch ? items - first : kDenseLaunch;
-            hipLaunchKernelGGL(k_sample_dense, dim3((uint32_t)blocks), dim3(kBlock), 0, s, g, (uint32_t)first, rec,
-                               cell_coarse, gids, cell_off, point_off, keys, order, it.item_off, it.items, T, tau,
-                               out_v, out_i, pr.pos, pr.out);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-    }
-    const int64_t waves = boxed ? g.ncells + 1 : it.max_items;
-    hipLaunchKernelGGL(k_sample_cells, dim3((uint32_t)((waves + kSampWaves - 1) / kSampWaves)), dim3(kSampBlock), 0, s,
-                       q, g, rec, cell_coarse, gids, cell_off, point_off, order, it.item_off, it.items, it.max_items,
-                       dense_item_queries(q.n), boxed, T, tau, out_v, out_i, pr);
-    prof_end("sample_points", s);
+hipError_t launch_cell_items(int64_t nq, const GridParams &g, const uint32_t *point_off, const PointItems &it,
+                             hipStream_t s) {
+    if (nq <= 0) return hipSuccess;
+    return list_items(g, point_off, dense_item_queries(nq), it, it.item_off, it.items, it.max_items, nullptr, nullptr,
+                      0, nullptr, s);
+}
+
+hipError_t launch_boxed_items(const QueryParams &q, const GridParams &g, const uint32_t *cell_off,
+                              const uint32_t *keys, const uint32_t *point_off, int64_t list, const PointItems &it,
+                              const BoxedItems &b, uint32_t *order, float4 *pos, hipStream_t s) {
+    hipError_t e = list_items(g, point_off, kBoxedQ, it, b.item_off, b.items, b.max_items, cell_off, b.group_vote,
+                              (uint32_t)list, b.flags, s);
+    if (e != hipSuccess) return e;
+    prof_begin("refine_order", s);
+    hipLaunchKernelGGL(k_refine_order, dim3((uint32_t)((q.n + kRefineTile - 1) / kRefineTile)), dim3(kBlock), 0, s, q,
+                       g, b.flags, keys, order, pos);
+    prof_end("refine_order", s);
     return hipGetLastError();
 }
 
-hipError_t launch_refine_order(const QueryParams &q, const GridParams &g, const uint32_t *keys, uint32_t *order,
-                               float4 *pos, hipStream_t s) {
+hipError_t launch_sample_points(const QueryParams &q, const GridParams &g, const Record *rec,
+                                const uint8_t *cell_coarse, const uint32_t *gids, const uint32_t *cell_off,
+                                const uint32_t *keys, const uint32_t *order, const uint32_t *point_off,
+                                const PointItems &it, const BoxedItems &b, float T, float tau, float *out_v,
+                                float *out_i, const PlanResults &pr, hipStream_t s) {
     if (q.n <= 0) return hipSuccess;
-    prof_begin("refine_order", s);
-    hipLaunchKernelGGL(k_refine_order, dim3((uint32_t)((q.n + kRefineTile - 1) / kRefineTile)), dim3(kBlock), 0, s, q,
-                       g, keys, order, pos);
-    prof_end("refine_order", s);
+    prof_begin("sample_points", s);
+    if (b.item_off) {
+        hipLaunchKernelGGL(k_sample_dense, dim3((uint32_t)(compute_units() * kDensePerSimd)), dim3(kBlock), 0, s, g,
+                           rec, cell_coarse, gids, cell_off, point_off, keys, order, b.item_off, b.items, b.flags, T,
+                           tau, out_v, out_i, pr.pos, pr.out);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_sample_cells, dim3((uint32_t)((it.max_items + kSampWaves - 1) / kSampWaves)),
+                       dim3(kSampBlock), 0, s, q, g, rec, cell_coarse, gids, cell_off, point_off, order, it.item_off,
+                       it.items, it.max_items, dense_item_queries(q.n), b.item_off, b.items, b.flags, T, tau, out_v,
+                       out_i, pr);
+    prof_end("sample_points", s);
     return hipGetLastError();
 }
 

@@ -28,10 +28,10 @@ def dev_gauss(g: synth.Gaussians, device="cuda"):
     return gs.Gaussians(t(g.mean), t(g.scale), t(g.rot), t(g.value), t(g.weight))
 
 
-def with_long_lists(g: synth.Gaussians, m=260, mean=(0.5, 0.5, 0.5), scale=(0.6, 0.6, 0.6)):
+def with_long_lists(g: synth.Gaussians, m=340, mean=(0.5, 0.5, 0.5), scale=(0.6, 0.6, 0.6)):
     """g and m Gaussians of weight 1e-30 that vanish in float32 sums: they only
     lengthen the lists of the cells they reach (all of the unit box with the
-    defaults), as boxed launches (240 pairs a cell or more) need them."""
+    defaults), as boxed launches need them."""
     f = np.float32
     rep = lambda a: np.tile(np.asarray(a, f), (m, 1))
     cat = lambda a, b: np.concatenate([a, b]).astype(f)
@@ -40,9 +40,22 @@ def with_long_lists(g: synth.Gaussians, m=260, mean=(0.5, 0.5, 0.5), scale=(0.6,
 
 
 def is_boxed(run) -> bool:
-    """The library's rule for boxed launches of ordered queries."""
+    """The library's rule for boxed launches of ordered queries: 2^21 queries
+    and 320 a cell or more, 60 pairs a cell or more, and 320 pairs or more that
+    a query of the domain tests, 600 where the other walk has two queries a
+    lane. (After run.forward(), unless the first say no.)"""
     nc = run.cells[0] * run.cells[1] * run.cells[2]
-    return run.nq >= max(320 * nc, 1 << 20) and run.index.n_pairs >= 240 * nc
+    if run.nq < max(320 * nc, 1 << 21) or run.index.n_pairs < 60 * nc:
+        return False
+    cus = run.torch.cuda.get_device_properties(0).multi_processor_count
+    two_a_lane = run.nq // 64 >= 32 * cus * 4 * 7
+    tests, _ = run.gs.sample_pair_counts(run.index, run.query, run.plan,
+                                         run.gs.alloc_backward_work(run.index, run.query, "cuda"))
+    inside = run.nq
+    if run.kind == "points":
+        p = run.points_np
+        inside = int(((p >= np.asarray(run.lo, np.float32)) & (p <= np.asarray(run.hi, np.float32))).all(1).sum())
+    return tests >= (600 if two_a_lane else 320) * inside
 
 
 class Run:

@@ -1,8 +1,8 @@
-"""Boxed launches (2^20 queries and 320 a cell or more, on lists of 240 pairs a
-cell or more on average), whose plans are refined by place and whose positions
-carry the places: every way of filling and using the plan, for points, voxel
-lists and jitter, with gs_sample's outputs as the reference, bit for bit; their
-exactness; coarse cells; and more queries than a launch has threads."""
+"""Boxed launches (2^21 queries and 320 a cell or more that meet long lists),
+whose plans are refined by place and whose positions carry the places: every
+way of filling and using the plan, for points, voxel lists and jitter, with
+gs_sample's outputs as the reference, bit for bit; their exactness; coarse
+cells; and more queries than a launch has threads."""
 import numpy as np
 import pytest
 
@@ -11,13 +11,14 @@ from harness import TAU, Run, check_forward, is_boxed, log, with_long_lists
 
 pytestmark = pytest.mark.gpu
 
-DIMS = (110, 104, 106)
-N = (1 << 20) + 5003
+DIMS = (140, 130, 132)
+N = (1 << 21) + 5003
 
 
-def boxed_run(kind, cells):
-    """N queries, some of them outside the domain."""
-    g = with_long_lists(synth.random_gaussians(171, 1200, log_mu=np.log(0.03), log_sd=0.6))
+def plan_run(kind, cells, lists):
+    """N queries, some of them outside the domain, on lists of `lists` pairs and
+    more."""
+    g = with_long_lists(synth.random_gaussians(171, 1200, log_mu=np.log(0.03), log_sd=0.6), lists)
     if kind == "points":
         return Run(g, cells, kind, points=synth.random_points(172, N, -0.01, 1.01))
     nvox = DIMS[0] * DIMS[1] * DIMS[2]
@@ -44,17 +45,19 @@ def plan_parts(r):
     return p[:4 * n], p[a:a + 4 * n], p[at:at + 16 * n]
 
 
-@pytest.mark.parametrize("cells", [(13, 12, 11), (3, 2, 2)])  # 614 and 87,798 a cell: both box sizes
-@pytest.mark.parametrize("kind", ["points", "voxels", "jitter"])
-def test_a_plan_serves_every_forward(kind, cells):
-    log(f"case boxed plans, {kind}, cells {cells}")
-    r = boxed_run(kind, cells)
-    assert is_boxed(r)
+@pytest.mark.parametrize("cells", [(17, 16, 15), (3, 2, 2)])  # 515 and 175,179 a cell: both box sizes
+@pytest.mark.parametrize("kind,lists", [("points", 340), ("voxels", 340), ("jitter", 340), ("points", 70)])
+def test_a_plan_serves_every_forward(kind, lists, cells):
+    """(Lists of 70: asked, and found not to be boxed.)"""
+    log(f"case plans, {kind}, cells {cells}, lists of {lists}")
+    r = plan_run(kind, cells, lists)
     phi, inf = r.forward()
+    assert is_boxed(r) == (lists >= 320) and r.index.n_pairs >= 60 * np.prod(cells)
     sel = np.sort(np.random.default_rng(178).choice(np.arange(5, N), 20000, replace=False))
     check_forward(r, phi, inf, sel=sel, label=f"boxed {kind}")
     want = plan_parts(r)
-    assert len(np.unique(want[2].view(np.uint32).reshape(-1, 4)[:, 3])) > 8, "the places are in w"
+    places = np.unique(want[2].view(np.uint32).reshape(-1, 4)[:, 3])
+    assert (len(places) > 3) == is_boxed(r), "the places are in w"
 
     r.plan.zero_()
     r.gs.gs_plan_queries(r.query, r.grid, r.plan)
@@ -77,7 +80,7 @@ def test_boxed_coarse_cells_keep_small_gaussians_exact(cells):
     cutoff surfaces, under wide ones that make every point defined. Every
     output within the oracle's bar."""
     rng = np.random.default_rng(179)
-    nt, per = 3400, 310
+    nt, per = 3400, 620
     mean = rng.uniform(0.1, 0.9, (nt, 3))
     scale = 0.0003 * rng.uniform(1.0, 2.0, (nt, 3))
     q = rng.standard_normal((nt, 4))
@@ -93,8 +96,8 @@ def test_boxed_coarse_cells_keep_small_gaussians_exact(cells):
                         np.concatenate([rng.uniform(0.5, 1.0, nt), np.ones(nw)]).astype(f))
     log(f"case boxed coarse cells {cells}")
     r = Run(with_long_lists(g), cells, "points", points=pts)
-    assert is_boxed(r)
     phi, inf = r.forward()
+    assert is_boxed(r)
     sel = np.sort(rng.choice(len(pts), 200000, replace=False))
     _, stats = check_forward(r, phi, inf, sel=sel, label="boxed coarse cells")
     assert stats["defined"] > 0.9 * len(sel)
@@ -120,7 +123,7 @@ def test_boxed_sums_are_as_exact_as_the_unboxed_ones(flat, ratio):
     times the other launch's (150,000 pairs or more a side: sampling moves an
     rms by under 1 %)."""
     f = np.float32
-    c, n, per = 12, 64, 16400
+    c, n, per = 12, 64, 33000
     rng = np.random.default_rng(175)
     k = np.arange(n)
     cell = np.stack([k % 4 * 3 + 1, k // 4 % 4 * 3 + 1, k // 16 * 3 + 1], 1)
@@ -134,7 +137,7 @@ def test_boxed_sums_are_as_exact_as_the_unboxed_ones(flat, ratio):
     x = pts.astype(np.float64) - mean[:, None].astype(np.float64)
     u = np.einsum("nij,npi->npj", R, x) / scale[:, None].astype(np.float64)
     Q = (u * u).sum(2) / 2 * np.log2(np.e)
-    m = 260
+    m = 340
     g = with_long_lists(synth.Gaussians(mean, scale, q, np.full(n, 0.5, f), np.full(n, 4.0, f)), m)
 
     def rms(queries):
@@ -166,22 +169,22 @@ def test_boxed_sums_are_as_exact_as_the_unboxed_ones(flat, ratio):
 
 def test_boxed_launch_of_more_than_2_30_queries():
     """A launch takes fewer than 2^32 threads, and the boxed walk gives 256 to
-    every 64 queries: 2^30 + 2^20 queries, 2^20 points over and over, give
-    the 2^20 points' bits over and over (their cells hold 16,384, the level of
+    every 64 queries: 2^30 + 2^21 queries, 2^21 points over and over, give
+    the 2^21 points' bits over and over (their cells hold 32,768, the level of
     the larger counts too). About 70 GB of device memory."""
     import torch
     import paper_2607_01164_amd as gs
     from harness import dev_gauss
     if torch.cuda.get_device_properties(0).total_memory < 100 << 30:
         pytest.skip("needs 100 GB")
-    log("case 2^30 + 2^20 queries")
-    g = with_long_lists(synth.random_gaussians(176, 250, log_mu=np.log(0.1), log_sd=0.3))
-    base = torch.from_numpy(synth.random_points(177, 1 << 20)).cuda()
+    log("case 2^30 + 2^21 queries")
+    g = with_long_lists(synth.random_gaussians(176, 250, log_mu=np.log(0.1), log_sd=0.3), 650)
+    base = torch.from_numpy(synth.random_points(177, 1 << 21)).cuda()
     dg, grid = dev_gauss(g), gs.make_grid((4, 4, 4))
     index = gs.build_index(dg, grid, 0.01)
-    assert index.n_pairs >= 240 * 64
+    assert index.n_pairs >= 650 * 64  # a uniform launch's queries test as many: boxed both ways
     out = []
-    for repeats in (1, (1 << 10) + 1):
+    for repeats in (1, (1 << 9) + 1):
         pts = base.repeat(repeats, 1)
         query = gs.Query.pts(pts)
         v = torch.empty(len(pts), dtype=torch.float32, device="cuda")
