@@ -196,6 +196,12 @@ gs_status gs_sample(const gs_gaussians *gauss, const gs_index *index, const gs_q
  * query and the index's grid, unchanged since (the caller orders the two
  * streams, e.g. with an event). The outputs and the plan's contents equal
  * gs_sample's, bit for bit. Plans follow gs_plan_bytes; errors as gs_sample.
+ * A plan may be sampled again, with the same index (the same bits) or with
+ * another one on its grid. Sampling writes the plan, so calls that share one
+ * follow each other; where 2^21 queries or more meet long lists it also
+ * reorders the queries inside the quarters of cells, so a later call with
+ * another index, or its backward, may sum in another order than with a new
+ * plan (equal up to float32 rounding).
  */
 gs_status gs_plan_queries(const gs_query *query, const gs_grid *grid, void *plan, size_t plan_bytes,
                           hipStream_t stream);

@@ -73,6 +73,25 @@ def test_a_plan_serves_every_forward(kind, lists, cells):
         np.testing.assert_array_equal(i.view(np.uint32), inf.view(np.uint32), err_msg=f"after {after}")
 
 
+@pytest.mark.parametrize("kind", ["points", "voxels"])
+def test_a_plan_serves_another_index(kind):
+    """A plan that a boxed forward has reordered, sampled with an index whose
+    launches are not boxed, and with the first one again."""
+    cells = (17, 16, 15)
+    log(f"case plans, another index, {kind}")
+    r, other = plan_run(kind, cells, 340), plan_run(kind, cells, 70)
+    phi, inf = r.forward()
+    other.forward()
+    assert is_boxed(r) and not is_boxed(other)
+    other.plan = r.plan
+    v, i = planned(other)
+    sel = np.sort(np.random.default_rng(179).choice(np.arange(5, N), 20000, replace=False))
+    check_forward(other, v, i, sel=sel, label=f"another index, {kind}")
+    v, i = planned(r)
+    np.testing.assert_array_equal(v.view(np.uint32), phi.view(np.uint32))
+    np.testing.assert_array_equal(i.view(np.uint32), inf.view(np.uint32))
+
+
 @pytest.mark.parametrize("cells", [(13, 12, 11), (8, 8, 8)])
 def test_boxed_coarse_cells_keep_small_gaussians_exact(cells):
     """Cells that list a Gaussian far smaller than they are keep U (p - mu) in
