@@ -89,9 +89,10 @@ __device__ __forceinline__ void centre_offset(const Record &r, float ox, float o
 // takes it: with two queries a lane it is bound by VALU issue (10^8
 // clustered points, before they were boxed: the forward 6.6 % faster), and the
 // items of one query a lane take it too so that both give the same bits, which
-// are also the boxed walk's (stage_rows). The grid cells' walk and the query
-// rows are bound by their LDS reads; the rewrite made them 1-3 % slower, and
-// they keep U (p - mu).
+// are also the boxed walk's (stage_rows). The query rows are bound by their
+// LDS reads, and the rewrite made them 1-3 % slower; they keep U (p - mu). So
+// do the grid cells: the backward's sets are formed by it, and what rounds does
+// not grow with the cell (walk_split).
 __device__ __forceinline__ void offset_planes(float4 *buf, uint32_t lane, float ox, float oy, float oz) {
     Record r;
     r.f0 = buf[lane];
